@@ -115,8 +115,8 @@ typedef struct avl_config {
                                 register load issued), 2 sparse rows (loads past a row segment
                                 skipped); the default takes sparse rows when a segment averages
                                 below 0.6 of the register capacity; ignored by other forms;
-                            [2] resident blocks per compute unit of the FP32 1D-1V tiled count
-                                and scatter passes, 1..64 (at most what fits; the default is
+                            [2] resident blocks per compute unit of the 1D-1V count and
+                                scatter passes (four waves a block), 1..64 (at most what fits; the default is
                                 what fits);
                             [3] reserved, must be 0 */
     double B[3];         /* uniform background magnetic field (1D-3V, AVL_FP64 only; all zero

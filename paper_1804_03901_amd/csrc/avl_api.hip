@@ -16,7 +16,7 @@
 
 namespace avl {
 hipError_t launch_sort(const Geo& g, void* src, void* dst, const double* E, const RowShift* rows, double dtk,
-                       float bk, int* counts, int* offsets, int* tile_sums, int* tile_next, int* flags, bool push,
+                       float bk, int* counts, int* offsets, int* tile_sums, int* flags, bool push,
                        hipStream_t st, int phase, const int* off_old, const int* tf_old, int* tf_new);
 hipError_t launch_cells(const Geo& g, const int* offsets, int* cell, hipStream_t st);
 hipError_t launch_push(const Geo& g, void* m, const double* E, const RowShift* rows, double dtk, float bk,
@@ -61,7 +61,6 @@ hipError_t launch_fill_f64(double* p, int n, double value, hipStream_t st);
 hipError_t launch_scale_f64(double* p, int n, double s, hipStream_t st);
 int sort_blocks(const Geo& g, int phase);
 size_t sort_lds(const Geo& g);
-size_t scatter_lds(const Geo& g);
 int recon_waves_per_cu(int prec, int lds_per_cu);
 int scatter_blocks_per_cu(const Geo& g);
 int scatter_step_blocks_per_cu(const Geo& g);
@@ -128,9 +127,9 @@ int device_lds_per_cu()
     return lds;
 }
 
-// Grids of the tiled FP32 1D-1V sort passes: the blocks that fit on every
+// Grids of the 1D-1V wave sort passes: the blocks that fit on every
 // compute unit at once, at most sort_cap per compute unit when that is set.
-// A pass that is not tiled reports 0 (a block per tile) and stays 0.
+// 1D-3V, which has no wave passes, reports 0.
 void sort_launch_shapes(Geo& g)
 {
     const int cus = device_cus();
@@ -219,12 +218,29 @@ int make_geo(const avl_config* c, Geo* g)
         const double span = per_row > 0 ? (double)kCountTile / per_row : 1.0;
         int64_t want = (int64_t)(std::ceil(span) + 3) * c->nx;
         want = std::max<int64_t>(want, 4 * (int64_t)c->nx);
+        // one more row, which a window that follows the kick asks for, where it
+        // fits in what the FP32 1D-1V form holds anyway
+        if (want + c->nx <= kCountTile) want += c->nx;
+        if (g->magnetic) {
+            // the window also covers the neighbouring vy and vz planes a
+            // gyration reaches: a band at each, or all the rows between
+            const int64_t s1 = c->nv[0] + 1, s2 = s1 * (c->nv[1] + 1);
+            const bool y = c->B[0] != 0.0 || c->B[2] != 0.0, z = c->B[0] != 0.0 || c->B[1] != 0.0;
+            want = std::min((y ? 3 : 1) * (z ? 3 : 1) * want, want + 2 * ((y ? s1 : 0) + (z ? s2 : 0)) * c->nx);
+        }
         want = std::min<int64_t>(want, std::max<int64_t>(8192, 4 * (int64_t)c->nx));
         g->hist_bins = (int)want;
-        // the step's scatter (2048-marker tiles, a row or two of buckets in
-        // the dense rows) keeps three rows: a tile inside one row and its
-        // neighbours, which leaves room for five blocks per CU
-        g->sbins = (int)std::min<int64_t>(g->hist_bins, std::max<int64_t>(3 * (int64_t)c->nx, kSortTile));
+        // 1D-1V: the box of columns and rows a wave's tile of 512 markers lands
+        // in (three rows, one more for every row they span; a power of two of
+        // columns), and at least an FP32 tile's implied buckets
+        if (c->vdim == 1) {
+            const double tile = 512.0, ppc = std::max(1e-3, (double)c->n_markers / ((double)rows * c->nx));
+            const double width = std::min((double)c->nx, tile / ppc + 4.0 + 4.0 * (double)g->gam);
+            int w = 64;
+            while (w < width && w < c->nx) w <<= 1;
+            const int rowspan = (int)std::min(64.0, tile / (ppc * c->nx));
+            g->wbins = std::min(4096, std::max(512, std::min(w, c->nx) * (3 + rowspan)));
+        }
     }
     // reconstruction decomposition
     if (c->vdim == 1) {
@@ -279,9 +295,9 @@ void make_layout(const avl_config* c, const Geo& g, Layout* L)
     // run offsets and tile-start buckets of each marker buffer's order
     L->offsets[0] = take(sizeof(int) * (nbt + 1));
     L->offsets[1] = take(sizeof(int) * (nbt + 1));
-    L->tfirst[0] = take(sizeof(int) * (n / 2048 + 2));
-    L->tfirst[1] = take(sizeof(int) * (n / 2048 + 2));
-    L->tile_sums = take(sizeof(int) * 2 * (ntiles + 64));   // two parities of per-tile totals
+    L->tfirst[0] = take(sizeof(int) * (n / kTfStride + 2));
+    L->tfirst[1] = take(sizeof(int) * (n / kTfStride + 2));
+    L->tile_sums = take(sizeof(int) * (ntiles + 64));       // per-tile totals
     L->fgrid = take(esz * cells);
     L->rho_part = take(sizeof(double) * (size_t)std::max(1, g.nchunk) * g.nx);
     L->rho_slices = take(sizeof(double) * (size_t)kMaxFieldSlices * g.nx);
@@ -310,7 +326,9 @@ void fit_lds(Geo* g, int lds)
     int bins = (lds - fixed) / 4;
     bins = (bins >> g->lognx) << g->lognx;
     if (g->hist_bins > bins) g->hist_bins = bins;
-    if (g->sbins > g->hist_bins) g->sbins = g->hist_bins;
+    // the wave kernels' windows: four waves a block
+    const int wbins = std::max(512, ((lds - fixed) / 16) & ~3);
+    if (g->wbins > wbins) g->wbins = wbins;
 }
 
 }  // namespace
@@ -510,10 +528,6 @@ int do_sort(avl_handle* h, bool push, double kick)
     void* dst = marker_view(h, 1 - h->cur);
     const double dtk = g.dt * kick;
     const float bk = g.bscale * (float)kick;
-    // per-scan-tile totals alternate between two halves with the buffer parity
-    const size_t tstride = ((size_t)g.nb + 1 + kScanTile - 1) / kScanTile + 64;
-    int* tcur = h->tile_sums + (size_t)h->cur * tstride;
-    int* tnext = h->tile_sums + (size_t)(1 - h->cur) * tstride;
     // FP32 1D-1V markers in a sorted order carry implied cells
     const bool impl = implied_cells(h) && h->sorted;
     const int* off_old = impl ? h->offs[h->cur] : nullptr;
@@ -522,17 +536,17 @@ int do_sort(avl_handle* h, bool push, double kick)
     int* tf_new = h->tfirst[1 - h->cur];
     {
         Timer t(h, AVL_K_PUSH_COUNT, true);
-        AVL_TRY(launch_sort(g, src, dst, h->E, h->rows, dtk, bk, h->counts, off_new, tcur, tnext, h->flags,
+        AVL_TRY(launch_sort(g, src, dst, h->E, h->rows, dtk, bk, h->counts, off_new, h->tile_sums, h->flags,
                             push, h->st, 0, off_old, tf_old, tf_new));
     }
     {
         Timer t(h, AVL_K_SCAN);
-        AVL_TRY(launch_sort(g, src, dst, h->E, h->rows, dtk, bk, h->counts, off_new, tcur, tnext, h->flags,
+        AVL_TRY(launch_sort(g, src, dst, h->E, h->rows, dtk, bk, h->counts, off_new, h->tile_sums, h->flags,
                             push, h->st, 1, off_old, tf_old, tf_new));
     }
     {
         Timer t(h, AVL_K_SCATTER, true);
-        AVL_TRY(launch_sort(g, src, dst, h->E, h->rows, dtk, bk, h->counts, off_new, tcur, tnext, h->flags,
+        AVL_TRY(launch_sort(g, src, dst, h->E, h->rows, dtk, bk, h->counts, off_new, h->tile_sums, h->flags,
                             push, h->st, 2, off_old, tf_old, tf_new));
     }
     h->cur = 1 - h->cur;
@@ -620,10 +634,6 @@ int load_markers(avl_handle* h, const double* x, const double* v, const double* 
     const int total = g.n;
     const size_t nbt = (size_t)g.nb + 1;
     AVL_TRY(hipMemsetAsync(h->counts, 0, sizeof(int) * nbt, h->st));
-    {
-        const size_t ntiles = (nbt + kScanTile - 1) / kScanTile;
-        AVL_TRY(hipMemsetAsync(h->tile_sums, 0, sizeof(int) * 2 * (ntiles + 64), h->st));
-    }
     AVL_TRY(hipMemcpyAsync(h->offs[0] + nbt, &total, sizeof(int), hipMemcpyHostToDevice, h->st));
     AVL_TRY(hipMemcpyAsync(h->offs[1] + nbt, &total, sizeof(int), hipMemcpyHostToDevice, h->st));
     if (fresh) AVL_TRY(hipMemsetAsync(h->ctr, 0, sizeof(long long), h->st));
@@ -640,6 +650,16 @@ int load_markers(avl_handle* h, const double* x, const double* v, const double* 
     if ((rc = do_sort(h, false, 1.0))) return rc;
     if ((rc = do_recon(h, nullptr))) return rc;
     if ((rc = do_field(h, nullptr, false, nullptr))) return rc;
+    if (g.vdim == 1) {
+        // which sort kernels the steps take (results do not depend on it): the
+        // loaded field's largest kick, in velocity cells
+        std::vector<double> E(g.nx);
+        AVL_TRY(hipMemcpyAsync(E.data(), h->E, sizeof(double) * g.nx, hipMemcpyDeviceToHost, h->st));
+        AVL_TRY(hipStreamSynchronize(h->st));
+        h->g.follow = 0;
+        for (double e : E)
+            if (std::fabs(e * (g.qm * g.dt * g.inv_dv[0])) >= 1.0) h->g.follow = 1;
+    }
     return AVL_OK;
 }
 
@@ -736,7 +756,7 @@ int avl_init(const avl_config* cfg, void* workspace, size_t ws_bytes, void* stre
             std::fprintf(stderr,
                          "[avl] lds limit %d B, recon cap %d, hist bins %d, rc %d, chunks %d, strips %d, "
                          "recon waves per CU %d\n",
-                         lds, h->g.cap, h->g.hist_bins, h->g.rc, h->g.nchunk, h->g.nstrip,
+                         lds, h->g.cap, h->g.prec ? h->g.wbins : h->g.hist_bins, h->g.rc, h->g.nchunk, h->g.nstrip,
                          h->g.vdim == 1 ? recon_waves_per_cu(h->g.prec, device_lds_per_cu()) : 0);
     }
     if (hipMemsetAsync(h->flags, 0, sizeof(int), h->st) != hipSuccess || (rc = upload_tables(h)) != AVL_OK) {
@@ -1079,7 +1099,7 @@ struct avl_batch {
     int* pre;                   // device, BPRE_KINDS x (n+1)
     int tot[BPRE_KINDS];
     int prec, kahan, max_nx;
-    size_t lds, lds_scatter;
+    size_t lds;
     hipGraphExec_t gexec[2];
     hipStream_t cap_st;
     bool graph_ok;
@@ -1133,7 +1153,7 @@ int batch_launch(avl_batch* b, int cur, hipStream_t st)
 {
     AVL_TRY(launch_sort_batch(b->prec, b->tab, b->pre, b->n, b->tot[BPRE_COUNT], b->lds, cur, st, 0));
     AVL_TRY(launch_sort_batch(b->prec, b->tab, b->pre, b->n, b->tot[BPRE_SCAN], b->lds, cur, st, 1));
-    AVL_TRY(launch_sort_batch(b->prec, b->tab, b->pre, b->n, b->tot[BPRE_SCATTER], b->lds_scatter, cur, st, 2));
+    AVL_TRY(launch_sort_batch(b->prec, b->tab, b->pre, b->n, b->tot[BPRE_SCATTER], b->lds, cur, st, 2));
     // the sparse-row kernels when every instance with markers has sparse rows
     bool sparse = true;
     for (avl_handle* hi : b->h)
@@ -1215,7 +1235,6 @@ int avl_batch_init(const avl_config* cfgs, int32_t count, void* workspace, size_
     b->kahan = (cfgs[0].options & AVL_OPT_KAHAN32) ? 1 : 0;
     b->max_nx = 0;
     b->lds = 0;
-    b->lds_scatter = 0;
     for (int i = 0; i < count; ++i) {
         avl_handle* h = b->h[i];
         const Geo& g = h->g;
@@ -1233,9 +1252,7 @@ int avl_batch_init(const avl_config* cfgs, int32_t count, void* workspace, size_
             I.offsets[p] = h->offs[p];
             I.tfirst[p] = h->tfirst[p];
         }
-        const size_t tstride = ((size_t)g.nb + 1 + kScanTile - 1) / kScanTile + 64;
-        I.tsum[0] = h->tile_sums;
-        I.tsum[1] = h->tile_sums + tstride;
+        I.tsum = h->tile_sums;
         I.fgrid = h->fgrid;
         I.rho_part = h->rho_part;
         I.rho_slices = h->rho_slices;
@@ -1255,7 +1272,6 @@ int avl_batch_init(const avl_config* cfgs, int32_t count, void* workspace, size_
                                                                                        k >= BPRE_RECON ? items[k] : 0);
         b->max_nx = std::max(b->max_nx, g.nx);
         b->lds = std::max(b->lds, sort_lds(g));
-        b->lds_scatter = std::max(b->lds_scatter, scatter_lds(g));
     }
     for (int k = 0; k < BPRE_KINDS; ++k) b->tot[k] = pre[(size_t)k * (count + 1) + count];
     b->tab = (BInst*)(ws + tab_off);
@@ -1906,12 +1922,11 @@ extern "C" int avl_reconstruct_noalloc(const avl_config* cfg, void* stream, cons
                           64 * (3 + g.vdim);
     const size_t nbt = (size_t)g.nb + 1;
     const size_t ntiles = (nbt + kScanTile - 1) / kScanTile;
-    const size_t tstride = ntiles + 64;
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return o; };
     const size_t o_m0 = take(mbytes), o_m1 = take(mbytes);
     const size_t o_counts = take(sizeof(int) * nbt), o_offsets = take(sizeof(int) * (nbt + 1));
-    const size_t o_tsum = take(sizeof(int) * 2 * tstride);
+    const size_t o_tsum = take(sizeof(int) * (ntiles + 64));
     const size_t o_rho = take(sizeof(double) * (size_t)std::max(1, g.nchunk) * g.nx);
     const size_t o_flags = take(sizeof(int));
     if (off > (size_t)AVL_NOALLOC_SCRATCH_BYTES) return AVL_ESIZE;
@@ -1947,10 +1962,9 @@ extern "C" int avl_reconstruct_noalloc(const avl_config* cfg, void* stream, cons
     double* rho_part = (double*)(base + o_rho);
     int* flags = (int*)(base + o_flags);
     // the array keeps the previous call's contents: clear what the passes
-    // accumulate into (counts, both halves of the tile totals, flags) and set
+    // accumulate into (counts, flags) and set
     // the end offset, all with kernels (no memset or host copy)
     AVL_TRY(fill_int(counts, nbt, 0, st));
-    AVL_TRY(fill_int(tsum, 2 * tstride, 0, st));
     AVL_TRY(fill_int(flags, 1, 0, st));
     AVL_TRY(fill_int(offsets + nbt, 1, g.n, st));
     const size_t n = (size_t)g.n;
@@ -1964,8 +1978,7 @@ extern "C" int avl_reconstruct_noalloc(const avl_config* cfg, void* stream, cons
     void* src = g.prec == AVL_FP64 ? (void*)&m64[0] : (void*)&m32[0];
     void* dst = g.prec == AVL_FP64 ? (void*)&m64[1] : (void*)&m32[1];
     for (int phase = 0; phase < 3; ++phase)
-        AVL_TRY(launch_sort(g, src, dst, nullptr, nullptr, g.dt, g.bscale, counts, offsets, tsum, tsum + tstride,
-                            flags, false, st, phase, nullptr, nullptr, nullptr));
+        AVL_TRY(launch_sort(g, src, dst, nullptr, nullptr, g.dt, g.bscale, counts, offsets, tsum, flags, false, st, phase, nullptr, nullptr, nullptr));
     if (g.vdim == 1) AVL_TRY(launch_recon(g, dst, offsets, f_out, D_out, rho_part, st));
     else AVL_TRY(launch_recon3(g, dst, offsets, f_out, D_out, rho_part, nullptr, st));
     return AVL_OK;

@@ -30,9 +30,11 @@ constexpr int kCountMPT64 = 12;                           // the same for the FP
 constexpr int kCountTile = kSortThreads * kCountMPT;      // the larger count tile (window sizing)
 template <int PREC> constexpr int count_mpt() { return PREC ? kCountMPT : kCountMPT64; }
 constexpr int count_tile_size(int prec) { return kSortThreads * (prec ? kCountMPT : kCountMPT64); }
-constexpr int kScanThreads = 256;
-constexpr int kScanItems = 16;
+constexpr int kScanThreads = 1024;
+constexpr int kScanItems = 4;
 constexpr int kScanTile = kScanThreads * kScanItems;
+constexpr int kTfLog = 8;                                 // the scan records the bucket of every 2^kTfLog-th position
+constexpr int kTfStride = 1 << kTfLog;
 constexpr int kReconCols = kWave - 1;                     // target columns per reconstruct wave
 constexpr int kDiagCap = 4096;                            // per-step diagnostics ring
 constexpr int kFieldThreads = 1024;                      // threads of a field-solve block
@@ -52,14 +54,15 @@ struct Geo {
     int rc;              // target velocity rows per reconstruct chunk (1D-1V)
     int nchunk, nstrip;  // reconstruct chunks along v and column strips along x
     int hist_bins;       // LDS histogram bins per sort block
-    int sbins;           // LDS histogram bins of the step's scatter (FP32 1D-1V), at most hist_bins
+    int follow;          // 1D-1V: the loaded state's kicks reach a velocity cell
+    int wbins;           // 1D-1V: LDS bins of a wave's window in the count and scatter
     int cap;             // markers staged in LDS per reconstruct wave
     int jpad, jrange;    // FP32 1D-3V: x-velocity dual index stored with offset jpad, range jrange
     int kahan;           // FP32 form: compensated FP32 accumulation instead of FP64 accumulators
-    int sblocks;         // blocks of the tiled scatter (FP32 1D-1V): the resident capacity; 0 = a tile per block
-    int sblocks_step;    // blocks of the step's scatter (FP32 1D-1V): its resident capacity
-    int cblocks;         // blocks of the count pass: its resident capacity; 0 = a tile per block
-    int sort_cap;        // at most this many resident blocks per CU in the tiled sort passes (0: no limit)
+    int sblocks;         // blocks of the wave scatter with identities (1D-1V): its resident capacity
+    int sblocks_step;    // blocks of the wave scatter without: its resident capacity
+    int cblocks;         // blocks of the wave count: its resident capacity
+    int sort_cap;        // at most this many resident blocks per CU in the wave sort passes (0: no limit)
     int rform;           // FP32 1D-1V reconstruction rows: 0 chosen from the shape, 1 dense, 2 sparse
     int magnetic;        // 1D-3V FP64 with a background magnetic field: Boris push
     double B[3];         // background magnetic field
@@ -118,7 +121,7 @@ struct BInst {
     int* counts;
     int* offsets[2];           // run offsets of the order of marker buffer p
     int* tfirst[2];            // bucket of every 2048th position of that order (implied FP32 cells)
-    int* tsum[2];              // per-scan-tile totals, by buffer parity
+    int* tsum;                 // per-scan-tile totals
     void* fgrid;
     double* rho_part;
     double* rho_slices;
@@ -349,42 +352,40 @@ __device__ __forceinline__ void push32(const Geo& g, const float2* sE, const Row
     b = bn;
 }
 
-// The new buckets of K 1D-1V FP32-form markers after push32, without the
-// markers themselves or the flags (for a pass whose markers are pushed again,
-// with the same field, by a pass that raises them).  Every marker reads the
-// table's row shift; the FP32 formula is formed only in a branch, which a
-// wave enters when one of its markers lies beyond the table.  The bucket is
-// bucket32 of push32's clamped cell index, bit for bit.
+// The new rows and columns of K 1D-1V FP32-form markers after push32, without
+// the markers themselves or the flags (for a pass whose markers are pushed
+// again, with the same field, by a pass that raises them).  Every marker reads
+// the table's row shift; the FP32 formula is formed only in a branch, which a
+// wave enters when one of its markers lies beyond the table.  Row and column
+// are those of push32's clamped cell index wherever that has a bucket (the
+// lower clamp of push32 cannot bring a row into range, the upper one can).
 template <int K>
-__device__ __forceinline__ void push32_buckets(const Geo& g, const float2* sE, const RowShift* rows,
-                                               const int* cell, const float* a, const float* b, int* bkt)
+__device__ __forceinline__ void push32_cells(const Geo& g, const float2* sE, const RowShift* rows,
+                                             const int* cell, const float* a, const float* b, int* row, int* col)
 {
-    int ix[K], jx[K], whole[K];
+    int ix[K], whole[K];
     float bn[K], frac[K];
     bool beyond = false;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         int rest;
-        kick32<1>(g, sE, cell[k], a[k], b[k], ix[k], jx[k], rest, bn[k]);
-        const RowShift rs = rows[min(max(jx[k], 0), g.nv[0])];
+        kick32<1>(g, sE, cell[k], a[k], b[k], ix[k], row[k], rest, bn[k]);
+        const RowShift rs = rows[min(max(row[k], 0), g.nv[0])];
         whole[k] = rs.whole;
         frac[k] = rs.frac;
-        beyond |= !(jx[k] >= 0 && jx[k] <= g.nv[0]);
+        beyond |= !(row[k] >= 0 && row[k] <= g.nv[0]);
     }
     if (beyond) {
 #pragma unroll
         for (int k = 0; k < K; ++k)
-            if (!(jx[k] >= 0 && jx[k] <= g.nv[0])) row_shift32(g, jx[k], whole[k], frac[k]);
+            if (!(row[k] >= 0 && row[k] <= g.nv[0])) row_shift32(g, row[k], whole[k], frac[k]);
     }
     const int lim = row_limit32(g);
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         float an = a[k];
-        const int nix = drift32(g, ix[k], an, bn[k], whole[k], frac[k]);
-        // rows below 0 and from nrow on have no bucket; the lower clamp of
-        // push32 cannot bring a row into range, the upper one can
-        const int jc = min(jx[k], lim);
-        bkt[k] = (unsigned)jc < (unsigned)g.nrow ? (int)((unsigned)jc << g.lognx) + nix : g.nb;
+        col[k] = drift32(g, ix[k], an, bn[k], whole[k], frac[k]);
+        row[k] = min(row[k], lim);
     }
 }
 

@@ -2,31 +2,41 @@
 //
 // One step's sort is three passes over the markers:
 //   count   : (optionally) push each marker, find its new bucket, and count it;
-//   scan    : exclusive prefix sum of the bucket counts -> run offsets;
+//   scan    : exclusive prefix sum of the bucket counts -> run offsets (the
+//             totals of its tiles first, where there are more than a few: added
+//             up in the count they were atomics of every wave on a few cache
+//             lines, 99 us a count of 16.8M markers instead of 31);
 //   scatter : push again (bit-identical arithmetic), claim a slot in the run,
 //             and write the marker to its sorted position in the other buffer.
 // Pushing twice instead of storing pushed positions between the passes saves
 // a full write+read of the position/velocity streams; the push is a few
 // flops per marker against 16-40 bytes of traffic.
 //
-// Counting uses integer atomics only.  A block's markers are contiguous in the
-// previous sorted order, so after the push they land in a few neighbouring
-// bucket rows; each block keeps a histogram of those rows in LDS and issues
-// one global atomic per touched bucket.  Markers whose bucket falls outside
-// that window (large velocity jumps) use one global atomic each.  The scatter
-// uses the counts array itself as a descending cursor, which leaves it zeroed
-// for the next step.
+// Counting uses integer atomics only.  Consecutive markers of the previous
+// order land in few buckets after the push, so a wave (1D-1V) or a block
+// (1D-3V, and kicks of velocity cells) counts its markers in an LDS window of
+// the buckets it expects and issues one global atomic per touched bucket.  The
+// windows follow the markers: by the drift and kick of the tile, by the kick
+// column by column, or over the planes a gyration reaches.  Markers that miss
+// the window use one global atomic each, those of the overflow bucket one a
+// tile: with kicks of up to 8 velocity cells (13.5M FP64 markers, 512 x 6600) a
+// window of the old rows alone sent nearly every marker to memory, and the count
+// took 4.6 ms and the scatter 1.2 ms instead of 59 and 208 us; with a fifth of
+// the markers gyrating outside the grid (1.8M markers) the overflow bucket's
+// atomics took the scatter from 56 us to 2.4 ms.  The scatter uses the counts
+// array itself as a descending cursor, which leaves it zeroed for the next step.
 //
 // Implied cells (FP32 1D-1V).  In that form a marker's cell index equals its
 // bucket whenever its cloud touches the grid, and once sorted, a marker's
 // bucket is the run its position falls in.  So the scatter stores the cell
 // index only for markers of the overflow bucket, and the next sort recovers
 // every other cell from the previous run offsets: per tile, the starts of the
-// runs inside it are marked in LDS and a block-wide running maximum fills in
-// the rest (the scan also records the bucket of every kTfStride-th position,
-// where each tile starts).  That is 4 bytes a marker less to read in the count
+// runs inside it are marked in LDS and a running maximum over the wave (or
+// block) fills in the rest (the scan also records the bucket of every
+// kTfStride-th position, where each tile starts).  That is 4 bytes a marker less to read in the count
 // and the scatter and to write in the scatter.
 #include <algorithm>
+#include <type_traits>
 
 #include "avl_device.h"
 
@@ -202,9 +212,8 @@ template <int VD, int K> struct Group<1, VD, K> {
 // ---------------------------------------------------------------------------
 // Implied cells: the previous order's buckets of one tile's positions.
 // ---------------------------------------------------------------------------
-constexpr int kTfLog = 11;                   // the scan records the bucket of every 2^kTfLog-th position
-constexpr int kTfStride = 1 << kTfLog;
-static_assert(kSortTile == kTfStride && kCountTile % kTfStride == 0, "tiles start at recorded positions");
+constexpr int kNoBucket = 0x7fffffff;        // past the last marker
+static_assert(kSortTile % kTfStride == 0 && kCountTile % kTfStride == 0, "tiles start at recorded positions");
 
 // The order the markers are in, for implied cells: its run offsets (nb + 2
 // entries) and the bucket of every kTfStride-th position.  off == nullptr:
@@ -214,26 +223,7 @@ struct Prev {
     const int* tfirst;
 };
 
-// Run offsets of tile_buckets' first pass, loaded ahead of the tile: b0, the
-// run that holds the tile's first position, and the bounds of run b0 + 1 + t
-// for thread t (zero past the last run).
-struct TbAhead {
-    int b0, lo, hi;
-};
-
 __device__ __forceinline__ int tile_first_run(const Prev& pv, int base) { return pv.tfirst[base >> kTfLog]; }
-
-__device__ __forceinline__ TbAhead tile_runs_ahead(const Geo& g, const Prev& pv, int b0)
-{
-    TbAhead a{b0, 0, 0};
-    // clamped: tiles past the start of the overflow run load this too
-    const int b = min(max(b0, 0), g.nb) + 1 + (int)threadIdx.x;
-    if (b < g.nb) {
-        a.lo = pv.off[b];
-        a.hi = pv.off[b + 1];
-    }
-    return a;
-}
 
 // Buckets of the positions [base, end) of a tile (base a multiple of
 // kTfStride, end at most the start of the overflow run): the largest b with
@@ -241,17 +231,13 @@ __device__ __forceinline__ TbAhead tile_runs_ahead(const Geo& g, const Prev& pv,
 // kSortThreads SL ints of LDS, free on entry) and gets their buckets in bk[]
 // (undefined past end); with WRITE they are also left in map for other
 // threads, after a barrier.  s_aux: kSortThreads / kWave + 1 ints of LDS.
-// AHEAD: the first pass takes b0 and its offsets from ah instead of loading them.
-template <int SL, bool WRITE, bool AHEAD = false>
+template <int SL, bool WRITE>
 __device__ __forceinline__ void tile_buckets(const Geo& g, const Prev& pv, int base, int end, int* map, int* s_aux,
-                                             int (&bk)[SL], const TbAhead& ah = TbAhead{0, 0, 0})
+                                             int (&bk)[SL])
 {
     static_assert(SL % 4 == 0, "slots are cleared and read as 16-byte vectors");
     const int tid = threadIdx.x;
-    const int b0 = AHEAD ? ah.b0 : tile_first_run(pv, base);   // the run that holds position base
-    // the LDS is the previous tile's histogram, which its last stores may
-    // still be reading (a block walks several tiles)
-    __syncthreads();
+    const int b0 = tile_first_run(pv, base);       // the run that holds position base
 #pragma unroll
     for (int k = 0; k < SL; k += 4) *reinterpret_cast<int4*>(map + tid * SL + k) = make_int4(-1, -1, -1, -1);
     if (tid == 0) map[0] = b0;
@@ -261,14 +247,8 @@ __device__ __forceinline__ void tile_buckets(const Geo& g, const Prev& pv, int b
         const int b = bs + tid;
         int lo = end;
         if (b < g.nb) {
-            int hi;
-            if (AHEAD && bs == b0 + 1) {
-                lo = ah.lo;
-                hi = ah.hi;
-            } else {
-                lo = pv.off[b];
-                hi = pv.off[b + 1];
-            }
+            lo = pv.off[b];
+            const int hi = pv.off[b + 1];
             if (lo < hi && lo > base && lo < end) map[lo - base] = b;
         }
         if (tid == kSortThreads - 1) s_aux[kSortThreads / kWave] = (b < g.nb && lo < end) ? 1 : 0;
@@ -308,20 +288,140 @@ __device__ __forceinline__ void tile_buckets(const Geo& g, const Prev& pv, int b
     }
 }
 
-// The LDS window of a sort block: bucket rows around the rows of the block's
-// first and last marker (which bound the block's rows, the input being
-// sorted), widened by one row each way, at most maxbins buckets.
-__device__ __forceinline__ void set_window(const Geo& g, int b0, int b1, int* lo_out, int* nb_out, int maxbins)
+// The LDS window of a sort block: the buckets its markers are expected to
+// land in, counted in LDS slots 0 .. nbw-1.  The block's first and last marker
+// (before the push) bound its old bucket rows [r0, r1], the input being sorted.
+//  * plain: rows r0 - 1 .. r1 + 1, where every marker lands that is kicked by
+//    less than one velocity cell.
+//  * shear (the field's largest kick reaches a velocity cell): the rows follow
+//    the kick.  Slot (r, column i) stands for row lo + r + S(i), S(i) the whole
+//    part of the kick at the column markers of these rows drift to i from, so
+//    a few rows hold the tile's markers however large a smooth kick is.
+//  * bands (1D-3V with a magnetic field): a gyration moves a marker to
+//    neighbouring vy and vz planes, rows s1 (one vy plane) and s2 (one vz
+//    plane) apart; the window is a plain one at each of those planes.
+// The overflow bucket has an LDS counter of its own; any other bucket outside
+// the window takes one global atomic a marker.
+struct Window {
+    int lo, rows, nbw;      // first row, rows a band, slots (all bands)
+    int shear, drift;       // rows follow the kick; the columns these rows drift by
+    int nb1, nb2, s1, s2;   // bands along vy and vz planes and the rows between them
+};
+
+template <int PREC, int VD>
+__device__ __forceinline__ Window set_window(const Geo& g, int b0, int b1, int shear, const RowShift* rows, int maxbins)
 {
+    Window w;
+    // the same in every thread: scalar registers and scalar branches
+    b0 = __builtin_amdgcn_readfirstlane(b0);
+    b1 = __builtin_amdgcn_readfirstlane(b1);
+    shear = __builtin_amdgcn_readfirstlane(shear);
     int r0 = (b0 >= g.nb ? g.nrow - 1 : b0 >> g.lognx);
     int r1 = (b1 >= g.nb ? g.nrow - 1 : b1 >> g.lognx);
-    int lo = min(r0, r1) - 1, hi = max(r0, r1) + 1;
+    // sheared rows get one more: S is the kick at a cell centre near the marker's position
+    int lo = min(r0, r1) - 1, hi = max(r0, r1) + 1 + (shear ? 1 : 0);
+    const int maxrows = maxbins >> g.lognx;
+    w.shear = shear;
+    w.drift = 0;
+    w.nb1 = w.nb2 = 1;
+    w.s1 = w.s2 = 0;
+    if (shear) {
+        const int jx = VD == 1 ? r0 : r0 % (g.nv[0] + 1);
+        if constexpr (PREC == 1) w.drift = rows[min(jx, g.nv[0])].whole;
+        else w.drift = (int)floor((g.vmin[0] + (jx - 0.5) * g.dv[0]) * g.dt * g.inv_dx);
+    }
+    if constexpr (PREC == 0 && VD == 3) {
+        if (g.magnetic) {
+            // vy changes under B along x or z, vz under B along x or y
+            const int s1 = g.nv[0] + 1, s2 = s1 * (g.nv[1] + 1);
+            const int d1 = (g.B[0] != 0.0 || g.B[2] != 0.0) ? s1 : 0, d2 = (g.B[0] != 0.0 || g.B[1] != 0.0) ? s2 : 0;
+            const int n1 = d1 ? 3 : 1, n2 = d2 ? 3 : 1, len = min(hi - lo + 1, maxrows / (n1 * n2));
+            if (len > 0 && len <= s1 && 2 * d1 + len <= s2) {
+                w.lo = lo - d1 - d2;
+                w.rows = len;
+                w.nb1 = n1;
+                w.nb2 = n2;
+                w.s1 = s1;
+                w.s2 = s2;
+                w.nbw = (len * n1 * n2) << g.lognx;
+                return w;
+            }
+            lo -= d1 + d2;       // bands that would overlap: one window over all of them
+            hi += d1 + d2;
+        }
+    }
     lo = max(lo, 0);
     hi = min(hi, g.nrow - 1);
-    int maxrows = maxbins >> g.lognx;
     if (hi - lo + 1 > maxrows) hi = lo + maxrows - 1;
-    *lo_out = lo << g.lognx;
-    *nb_out = (hi - lo + 1) << g.lognx;
+    w.lo = lo;
+    w.rows = hi - lo + 1;
+    w.nbw = w.rows << g.lognx;
+    return w;
+}
+
+// The whole part of the kick, in velocity cells, at column i.
+template <int PREC>
+__device__ __forceinline__ int kick_rows(const Geo& g, const typename MarkersOf<PREC>::E* sE, int i, double dtk)
+{
+    if constexpr (PREC == 1) return (int)fminf(fmaxf(floorf(sE[i].x), -1e6f), 1e6f);
+    else return (int)fmin(fmax(floor(g.qm * sE[i] * dtk * g.inv_dv[0]), -1e6), 1e6);
+}
+
+// Window slot of bucket b, negative for any other (the overflow bucket, which
+// lies past every window, among them).
+template <int PREC, int VD>
+__device__ __forceinline__ int window_slot(const Geo& g, const Window& w, const typename MarkersOf<PREC>::E* sE, int b,
+                                           double dtk)
+{
+    if (w.shear || (VD == 3 && PREC == 0 && w.nb1 * w.nb2 > 1)) {
+        const int col = b & (g.nx - 1);
+        int d = (b >> g.lognx) - w.lo, q = 0;
+        if (VD == 3 && PREC == 0 && w.nb1 * w.nb2 > 1) {
+            if (w.nb2 > 1) {
+                const int q2 = (d >= w.s2) + (d >= 2 * w.s2);
+                d -= q2 * w.s2;
+                q = q2 * w.nb1;
+            }
+            if (w.nb1 > 1) {
+                const int q1 = (d >= w.s1) + (d >= 2 * w.s1);
+                d -= q1 * w.s1;
+                q += q1;
+            }
+        } else {
+            d -= kick_rows<PREC>(g, sE, (col - w.drift) & (g.nx - 1), dtk);
+        }
+        return b < g.nb && (unsigned)d < (unsigned)w.rows ? ((q * w.rows + d) << g.lognx) + col : -1;
+    }
+    const int rel = b - (w.lo << g.lognx);
+    return (unsigned)rel < (unsigned)w.nbw ? rel : -1;
+}
+
+// The bucket of an occupied window slot (the inverse of window_slot).
+template <int PREC, int VD>
+__device__ __forceinline__ int slot_bucket(const Geo& g, const Window& w, const typename MarkersOf<PREC>::E* sE, int i,
+                                           double dtk)
+{
+    if (w.shear || (VD == 3 && PREC == 0 && w.nb1 * w.nb2 > 1)) {
+        const int col = i & (g.nx - 1);
+        int r = i >> g.lognx;
+        if (VD == 3 && PREC == 0 && w.nb1 * w.nb2 > 1) {
+            const int q = r / w.rows, q2 = q / w.nb1;
+            r += (q - q2 * w.nb1) * w.s1 + q2 * w.s2 - q * w.rows;
+        } else {
+            r += kick_rows<PREC>(g, sE, (col - w.drift) & (g.nx - 1), dtk);
+        }
+        return ((w.lo + r) << g.lognx) + col;
+    }
+    return (w.lo << g.lognx) + i;
+}
+
+// Whether a staged kick reaches one velocity cell, decided by wave (each wave
+// staged a part of the field): combined from s_shear after a barrier.
+static_assert(kSortThreads / kWave == 4, "one byte a wave");
+__device__ __forceinline__ void note_shear(bool big, unsigned* s_shear)
+{
+    const int any = __any(big);
+    if ((threadIdx.x & (kWave - 1)) == 0) reinterpret_cast<unsigned char*>(s_shear)[threadIdx.x / kWave] = any ? 1 : 0;
 }
 
 // Stage the field and, in the FP32 form, the drift table into LDS.  The FP64
@@ -329,12 +429,15 @@ __device__ __forceinline__ void set_window(const Geo& g, int b0, int b1, int* lo
 // e_i = E_i * bk rounded once from FP64, with its forward difference
 // e_{i+1} - e_i.  Each thread issues all its loads before its first LDS
 // store, so staging costs one round trip to L2 instead of one per element.
+// Returns whether a kick this thread staged reaches one velocity cell.
 template <int PREC>
-__device__ __forceinline__ void stage_tables(const Geo& g, typename MarkersOf<PREC>::E* sE, RowShift* sRow,
+__device__ __forceinline__ bool stage_tables(const Geo& g, typename MarkersOf<PREC>::E* sE, RowShift* sRow,
                                              const double* __restrict__ E, const RowShift* __restrict__ rows_g,
-                                             float bk)
+                                             double dtk, float bk)
 {
     constexpr int U = 8;
+    bool big = false;
+    const double to_rows = g.qm * dtk * g.inv_dv[0];
     const int nr = PREC ? g.nv[0] + 1 : 0;
     const int span = U * (int)blockDim.x;
     const int ntot = max(g.nx, nr);
@@ -357,11 +460,14 @@ __device__ __forceinline__ void stage_tables(const Geo& g, typename MarkersOf<PR
                 const float k0 = (float)(e[u] * (double)bk), k1 = (float)(e1[u] * (double)bk);
                 if (i < g.nx) sE[i] = make_float2(k0, k1 - k0);
                 if (i < nr) sRow[i] = r[u];
+                big |= fabsf(k0) >= 1.0f;
             } else {
                 if (i < g.nx) sE[i] = e[u];
+                big |= fabs(e[u] * to_rows) >= 1.0;
             }
         }
     }
+    return big;
 }
 
 template <int PREC>
@@ -379,41 +485,17 @@ struct SortSmem {
     }
 };
 
-// Per-thread aggregation of a group's buckets.  Consecutive markers of the
-// previous order come from one or two runs and land in a few new buckets, so a
-// thread keeps two "open" buckets with counts and gives each marker its rank
-// inside its open bucket (tag 0 or 1); any further bucket is an "extra"
-// (tag 2) handled one marker at a time.
-template <int K>
-struct Agg {
-    int b0, b1, c0, c1;
-    int tag[K], r[K];
-    __device__ void build(const int* bkt) {
-        b0 = -1; b1 = -1; c0 = 0; c1 = 0;
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const int b = bkt[k];
-            tag[k] = -1;
-            r[k] = 0;
-            if (b < 0) continue;
-            if (b0 < 0 || b == b0) { b0 = b; tag[k] = 0; r[k] = c0++; }
-            else if (b1 < 0 || b == b1) { b1 = b; tag[k] = 1; r[k] = c1++; }
-            else tag[k] = 2;
-        }
-    }
-};
-
 // ---------------------------------------------------------------------------
 // count pass
 // ---------------------------------------------------------------------------
 // One tile of the count pass: the thread's group of K consecutive markers
 // [first, first+K) of the tile [base, last] is in grp (previous order), the
 // field and drift table staged in LDS.
-template <int PREC, int VD, bool PUSH, bool IMPL, bool AHEAD = false>
+template <int PREC, int VD, bool PUSH, bool IMPL>
 __device__ __forceinline__ void count_tile(const Geo& g, const SortSmem<PREC>& sm, Group<PREC, VD, count_mpt<PREC>()>& grp,
-                                           double dtk, float bk, int* __restrict__ counts, int* __restrict__ tsum,
-                                           int base, int last, int* s_b, int* s_tile, int& fl,
-                                           const Prev& pv, int ovf, int* s_aux, const TbAhead& ah = TbAhead{0, 0, 0})
+                                           double dtk, float bk, int* __restrict__ counts,
+                                           int base, int last, int* s_b, int& fl,
+                                           const Prev& pv, int ovf, int* s_aux, const unsigned* s_shear, int* s_ovf)
 {
     constexpr int K = count_mpt<PREC>();
     const int first = base + threadIdx.x * K;
@@ -421,7 +503,7 @@ __device__ __forceinline__ void count_tile(const Geo& g, const SortSmem<PREC>& s
         // implied cells: this thread's K consecutive positions are its own slots
         int ob[K];
         if (base < ovf) {
-            tile_buckets<K, false, AHEAD>(g, pv, base, min(last + 1, ovf), sm.hist, s_aux, ob, ah);
+            tile_buckets<K, false>(g, pv, base, min(last + 1, ovf), sm.hist, s_aux, ob);
 #pragma unroll
             for (int k = 0; k < K; ++k)
                 if (first + k < ovf) grp.p[k].cell = ob[k];
@@ -434,10 +516,9 @@ __device__ __forceinline__ void count_tile(const Geo& g, const SortSmem<PREC>& s
     }
     __syncthreads();
     // every thread forms the window from the tile's two end buckets itself
-    int lo, nbw;
-    set_window(g, s_b[0], s_b[1], &lo, &nbw, g.hist_bins);
-    for (int i = threadIdx.x; i < nbw; i += blockDim.x) sm.hist[i] = 0;
-    if (threadIdx.x < 8) s_tile[threadIdx.x] = 0;
+    const Window w = set_window<PREC, VD>(g, s_b[0], s_b[1], PUSH && *s_shear != 0, sm.sRow, g.hist_bins);
+    for (int i = threadIdx.x; i < w.nbw; i += blockDim.x) sm.hist[i] = 0;
+    if (threadIdx.x == 0) *s_ovf = 0;
     __syncthreads();
     int bkt[K];
     if constexpr (PUSH && PREC == 1 && VD == 1) {
@@ -453,48 +534,64 @@ __device__ __forceinline__ void count_tile(const Geo& g, const SortSmem<PREC>& s
             a[k] = grp.p[k].a;
             b[k] = grp.p[k].b[0];
         }
-        push32_buckets<K>(g, sm.sE, sm.sRow, c, a, b, bkt);
+        int row[K], col[K];
+        push32_cells<K>(g, sm.sE, sm.sRow, c, a, b, row, col);
+#pragma unroll
+        for (int k = 0; k < K; ++k) bkt[k] = (unsigned)row[k] < (unsigned)g.nrow ? (row[k] << g.lognx) + col[k] : g.nb;
 #pragma unroll
         for (int k = 0; k < K; ++k)
-            if (first + k > last) bkt[k] = -1;
+            if (first + k > last) bkt[k] = kNoBucket;
     } else {
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             // FP32 form: as above, copies of the last marker are pushed too
             if (PUSH && (PREC == 1 || first + k <= last)) grp.p[k].push(g, sm.sE, sm.sRow, dtk, bk, fl);
-            bkt[k] = first + k <= last ? grp.p[k].bucket(g) : -1;
+            bkt[k] = first + k <= last ? grp.p[k].bucket(g) : kNoBucket;
         }
     }
-    Agg<K> ag;
-    ag.build(bkt);
-    auto add = [&](int b, int c) {
-        const int rel = b - lo;
-        if (rel >= 0 && rel < nbw) {
-            atomicAdd(&sm.hist[rel], c);
+    // outside the window: the overflow bucket's own counter, or a global atomic
+    auto add_outside = [&](int b, int c) {
+        if (b == g.nb) {
+            atomicAdd(s_ovf, c);
         } else {
             atomicAdd(&counts[b], c);
-            atomicAdd(&tsum[b / kScanTile], c);
         }
     };
-    if (ag.c0) add(ag.b0, ag.c0);
-    if (ag.c1) add(ag.b1, ag.c1);
+    const bool plain = !w.shear && w.nb1 * w.nb2 == 1;
+    // a thread's markers come from one or two runs, so its neighbours work
+    // on other buckets: one LDS atomic a marker meets few conflicts, and
+    // costs less than the compares that would merge a thread's own first
+    // bkt[k] becomes the window slot, or ~bucket outside the window
+    if (plain) {
 #pragma unroll
-    for (int k = 0; k < K; ++k)
-        if (ag.tag[k] == 2) add(bkt[k], 1);
-    __syncthreads();
-    // flush the window; the same counts also go into per-scan-tile totals
-    // (kScanTile buckets each), so the scan needs no separate reduction pass
-    const int tlo = lo / kScanTile;
-    for (int i = threadIdx.x; i < nbw; i += blockDim.x) {
-        const int c = sm.hist[i];
-        if (c) {
-            atomicAdd(&counts[lo + i], c);
-            atomicAdd(&s_tile[(lo + i) / kScanTile - tlo], c);
+        for (int k = 0; k < K; ++k) {
+            const int rel = bkt[k] - (w.lo << g.lognx);
+            bkt[k] = (unsigned)rel < (unsigned)w.nbw ? rel : ~bkt[k];
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int slot = window_slot<PREC, VD>(g, w, sm.sE, bkt[k], dtk);
+            bkt[k] = slot >= 0 ? slot : ~bkt[k];
         }
     }
+    bool outside = false;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        if (bkt[k] >= 0) atomicAdd(&sm.hist[bkt[k]], 1);
+        else outside = true;
+    }
+    if (outside) {
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            if (bkt[k] < 0 && bkt[k] != ~kNoBucket) add_outside(~bkt[k], 1);
+    }
     __syncthreads();
-    const int ntile_win = (lo + nbw - 1) / kScanTile - tlo + 1;
-    if (threadIdx.x < ntile_win && s_tile[threadIdx.x]) atomicAdd(&tsum[tlo + threadIdx.x], s_tile[threadIdx.x]);
+    for (int i = threadIdx.x; i < w.nbw; i += blockDim.x) {
+        const int c = sm.hist[i];
+        if (c) atomicAdd(&counts[slot_bucket<PREC, VD>(g, w, sm.sE, i, dtk)], c);
+    }
+    if (threadIdx.x == 0 && *s_ovf) atomicAdd(&counts[g.nb], *s_ovf);
 }
 
 // Tile t of the count pass covers markers [t*T, ...), T = count_tile_size; in
@@ -506,19 +603,20 @@ __device__ __forceinline__ int count_tile_last(const Geo& g, int t)
     return min(t * T + T, g.n) - 1;
 }
 
-// count pass of one block over one tile (the batched kernel and the forms
-// without a tiled kernel)
+// count pass of one block over one tile (1D-3V, kicks of velocity cells, and
+// large dense FP64 sorts)
 template <int PREC, int VD, bool PUSH, bool IMPL>
 __device__ __forceinline__ void count_block(const Geo& g, const typename MarkersOf<PREC>::T& m,
                                             const double* __restrict__ E, const RowShift* __restrict__ rows_g,
-                                            double dtk, float bk, int* __restrict__ counts, int* __restrict__ tsum,
+                                            double dtk, float bk, int* __restrict__ counts,
                                             int* __restrict__ flags, int blk, const Prev& pv)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     SortSmem<PREC> sm(smem, g);
-    __shared__ int s_b[2], s_flags, s_tile[8], s_aux[kSortThreads / kWave + 1];
+    __shared__ int s_b[2], s_flags, s_aux[kSortThreads / kWave + 1], s_ovf;
+    __shared__ unsigned s_shear;
     if (threadIdx.x == 0) s_flags = 0;
-    if (PUSH) stage_tables<PREC>(g, sm.sE, sm.sRow, E, rows_g, bk);
+    if (PUSH) note_shear(stage_tables<PREC>(g, sm.sE, sm.sRow, E, rows_g, dtk, bk), &s_shear);
     constexpr int K = count_mpt<PREC>();
     Group<PREC, VD, K> grp;
     const int base = blk * (kSortThreads * K);
@@ -526,72 +624,32 @@ __device__ __forceinline__ void count_block(const Geo& g, const typename Markers
     const int ovf = IMPL ? pv.off[g.nb] : -1;
     grp.load(m, g, base + threadIdx.x * K, last, false, PREC ? 1 : VD, ovf);
     int fl = 0;
-    count_tile<PREC, VD, PUSH, IMPL>(g, sm, grp, dtk, bk, counts, tsum, base, last, s_b, s_tile, fl, pv,
-                                     ovf, s_aux);
+    count_tile<PREC, VD, PUSH, IMPL>(g, sm, grp, dtk, bk, counts, base, last, s_b, fl, pv,
+                                     ovf, s_aux, &s_shear, &s_ovf);
     if (fl) atomicOr(&s_flags, fl);
     __syncthreads();
     if (threadIdx.x == 0 && s_flags) atomicOr(flags, s_flags);
 }
 
-template <int PREC, int VD, bool PUSH>
+// Tile of block b of n (n a multiple of 8).  In 1D-3V each XCD (blocks go round
+// the 8 of them) takes a contiguous range of tiles, so that the lines of
+// destinations that neighbouring tiles share stay in one L2: 2.89 -> 2.77 ms a
+// scatter of 268M FP32-form markers.  In 1D-1V blocks take tiles in order: there
+// the contiguous ranges ran the scatter of 16.8M FP64 markers at 153 us against
+// 139.
+template <int VD>
+__device__ __forceinline__ int block_tile(int b, int n) { return VD == 3 ? (b & 7) * (n >> 3) + (b >> 3) : b; }
+
+template <int PREC, int VD, bool PUSH, bool IMPL = false>
 __global__ __launch_bounds__(kSortThreads) void k_count(Geo g, typename MarkersOf<PREC>::T m,
                                                          const double* __restrict__ E,
                                                          const RowShift* __restrict__ rows_g,
                                                          double dtk, float bk,
-                                                         int* __restrict__ counts, int* __restrict__ tsum,
-                                                         int* __restrict__ flags)
+                                                         int* __restrict__ counts, int* __restrict__ flags, Prev pv)
 {
-    count_block<PREC, VD, PUSH, false>(g, m, E, rows_g, dtk, bk, counts, tsum, flags, blockIdx.x, Prev{nullptr, nullptr});
-}
-
-// Tiled count pass: each block takes tiles blockIdx.x, blockIdx.x + gridDim.x,
-// ... (one block per resident slot), so the field and drift table are staged
-// once per block instead of once per tile.
-template <int PREC, int VD, bool PUSH, bool IMPL>
-__global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_count_tiled(Geo g, typename MarkersOf<PREC>::T m,
-                                                         const double* __restrict__ E,
-                                                         const RowShift* __restrict__ rows_g,
-                                                         double dtk, float bk,
-                                                         int* __restrict__ counts, int* __restrict__ tsum,
-                                                         int* __restrict__ flags, Prev pv)
-{
-    extern __shared__ __align__(16) unsigned char smem[];
-    SortSmem<PREC> sm(smem, g);
-    __shared__ int s_b[2], s_flags, s_tile[8], s_aux[kSortThreads / kWave + 1];
-    constexpr int K = count_mpt<PREC>();
-    constexpr int T = kSortThreads * K;
-    const int ntiles = (g.n + T - 1) / T;
-    const int ovf = IMPL ? pv.off[g.nb] : -1;
-    if (threadIdx.x == 0) s_flags = 0;
-    if (PUSH) stage_tables<PREC>(g, sm.sE, sm.sRow, E, rows_g, bk);
-    int fl = 0;
-    // implied cells: a tile's first-pass run offsets are loaded one tile
-    // ahead, its first run two tiles ahead (as in the scatter)
-    TbAhead ah{0, 0, 0};
-    int b0n = 0;
-    if constexpr (IMPL) {
-        if ((int)blockIdx.x < ntiles) ah = tile_runs_ahead(g, pv, tile_first_run(pv, blockIdx.x * T));
-        if ((int)(blockIdx.x + gridDim.x) < ntiles) b0n = tile_first_run(pv, (blockIdx.x + gridDim.x) * T);
-    }
-    const int my_tiles = (ntiles - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;
-    for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
-        prio_by_progress((t - (int)blockIdx.x) / (int)gridDim.x, my_tiles);
-        Group<PREC, VD, K> grp;
-        const int last = count_tile_last<PREC>(g, t);
-        grp.load(m, g, t * T + threadIdx.x * K, last, false, PREC ? 1 : VD, ovf);
-        TbAhead an{0, 0, 0};
-        if constexpr (IMPL) {
-            const int tn = t + gridDim.x, tnn = tn + gridDim.x;
-            if (tn < ntiles) an = tile_runs_ahead(g, pv, b0n);
-            if (tnn < ntiles) b0n = tile_first_run(pv, tnn * T);
-        }
-        count_tile<PREC, VD, PUSH, IMPL, IMPL>(g, sm, grp, dtk, bk, counts, tsum, t * T, last, s_b,
-                                               s_tile, fl, pv, ovf, s_aux, ah);
-        ah = an;
-    }
-    if (fl) atomicOr(&s_flags, fl);
-    __syncthreads();
-    if (threadIdx.x == 0 && s_flags) atomicOr(flags, s_flags);
+    const int t = block_tile<VD>(blockIdx.x, gridDim.x);
+    if (t * (kSortThreads * count_mpt<PREC>()) >= g.n) return;
+    count_block<PREC, VD, PUSH, IMPL>(g, m, E, rows_g, dtk, bk, counts, flags, t, pv);
 }
 
 // ---------------------------------------------------------------------------
@@ -602,22 +660,26 @@ __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_eu(4)
 // consecutive ranks in their new run from the LDS atomics, so each store
 // instruction writes a few contiguous stretches instead of 64 scattered words.
 // ---------------------------------------------------------------------------
+constexpr int kRankBits = 12;                          // a marker's rank in its window slot
+constexpr int kOverflowSlot = (1 << (31 - kRankBits)) - 1;
+enum : int { kOutside = -1, kNoMarker = -2 };
+static_assert(kSortTile <= 1 << kRankBits && kOverflowSlot > 160 * 1024 / 4, "slot and rank share 31 bits");
+
 // One tile of the scatter: the markers [base, last] of the previous order are
 // in p[] (lane-strided), the field and drift table staged in LDS.
-template <int PREC, int VD, bool PUSH, bool IMPL, bool AHEAD = false>
+template <int PREC, int VD, bool PUSH, bool IMPL>
 __device__ __forceinline__ void scatter_tile(const Geo& g, const SortSmem<PREC>& sm, Pay<PREC, VD>* p,
                                              const typename MarkersOf<PREC>::T& dst, double dtk, float bk,
                                              const int* __restrict__ offsets, int* __restrict__ counts,
                                              int base, int last, int* s_b, int& fl,
-                                             const Prev& pv, int ovf, int* s_aux, int maxbins,
-                                             const TbAhead& ah = TbAhead{0, 0, 0})
+                                             const Prev& pv, int ovf, int* s_aux, const unsigned* s_shear, int* s_ovf, int maxbins)
 {
     constexpr int K = kSortMPT;
     if constexpr (IMPL) {
         // implied cells: the tile's buckets are left in LDS, read lane-strided
         if (base < ovf) {
             int ob[K];
-            tile_buckets<K, true, AHEAD>(g, pv, base, min(last + 1, ovf), sm.hist, s_aux, ob, ah);
+            tile_buckets<K, true>(g, pv, base, min(last + 1, ovf), sm.hist, s_aux, ob);
 #pragma unroll
             for (int k = 0; k < K; ++k) {
                 const int i = base + k * kSortThreads + threadIdx.x;
@@ -633,21 +695,24 @@ __device__ __forceinline__ void scatter_tile(const Geo& g, const SortSmem<PREC>&
     }
     __syncthreads();
     // every thread forms the window from the tile's two end buckets itself
-    int lo, nbw;
-    set_window(g, s_b[0], s_b[1], &lo, &nbw, maxbins);
-    for (int i = threadIdx.x; i < nbw; i += blockDim.x) sm.hist[i] = 0;
+    const Window w = set_window<PREC, VD>(g, s_b[0], s_b[1], PUSH && *s_shear != 0, sm.sRow, maxbins);
+    for (int i = threadIdx.x; i < w.nbw; i += blockDim.x) sm.hist[i] = 0;
+    if (threadIdx.x == 0) *s_ovf = 0;
     __syncthreads();
-    int bkt[K], rank[K];
+    // place[k]: window slot (or kOverflowSlot) and rank of marker k in it, in
+    // one register; kOutside and kNoMarker are negative
+    int place[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const int i = base + k * kSortThreads + threadIdx.x;
-        bkt[k] = -1;
-        rank[k] = -1;
+        place[k] = kNoMarker;
         if (i <= last) {
             if (PUSH) p[k].push(g, sm.sE, sm.sRow, dtk, bk, fl);
-            bkt[k] = p[k].bucket(g);
-            const int rel = bkt[k] - lo;
-            if (rel >= 0 && rel < nbw) rank[k] = atomicAdd(&sm.hist[rel], 1);
+            const int b = p[k].bucket(g);
+            const int slot = window_slot<PREC, VD>(g, w, sm.sE, b, dtk);
+            place[k] = kOutside;
+            if (slot >= 0) place[k] = (slot << kRankBits) + atomicAdd(&sm.hist[slot], 1);
+            else if (b == g.nb) place[k] = (kOverflowSlot << kRankBits) + atomicAdd(s_ovf, 1);
         }
     }
     __syncthreads();
@@ -655,27 +720,30 @@ __device__ __forceinline__ void scatter_tile(const Geo& g, const SortSmem<PREC>&
     // still free, counting down from the run length, so a claim that starts
     // at or above zero lies inside the run; the histogram entry becomes the
     // first claimed position
-    for (int i = threadIdx.x; i < nbw; i += blockDim.x) {
+    auto claim = [&](int b, int c) {
+        const int start = atomicSub(&counts[b], c) - c;
+        if (start < 0) fl |= FLAG_SLOT;
+        return start < 0 ? -1 : offsets[b] + start;
+    };
+    for (int i = threadIdx.x; i < w.nbw; i += blockDim.x) {
         const int c = sm.hist[i];
-        if (c) {
-            const int old = atomicSub(&counts[lo + i], c);
-            const int start = old - c;
-            if (start < 0) fl |= FLAG_SLOT;
-            sm.hist[i] = start < 0 ? -1 : offsets[lo + i] + start;
-        }
+        if (c) sm.hist[i] = claim(slot_bucket<PREC, VD>(g, w, sm.sE, i, dtk), c);
     }
+    if (threadIdx.x == 0 && *s_ovf) *s_ovf = claim(g.nb, *s_ovf);
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        if (bkt[k] < 0) continue;
+        if (place[k] == kNoMarker) continue;
         int dest;
-        if (rank[k] >= 0) {
-            const int first = sm.hist[bkt[k] - lo];
-            dest = first < 0 ? -1 : first + rank[k];
+        if (place[k] >= 0) {
+            const int slot = place[k] >> kRankBits;
+            const int first = slot == kOverflowSlot ? *s_ovf : sm.hist[slot];
+            dest = first < 0 ? -1 : first + (place[k] & ((1 << kRankBits) - 1));
         } else {
-            // outside the window (a large velocity jump): one slot at a time
-            const int slot = atomicSub(&counts[bkt[k]], 1) - 1;
-            dest = slot < 0 ? -1 : offsets[bkt[k]] + slot;
+            // outside the window (a jump it does not follow): one slot at a time
+            const int b = p[k].bucket(g);
+            const int free = atomicSub(&counts[b], 1) - 1;
+            dest = free < 0 ? -1 : offsets[b] + free;
         }
         if (dest < 0) { fl |= FLAG_SLOT; continue; }
         p[k].store(dst, g, dest, false);
@@ -694,8 +762,8 @@ __device__ __forceinline__ void load_tile(const typename MarkersOf<PREC>::T& src
     }
 }
 
-// scatter pass of one block over one tile (the batched kernel and the forms
-// without a tiled kernel)
+// scatter pass of one block over one tile (1D-3V, kicks of velocity cells, and
+// large dense FP64 sorts)
 template <int PREC, int VD, bool PUSH, bool IMPL>
 __device__ __forceinline__ void scatter_block(const Geo& g, const typename MarkersOf<PREC>::T& src,
                                               const typename MarkersOf<PREC>::T& dst,
@@ -706,127 +774,559 @@ __device__ __forceinline__ void scatter_block(const Geo& g, const typename Marke
 {
     extern __shared__ __align__(16) unsigned char smem[];
     SortSmem<PREC> sm(smem, g);
-    __shared__ int s_b[2], s_flags, s_aux[kSortThreads / kWave + 1];
+    __shared__ int s_b[2], s_flags, s_aux[kSortThreads / kWave + 1], s_ovf;
+    __shared__ unsigned s_shear;
     const int base = blk * kSortTile;
     const int last = min(base + kSortTile, g.n) - 1;
     const int ovf = IMPL ? pv.off[g.nb] : -1;
     if (threadIdx.x == 0) s_flags = 0;
-    if (PUSH) stage_tables<PREC>(g, sm.sE, sm.sRow, E, rows_g, bk);
+    if (PUSH) note_shear(stage_tables<PREC>(g, sm.sE, sm.sRow, E, rows_g, dtk, bk), &s_shear);
     Pay<PREC, VD> p[kSortMPT];
     load_tile<PREC, VD>(src, g, p, base, last, ovf);
     int fl = 0;
     scatter_tile<PREC, VD, PUSH, IMPL>(g, sm, p, dst, dtk, bk, offsets, counts, base, last, s_b, fl,
-                                       pv, ovf, s_aux, maxbins);
+                                       pv, ovf, s_aux, &s_shear, &s_ovf, maxbins);
     if (fl) atomicOr(&s_flags, fl);
     __syncthreads();
     if (threadIdx.x == 0 && s_flags) atomicOr(flags, s_flags);
 }
 
-template <int PREC, int VD, bool PUSH>
+template <int PREC, int VD, bool PUSH, bool IMPL = false>
 __global__ __launch_bounds__(kSortThreads) void k_scatter1(Geo g, typename MarkersOf<PREC>::T src,
                                                            typename MarkersOf<PREC>::T dst,
                                                            const double* __restrict__ E,
                                                            const RowShift* __restrict__ rows_g,
                                                            double dtk, float bk,
                                                            const int* __restrict__ offsets,
-                                                           int* __restrict__ counts, int* __restrict__ flags)
+                                                           int* __restrict__ counts, int* __restrict__ flags, Prev pv)
 {
-    scatter_block<PREC, VD, PUSH, false>(g, src, dst, E, rows_g, dtk, bk, offsets, counts, flags, blockIdx.x,
-                                         Prev{nullptr, nullptr}, g.hist_bins);
+    const int t = block_tile<VD>(blockIdx.x, gridDim.x);
+    if (t * kSortTile >= g.n) return;
+    scatter_block<PREC, VD, PUSH, IMPL>(g, src, dst, E, rows_g, dtk, bk, offsets, counts, flags, t, pv, g.hist_bins);
 }
 
-// Tiled scatter: each block takes tiles blockIdx.x, blockIdx.x + gridDim.x,
-// ... and loads its next tile's markers while the current one is pushed,
-// ranked, claimed and stored, so the loads of one tile overlap the latency
-// chain of the previous one; the field and drift table are staged once.
-// ID false: the markers carry no identities (every run but an adjoint's), so
-// the payload holds no id register (the null pointers are known at compile
-// time).
-template <int PREC, int VD, bool PUSH, bool IMPL, bool ID>
-__device__ __forceinline__ void scatter_tiled(const Geo& g, typename MarkersOf<PREC>::T src,
-                                              typename MarkersOf<PREC>::T dst, const double* __restrict__ E,
-                                              const RowShift* __restrict__ rows_g, double dtk, float bk,
-                                              const int* __restrict__ offsets, int* __restrict__ counts,
-                                              int* __restrict__ flags, const Prev& pv)
+// ---------------------------------------------------------------------------
+// 1D-1V count and scatter: one wavefront a tile
+//
+// A tile of 64 K markers (K = 8, or 4) is worked on by one wavefront alone,
+// with its own window in LDS, so a pass has no block barriers (only the staged tables are shared, behind one barrier at
+// the start): the count and scatter are chains of dependent loads, LDS round
+// trips and atomics, and waves that wait for each other at every link are what
+// bounded them.  16.8M FP32-form markers, 1024 x 1024 cells: count 49.6 us by
+// blocks of 4096 markers, 30.3 by waves (138 MB, 25 us at the copy kernel's
+// rate); scatter 92.5 by blocks of 2048, 86.4 by waves (407 MB, 74 us).  16,384
+// FP64 markers: count 8.3 -> 5.2, scatter 9.0 -> 7.0.
+//
+// A wave's window is a box of W columns by R rows.  512 consecutive markers of
+// the previous order span few columns (32 at 16 markers a cell); the push
+// moves all of them by about their row's drift, and their rows by about the
+// kick at their columns, so the box [first column + drift, ...) x [first row +
+// smallest kick, last row + largest kick + 1] holds nearly all of them however
+// far they move, in 1-3 bins a lane instead of whole bucket rows.  W is a power
+// of two from 64, so 64 lanes take bins of one row.  Markers outside the box
+// take one global atomic each, those of the overflow bucket one a tile.
+// ---------------------------------------------------------------------------
+template <int K> constexpr int kWTile = kWave * K;         // markers of a wave tile, K a lane
+constexpr int kWaves = kSortThreads / kWave;
+static_assert(kWTile<4> % kTfStride == 0, "wave tiles start at recorded positions");
+
+__device__ __forceinline__ void wave_lds_fence()
 {
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Inclusive running maximum over the lanes (values >= -1): DPP row shifts, then
+// row broadcasts.
+__device__ __forceinline__ int wave_running_max(int v)
+{
+    v = max(v, __builtin_amdgcn_update_dpp(-1, v, 0x111, 0xf, 0xf, false));   // row_shr:1
+    v = max(v, __builtin_amdgcn_update_dpp(-1, v, 0x112, 0xf, 0xf, false));   // row_shr:2
+    v = max(v, __builtin_amdgcn_update_dpp(-1, v, 0x114, 0xf, 0xf, false));   // row_shr:4
+    v = max(v, __builtin_amdgcn_update_dpp(-1, v, 0x118, 0xf, 0xf, false));   // row_shr:8
+    v = max(v, __builtin_amdgcn_update_dpp(-1, v, 0x142, 0xa, 0xf, false));   // row_bcast:15
+    v = max(v, __builtin_amdgcn_update_dpp(-1, v, 0x143, 0xc, 0xf, false));   // row_bcast:31
+    return v;
+}
+
+// Bounds of run b0 + 1 + lane, loaded ahead of a tile whose first position
+// lies in run b0 (past the last run: empty).
+struct WaveRuns {
+    int b0, lo, hi;
+};
+
+__device__ __forceinline__ WaveRuns wave_runs_ahead(const Geo& g, const Prev& pv, int b0, int lane)
+{
+    WaveRuns r{b0, 0, 0};
+    const int b = min(max(b0, 0), g.nb) + 1 + lane;
+    if (b < g.nb) {
+        r.lo = pv.off[b];
+        r.hi = pv.off[b + 1];
+    }
+    return r;
+}
+
+// Buckets of the positions [base, end) of a wave's tile (implied cells): the
+// start of every run is marked in map, a running maximum fills in the rest.
+// Lane l gets the buckets of its K consecutive positions in bk[]; they are
+// also left in map.
+template <int K>
+__device__ __forceinline__ void wave_buckets(const Geo& g, const Prev& pv, int base, int end, int lane, int* map,
+                                             int (&bk)[K], const WaveRuns& ahead)
+{
+    static_assert(K % 4 == 0, "positions are cleared and read as 16-byte vectors");
+    int4* own = reinterpret_cast<int4*>(map + lane * K);
+#pragma unroll
+    for (int k = 0; k < K / 4; ++k) own[k] = make_int4(lane == 0 && k == 0 ? ahead.b0 : -1, -1, -1, -1);
+    wave_lds_fence();
+    int b = ahead.b0 + 1 + lane, lo = b < g.nb ? ahead.lo : end, hi = ahead.hi;
+    while (true) {
+        if (lo < hi && lo > base && lo < end) map[lo - base] = b;
+        if (__builtin_amdgcn_readlane(lo, kWave - 1) >= end) break;
+        b += kWave;
+        lo = end;
+        if (b < g.nb) {
+            lo = pv.off[b];
+            hi = pv.off[b + 1];
+        }
+    }
+    wave_lds_fence();
+#pragma unroll
+    for (int k = 0; k < K / 4; ++k) {
+        const int4 v = own[k];
+        bk[4 * k] = v.x; bk[4 * k + 1] = v.y; bk[4 * k + 2] = v.z; bk[4 * k + 3] = v.w;
+    }
+#pragma unroll
+    for (int k = 1; k < K; ++k) bk[k] = max(bk[k], bk[k - 1]);
+    const int inc = wave_running_max(bk[K - 1]);
+    const int carry = __builtin_amdgcn_update_dpp(-1, inc, 0x138, 0xf, 0xf, false);   // wave_shr:1
+#pragma unroll
+    for (int k = 0; k < K; ++k) bk[k] = max(bk[k], carry);
+#pragma unroll
+    for (int k = 0; k < K / 4; ++k) own[k] = make_int4(bk[4 * k], bk[4 * k + 1], bk[4 * k + 2], bk[4 * k + 3]);
+    wave_lds_fence();
+}
+
+// A wave's window: bin (r << lgw) + c stands for row row0 + r, column
+// (col0 + c) mod nx.
+struct Box {
+    int row0, col0, lgw, rows, nbins;
+    // bin of (row, col); false outside
+    __device__ bool bin(const Geo& g, int row, int col, int& s) const {
+        const int c = (col - col0) & (g.nx - 1), r = row - row0;
+        s = (r << lgw) + c;
+        return (unsigned)r < (unsigned)rows && (c >> lgw) == 0;
+    }
+    __device__ int bucket(const Geo& g, int s) const {
+        const int c = s & ((1 << lgw) - 1);
+        return ((row0 + (s >> lgw)) << g.lognx) + ((col0 + c) & (g.nx - 1));
+    }
+};
+
+// The box of a tile whose first and last marker (before the push) lie in
+// buckets b0 and b1, in at most maxbins bins; empty when b0 is the overflow
+// bucket.  SORTED: the tile's markers are in bucket order (b0 <= b1).
+template <int PREC, int K, bool PUSH, bool SORTED>
+__device__ __forceinline__ Box wave_box(const Geo& g, const SortSmem<PREC>& sm, double dtk, int b0, int b1, int maxbins)
+{
+    Box x;
+    b0 = __builtin_amdgcn_readfirstlane(b0);
+    b1 = __builtin_amdgcn_readfirstlane(b1);
+    const int r0 = min(b0, b1) >> g.lognx, r1 = max(b0, b1) >> g.lognx;
+    const int c0 = b0 & (g.nx - 1), c1 = b1 & (g.nx - 1);
+    int lo = r0, hi = r1, col = c0, ncol;
+    if (SORTED) {
+        ncol = min(b1 - b0 + 1, g.nx);
+    } else {
+        // markers in the order they were loaded or pushed in: either end may
+        // lie a cell off its neighbours'; sparse rows take every column
+        ncol = (long long)kWTile<K> * g.nb >= (long long)g.n * g.nx ? g.nx : ((c1 - c0) & (g.nx - 1)) + 3;
+        col -= 1;
+        lo -= 1;
+        hi += 1;
+    }
+    if constexpr (PUSH) {
+        // the kick at the tile's ends, with some slack for what lies between,
+        // and the drift P of row r0, whole and fractional
+        float k0, k1, frac;
+        int whole;
+        if constexpr (PREC == 1) {
+            k0 = sm.sE[c0].x;
+            k1 = sm.sE[c1].x;
+            const RowShift p = sm.sRow[min(r0, g.nv[0])];
+            whole = p.whole;
+            frac = p.frac;
+        } else {
+            const double to_rows = g.qm * dtk * g.inv_dv[0];
+            k0 = (float)(sm.sE[c0] * to_rows);
+            k1 = (float)(sm.sE[c1] * to_rows);
+            const double P = (g.vmin[0] + ((double)r0 - 0.5) * g.dv[0]) * g.dt * g.inv_dx;
+            const double fP = floor(P);
+            whole = (int)fmin(fmax(fP, -1e6), 1e6);
+            frac = (float)(P - fP);
+        }
+        const float slack = 0.03125f + fabsf(k1 - k0);
+        lo += (int)fminf(fmaxf(floorf(fminf(k0, k1) - slack), -1e6f), 1e6f);
+        hi += (int)fminf(fmaxf(floorf(fmaxf(k0, k1) + slack), -1e6f), 1e6f) + 1;
+        // a marker that ends in row r drifts by P(r) + [0, gam) cells, P growing
+        // by gam a row; its offset adds less than one
+        const float d0 = floorf(fmaxf(frac + (float)(lo - r0) * g.gam, -1e6f));
+        const float d1 = floorf(fminf(frac + (float)(hi - r0 + 1) * g.gam, 1e6f)) + 1.0f;
+        col += whole + (int)d0;
+        ncol += (int)(d1 - d0);
+    }
+    lo = __builtin_amdgcn_readfirstlane(max(lo, 0));
+    hi = __builtin_amdgcn_readfirstlane(min(hi, g.nrow - 1));
+    ncol = __builtin_amdgcn_readfirstlane(min(ncol, g.nx));
+    x.row0 = lo;
+    x.col0 = __builtin_amdgcn_readfirstlane(col);
+    x.lgw = min(max(6, 32 - __builtin_clz(max(ncol - 1, 1))), g.lognx);
+    x.rows = b0 >= g.nb ? 0 : max(min(hi - lo + 1, maxbins >> x.lgw), 0);
+    x.nbins = x.rows << x.lgw;
+    return x;
+}
+
+// Bucket row and column of a marker; a row outside [0, nrow) has no bucket.
+__device__ __forceinline__ void row_col(const Geo& g, const Pay<1, 1>& p, int& row, int& col)
+{
+    row = p.cell >> g.lognx;
+    col = p.cell & (g.nx - 1);
+}
+__device__ __forceinline__ void row_col(const Geo& g, const Pay<0, 1>& p, int& row, int& col)
+{
+    const int b = p.bucket(g);
+    row = b >> g.lognx;          // nrow for the overflow bucket
+    col = b & (g.nx - 1);
+}
+
+// Buckets of a tile's first and last marker before the push.  FP32: from the
+// implied cells in map (positions below ovf), else from the stored cells.
+// FP64: from lane 0's first and lane 63's last marker (copies of the tile's
+// last one past its end).
+template <int PREC, int K, bool IMPL>
+__device__ __forceinline__ void end_buckets(const Geo& g, const Pay<PREC, 1>* p, const typename MarkersOf<PREC>::T& m,
+                                            const int* map, int base, int last, int ovf, int b0_run, int& b0, int& b1)
+{
+    if constexpr (PREC == 0) {
+        b0 = __builtin_amdgcn_readlane(p[0].bucket(g), 0);
+        b1 = __builtin_amdgcn_readlane(p[K - 1].bucket(g), kWave - 1);
+    } else if (IMPL && base < ovf) {
+        b0 = b0_run;
+        b1 = map[min(last + 1, ovf) - 1 - base];
+        wave_lds_fence();
+    } else {
+        b0 = bucket32<1>(g, m.cell[base]);
+        b1 = bucket32<1>(g, m.cell[last]);
+    }
+}
+
+// One tile of the count: lane l has the K consecutive markers from base + K l
+// in grp.
+template <int PREC, int K, bool PUSH, bool IMPL>
+__device__ __forceinline__ void count_wave(const Geo& g, const SortSmem<PREC>& sm, Group<PREC, 1, K>& grp,
+                                           const typename MarkersOf<PREC>::T& m, int* map, double dtk,
+                                           int* __restrict__ counts, int base, int last, int lane, int& fl,
+                                           const Prev& pv, int ovf, const WaveRuns& ahead)
+{
+    const int first = base + lane * K;
+    if constexpr (PREC == 1 && IMPL) {
+        if (base < ovf) {
+            int ob[K];
+            wave_buckets<K>(g, pv, base, min(last + 1, ovf), lane, map, ob, ahead);
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                if (first + k < ovf) grp.p[k].cell = ob[k];
+        }
+    }
+    int b0, b1;
+    end_buckets<PREC, K, IMPL>(g, grp.p, m, map, base, last, ovf, ahead.b0, b0, b1);
+    const Box box = wave_box<PREC, K, PUSH, PREC ? IMPL : PUSH>(g, sm, dtk, b0, b1, g.wbins);
+    for (int i = lane; i < box.nbins; i += kWave) map[i] = 0;
+    wave_lds_fence();
+    int row[K], col[K];
+    if constexpr (PUSH && PREC == 1) {
+        // only the new buckets; past the last marker the group holds copies of
+        // it, pushed too (the markers' LDS round trips interleave) and not
+        // counted.  The flags are raised by the scatter, which pushes the same
+        // markers with the same field.
+        int c[K];
+        float a[K], b[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            c[k] = grp.p[k].cell;
+            a[k] = grp.p[k].a;
+            b[k] = grp.p[k].b[0];
+        }
+        push32_cells<K>(g, sm.sE, sm.sRow, c, a, b, row, col);
+    } else {
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            if (PUSH) grp.p[k].push(g, sm.sE, sm.sRow, dtk, 0.0f, fl);
+            row_col(g, grp.p[k], row[k], col[k]);
+        }
+    }
+    // a lane's markers come from one or two runs, so its neighbours work on
+    // other buckets: one LDS atomic a marker meets few conflicts, and costs
+    // less than the compares that would merge a lane's own first
+    bool outside = false;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        int s;
+        const bool in = box.bin(g, row[k], col[k], s) && first + k <= last;
+        if (in) atomicAdd(&map[s], 1);
+        else outside = true;
+        // what is left: the bucket, or -1
+        row[k] = in || first + k > last ? -1 : (unsigned)row[k] < (unsigned)g.nrow ? (row[k] << g.lognx) + col[k] : g.nb;
+    }
+    int novf = 0;
+    if (__any(outside)) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            novf += __popcll(__ballot(row[k] == g.nb));
+            if (row[k] >= 0 && row[k] != g.nb) atomicAdd(&counts[row[k]], 1);
+        }
+    }
+    wave_lds_fence();
+    for (int i = lane; i < box.nbins; i += kWave) {
+        const int c = map[i];
+        if (c) atomicAdd(&counts[box.bucket(g, i)], c);
+    }
+    if (novf && lane == 0) atomicAdd(&counts[g.nb], novf);
+    wave_lds_fence();
+}
+
+// Wave wv of block blk takes wave tiles blk * 4 + wv, + stride, ...
+template <int PREC, int K, bool PUSH, bool IMPL>
+__device__ __forceinline__ void count_waves(const Geo& g, const typename MarkersOf<PREC>::T& m,
+                                            const double* __restrict__ E, const RowShift* __restrict__ rows_g, double dtk,
+                                            float bk, int* __restrict__ counts, int* __restrict__ flags, const Prev& pv,
+                                            int blk, int nblk)
+{
+    constexpr int T = kWTile<K>;
+    extern __shared__ __align__(16) unsigned char smem[];
+    SortSmem<PREC> sm(smem, g);
+    const int lane = threadIdx.x & (kWave - 1), wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    int* map = sm.hist + wv * g.wbins;
+    if (PUSH) {
+        stage_tables<PREC>(g, sm.sE, sm.sRow, E, rows_g, dtk, bk);
+        __syncthreads();
+    }
+    const int ntiles = (g.n + T - 1) / T, stride = nblk * kWaves;
+    int t = blk * kWaves + wv, fl = 0;
+    const int ovf = IMPL ? pv.off[g.nb] : -1;
+    // implied cells: a tile's run bounds are loaded one tile ahead, its first
+    // run two tiles ahead (the bounds' addresses depend on it)
+    WaveRuns ah{0, 0, 0};
+    int b0n = 0;
+    if constexpr (IMPL) {
+        if (t < ntiles) ah = wave_runs_ahead(g, pv, tile_first_run(pv, t * T), lane);
+        if (t + stride < ntiles) b0n = tile_first_run(pv, (t + stride) * T);
+    }
+    const int mine = (ntiles - t + stride - 1) / stride;
+    for (int k = 0; t < ntiles; t += stride, ++k) {
+        prio_by_progress(k, mine);
+        const int last = min(t * T + T, g.n) - 1;
+        Group<PREC, 1, K> grp;
+        grp.load(m, g, t * T + lane * K, last, false, 1, ovf);
+        WaveRuns an{0, 0, 0};
+        if constexpr (IMPL) {
+            if (t + stride < ntiles) an = wave_runs_ahead(g, pv, b0n, lane);
+            if (t + 2 * stride < ntiles) b0n = tile_first_run(pv, (t + 2 * stride) * T);
+        }
+        count_wave<PREC, K, PUSH, IMPL>(g, sm, grp, m, map, dtk, counts, t * T, last, lane, fl, pv, ovf, ah);
+        ah = an;
+    }
+    if (fl) atomicOr(flags, fl);
+}
+
+template <int PREC, int K, bool PUSH, bool IMPL>
+__global__ __launch_bounds__(kSortThreads) void k_count_w(Geo g, typename MarkersOf<PREC>::T m, const double* __restrict__ E,
+                                                          const RowShift* __restrict__ rows_g, double dtk, float bk,
+                                                          int* __restrict__ counts, int* __restrict__ flags, Prev pv)
+{
+    count_waves<PREC, K, PUSH, IMPL>(g, m, E, rows_g, dtk, bk, counts, flags, pv, blockIdx.x, gridDim.x);
+}
+
+// One tile of the scatter: marker base + 64 k + lane is in p[k].
+template <int PREC, int K, bool PUSH, bool IMPL>
+__device__ __forceinline__ void scatter_wave(const Geo& g, const SortSmem<PREC>& sm, Pay<PREC, 1>* p,
+                                             const typename MarkersOf<PREC>::T& src,
+                                             const typename MarkersOf<PREC>::T& dst, int* map, double dtk,
+                                             const int* __restrict__ offsets, int* __restrict__ counts,
+                                             int base, int last, int lane, int& fl, const Prev& pv, int ovf,
+                                             const WaveRuns& ahead)
+{
+    if constexpr (PREC == 1 && IMPL) {
+        if (base < ovf) {
+            int ob[K];
+            wave_buckets<K>(g, pv, base, min(last + 1, ovf), lane, map, ob, ahead);
+            // past the end of the tile the map holds its last run
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                if (base + k * kWave + lane < ovf) p[k].cell = map[k * kWave + lane];
+        }
+    }
+    int b0, b1;
+    end_buckets<PREC, K, IMPL>(g, p, src, map, base, last, ovf, ahead.b0, b0, b1);
+    const Box box = wave_box<PREC, K, PUSH, PREC ? IMPL : PUSH>(g, sm, dtk, b0, b1, g.wbins);
+    for (int i = lane; i < box.nbins; i += kWave) map[i] = 0;
+    wave_lds_fence();
+    // place[k]: bin (or kOverflowSlot) and rank of marker k in it, in one
+    // register; kOutside and kNoMarker are negative
+    int place[K], novf = 0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        if (PUSH) p[k].push(g, sm.sE, sm.sRow, dtk, 0.0f, fl);
+        int row, col, s;
+        row_col(g, p[k], row, col);
+        const bool there = base + k * kWave + lane <= last;
+        place[k] = there ? kOutside : kNoMarker;
+        if (box.bin(g, row, col, s) && there) place[k] = (s << kRankBits) + atomicAdd(&map[s], 1);
+        const unsigned long long over = __ballot(there && (unsigned)row >= (unsigned)g.nrow);
+        if (over) {
+            if (there && (unsigned)row >= (unsigned)g.nrow)
+                place[k] = (kOverflowSlot << kRankBits) + novf + __popcll(over & ((1ull << lane) - 1));
+            novf += __popcll(over);
+        }
+    }
+    wave_lds_fence();
+    // claim each touched bin's slots: counts[] holds the slots still free,
+    // counting down from the run length, so a claim that starts at or above
+    // zero lies inside the run; the bin becomes the first claimed position.
+    // Four bins a lane at a time, so that their atomics' round trips overlap.
+    for (int i0 = lane; i0 < box.nbins; i0 += 4 * kWave) {
+        int c[4], at[4], off[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = i0 + u * kWave;
+            c[u] = i < box.nbins ? map[i] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            at[u] = off[u] = 0;
+            if (c[u]) {
+                const int b = box.bucket(g, i0 + u * kWave);
+                at[u] = atomicSub(&counts[b], c[u]) - c[u];
+                off[u] = offsets[b];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (c[u]) {
+                if (at[u] < 0) fl |= FLAG_SLOT;
+                map[i0 + u * kWave] = at[u] < 0 ? -1 : off[u] + at[u];
+            }
+    }
+    int over_first = 0;
+    if (novf) {
+        if (lane == 0) {
+            const int at = atomicSub(&counts[g.nb], novf) - novf;
+            if (at < 0) fl |= FLAG_SLOT;
+            over_first = at < 0 ? -1 : offsets[g.nb] + at;
+        }
+        over_first = __builtin_amdgcn_readfirstlane(over_first);
+    }
+    wave_lds_fence();
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        if (place[k] == kNoMarker) continue;
+        int dest;
+        if (place[k] >= 0) {
+            const int s = place[k] >> kRankBits;
+            const int first = s == kOverflowSlot ? over_first : map[s];
+            dest = first < 0 ? -1 : first + (place[k] & ((1 << kRankBits) - 1));
+        } else {
+            const int b = p[k].bucket(g);
+            const int free = atomicSub(&counts[b], 1) - 1;
+            dest = free < 0 ? -1 : offsets[b] + free;
+        }
+        if (dest < 0) { fl |= FLAG_SLOT; continue; }
+        p[k].store(dst, g, dest, false);
+    }
+    wave_lds_fence();
+}
+
+// Each wave loads its next tile's markers while the current one is pushed,
+// ranked, claimed and stored.  FP32: f and the cells of the overflow run are
+// loaded when a tile's processing starts: only its last stores need f, and few
+// tiles have such cells.  ID false: the markers carry no identities (every run
+// but an adjoint's), so the payload holds no id register.
+template <int PREC, int K, bool PUSH, bool IMPL, bool ID>
+__device__ __forceinline__ void scatter_waves(const Geo& g, typename MarkersOf<PREC>::T src, typename MarkersOf<PREC>::T dst,
+                                              const double* __restrict__ E, const RowShift* __restrict__ rows_g, double dtk,
+                                              float bk, const int* __restrict__ offsets, int* __restrict__ counts,
+                                              int* __restrict__ flags, const Prev& pv, int blk, int nblk)
+{
+    constexpr int T = kWTile<K>;
+    constexpr bool F_AHEAD = ID || PREC == 0;
     if constexpr (!ID) {
         src.id = nullptr;
         dst.id = nullptr;
     }
     extern __shared__ __align__(16) unsigned char smem[];
     SortSmem<PREC> sm(smem, g);
-    __shared__ int s_b[2], s_flags, s_aux[kSortThreads / kWave + 1];
-    const int ntiles = (g.n + kSortTile - 1) / kSortTile;
-    const int ovf = IMPL ? pv.off[g.nb] : -1;
-    if (threadIdx.x == 0) s_flags = 0;
-    if (PUSH) stage_tables<PREC>(g, sm.sE, sm.sRow, E, rows_g, bk);
-    int fl = 0;
-    Pay<PREC, VD> p[kSortMPT], q[kSortMPT];
-    int t = blockIdx.x;
-    // f is only needed when the marker is stored: each tile's f is loaded
-    // when its processing starts, not with the tile loaded ahead
-    load_tile<PREC, VD>(src, g, p, t * kSortTile, min(t * kSortTile + kSortTile, g.n) - 1, ovf, ID);
-    // implied cells: the run offsets of a tile's first pass are loaded one
-    // tile ahead, and its first run two tiles ahead (the offsets' addresses
-    // depend on it), so neither load's latency is waited for when the tile
-    // starts
-    TbAhead ah{0, 0, 0};
-    int b0n = 0;
-    if constexpr (IMPL) {
-        if (t < ntiles) ah = tile_runs_ahead(g, pv, tile_first_run(pv, t * kSortTile));
-        if (t + (int)gridDim.x < ntiles) b0n = tile_first_run(pv, (t + gridDim.x) * kSortTile);
+    const int lane = threadIdx.x & (kWave - 1), wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    int* map = sm.hist + wv * g.wbins;
+    if (PUSH) {
+        stage_tables<PREC>(g, sm.sE, sm.sRow, E, rows_g, dtk, bk);
+        __syncthreads();
     }
-    const int my_tiles = (ntiles - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;
-    for (; t < ntiles; t += gridDim.x) {
-        const int tn = t + gridDim.x;
-        prio_by_progress((t - (int)blockIdx.x) / (int)gridDim.x, my_tiles);
-        if constexpr (PREC == 1 && !ID) {
-            const int last = min(t * kSortTile + kSortTile, g.n) - 1;
+    const int ntiles = (g.n + T - 1) / T, stride = nblk * kWaves;
+    int t = blk * kWaves + wv;
+    const int ovf = IMPL ? pv.off[g.nb] : -1;
+    int fl = 0;
+    Pay<PREC, 1> p[K], q[K];
+    auto load_ahead = [&](Pay<PREC, 1>* r, int tile) {
+        const int last = min(tile * T + T, g.n) - 1;
 #pragma unroll
-            for (int k = 0; k < kSortMPT; ++k) p[k].f = src.f[min(t * kSortTile + k * kSortThreads + (int)threadIdx.x, last)];
-        }
-        if (tn < ntiles)
-            load_tile<PREC, VD>(src, g, q, tn * kSortTile, min(tn * kSortTile + kSortTile, g.n) - 1, ovf, ID);
-        TbAhead an{0, 0, 0};
-        if constexpr (IMPL) {
-            const int tnn = tn + gridDim.x;
-            if (tn < ntiles) an = tile_runs_ahead(g, pv, b0n);
-            if (tnn < ntiles) b0n = tile_first_run(pv, tnn * kSortTile);
-        }
-        scatter_tile<PREC, VD, PUSH, IMPL, IMPL>(g, sm, p, dst, dtk, bk, offsets, counts, t * kSortTile,
-                                                 min(t * kSortTile + kSortTile, g.n) - 1, s_b, fl, pv,
-                                                 ovf, s_aux, g.sbins, ah);
+        for (int k = 0; k < K; ++k) r[k].load(src, g, min(tile * T + k * kWave + lane, last), F_AHEAD, 1, !IMPL);
+    };
+    WaveRuns ah{0, 0, 0};
+    int b0n = 0;
+    if (t < ntiles) load_ahead(p, t);
+    if constexpr (IMPL) {
+        if (t < ntiles) ah = wave_runs_ahead(g, pv, tile_first_run(pv, t * T), lane);
+        if (t + stride < ntiles) b0n = tile_first_run(pv, (t + stride) * T);
+    }
+    const int mine = (ntiles - t + stride - 1) / stride;
+    for (int n = 0; t < ntiles; t += stride, ++n) {
+        prio_by_progress(n, mine);
+        const int base = t * T, last = min(base + T, g.n) - 1;
+        if constexpr (!F_AHEAD) {
 #pragma unroll
-        for (int k = 0; k < kSortMPT; ++k) p[k] = q[k];
+            for (int k = 0; k < K; ++k) p[k].f = src.f[min(base + k * kWave + lane, last)];
+        }
+        if constexpr (PREC == 1 && IMPL) {
+            if (last >= ovf) {
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    const int i = min(base + k * kWave + lane, last);
+                    if (i >= ovf) p[k].cell = src.cell[i];
+                }
+            }
+        }
+        WaveRuns an{0, 0, 0};
+        if (t + stride < ntiles) {
+            load_ahead(q, t + stride);
+            if constexpr (IMPL) an = wave_runs_ahead(g, pv, b0n, lane);
+        }
+        if constexpr (IMPL)
+            if (t + 2 * stride < ntiles) b0n = tile_first_run(pv, (t + 2 * stride) * T);
+        scatter_wave<PREC, K, PUSH, IMPL>(g, sm, p, src, dst, map, dtk, offsets, counts, base, last, lane, fl, pv, ovf, ah);
+#pragma unroll
+        for (int k = 0; k < K; ++k) p[k] = q[k];
         ah = an;
     }
-    if (fl) atomicOr(&s_flags, fl);
-    __syncthreads();
-    if (threadIdx.x == 0 && s_flags) atomicOr(flags, s_flags);
+    if (fl) atomicOr(flags, fl);
 }
 
-template <int PREC, int VD, bool PUSH, bool IMPL>
-__global__ __launch_bounds__(kSortThreads) void k_scatter(Geo g, typename MarkersOf<PREC>::T src,
-                                                          typename MarkersOf<PREC>::T dst,
-                                                          const double* __restrict__ E,
-                                                          const RowShift* __restrict__ rows_g,
-                                                          double dtk, float bk,
-                                                          const int* __restrict__ offsets,
-                                                          int* __restrict__ counts, int* __restrict__ flags, Prev pv)
+template <int PREC, int K, bool PUSH, bool IMPL, bool ID>
+__global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_eu(ID ? 4 : 5)))
+void k_scatter_w(Geo g, typename MarkersOf<PREC>::T src, typename MarkersOf<PREC>::T dst, const double* __restrict__ E,
+                 const RowShift* __restrict__ rows_g, double dtk, float bk, const int* __restrict__ offsets,
+                 int* __restrict__ counts, int* __restrict__ flags, Prev pv)
 {
-    scatter_tiled<PREC, VD, PUSH, IMPL, true>(g, src, dst, E, rows_g, dtk, bk, offsets, counts, flags, pv);
-}
-
-// The step's scatter (push, implied cells, no identities), fitted to five
-// waves per SIMD: with the smaller scatter window its LDS admits five blocks
-// per CU, and the registers are held to match.
-template <int PREC, int VD>
-__global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_eu(5)))
-void k_scatter_step(Geo g, typename MarkersOf<PREC>::T src, typename MarkersOf<PREC>::T dst,
-                    const double* __restrict__ E, const RowShift* __restrict__ rows_g, double dtk, float bk,
-                    const int* __restrict__ offsets, int* __restrict__ counts, int* __restrict__ flags, Prev pv)
-{
-    scatter_tiled<PREC, VD, true, true, false>(g, src, dst, E, rows_g, dtk, bk, offsets, counts, flags, pv);
+    scatter_waves<PREC, K, PUSH, IMPL, ID>(g, src, dst, E, rows_g, dtk, bk, offsets, counts, flags, pv, blockIdx.x, gridDim.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -842,7 +1342,7 @@ __global__ __launch_bounds__(kSortThreads) void k_push(Geo g, typename MarkersOf
     extern __shared__ __align__(16) unsigned char smem[];
     ET* sE = reinterpret_cast<ET*>(smem);
     RowShift* sRow = reinterpret_cast<RowShift*>(smem + sizeof(ET) * g.nx);
-    stage_tables<PREC>(g, sE, sRow, E, rows_g, bk);
+    stage_tables<PREC>(g, sE, sRow, E, rows_g, dtk, bk);
     __syncthreads();
     int fl = 0;
     const int base = blockIdx.x * kSortTile;
@@ -912,51 +1412,97 @@ __global__ __launch_bounds__(1024) void k_scan_tiles(int* __restrict__ tile_sums
     }
 }
 
-// Offsets of one tile of kScanTile buckets: the tile's start (the sum of the
-// preceding tiles' totals, or an already-scanned prefix when `scanned`) plus
-// an in-block exclusive scan of its counts, 16 per thread as 16-byte vectors.
-// Also clears the other parity's tile totals for the next count pass, and
-// (tfirst non-null) records for every position p = t kTfStride of the new
-// order the bucket whose run holds it: tfirst[t].
-__device__ __forceinline__ void scan_tile(const int* __restrict__ counts, int nbt, const int* __restrict__ tsum,
-                                          int scanned, int* __restrict__ tsum_next, int* __restrict__ offsets,
-                                          int tile, int* __restrict__ tfirst)
+// Where a scan tile's start comes from: the totals of the tiles before it
+// (summed here, or already scanned), or, on grids of a few tiles, the counts
+// before it themselves, which saves the totals' launch.
+enum : int { SCAN_TOTALS = 0, SCAN_PREFIXED = 1, SCAN_COUNTS = 2 };
+constexpr int kScanDirect = 24;                      // tiles up to which the counts are summed
+
+// This thread's part of the sum of counts [first, last), first a multiple of
+// 4: 16-byte loads, eight in flight.
+__device__ __forceinline__ int scan_part(const int* __restrict__ counts, int nbt, int first, int last)
 {
-    __shared__ int s_w[kScanThreads / kWave + 1];
-    __shared__ int s_pre;
+    int s = 0;
+    for (int i = first + 4 * (int)threadIdx.x; i < last; i += 8 * 4 * kScanThreads) {
+        int4 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int b = i + u * 4 * kScanThreads;
+            v[u] = make_int4(0, 0, 0, 0);
+            if (b + 4 <= last) {
+                v[u] = *reinterpret_cast<const int4*>(counts + b);
+            } else if (b < last) {
+                v[u].x = counts[b];
+                if (b + 1 < last) v[u].y = counts[b + 1];
+                if (b + 2 < last) v[u].z = counts[b + 2];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += (v[u].x + v[u].y) + (v[u].z + v[u].w);
+    }
+    return s;
+}
+
+// Total of one tile of kScanTile bucket counts.
+__device__ __forceinline__ void scan_total(const int* __restrict__ counts, int nbt, int* __restrict__ tsum, int tile)
+{
+    __shared__ int s_w[kScanThreads / kWave];
+    const int inc = wave_incl_scan(scan_part(counts, nbt, tile * kScanTile, min((tile + 1) * kScanTile, nbt)));
+    if ((threadIdx.x & (kWave - 1)) == kWave - 1) s_w[threadIdx.x / kWave] = inc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int t = 0;
+        for (int q = 0; q < kScanThreads / kWave; ++q) t += s_w[q];
+        tsum[tile] = t;
+    }
+}
+
+__global__ __launch_bounds__(kScanThreads) void k_scan_total(const int* __restrict__ counts, int nbt, int* __restrict__ tsum)
+{
+    scan_total(counts, nbt, tsum, blockIdx.x);
+}
+
+// Offsets of one tile of kScanTile buckets: the tile's start plus an in-block
+// exclusive scan of its counts, four per thread, both reduced behind one
+// barrier.  Also (tfirst non-null) records for every position p = t kTfStride
+// of the new order the bucket whose run holds it: tfirst[t].
+__device__ __forceinline__ void scan_tile(const int* __restrict__ counts, int nbt, const int* __restrict__ tsum,
+                                          int from, int* __restrict__ offsets, int tile, int* __restrict__ tfirst)
+{
+    constexpr int W = kScanThreads / kWave;
+    __shared__ int s_pre[W], s_cnt[W];
     // the tile's counts first, so their loads overlap the tile-start sum
     const int base = tile * kScanTile + threadIdx.x * kScanItems;
-    int c[kScanItems];
+    int c[kScanItems] = {0, 0, 0, 0};
     if (base + kScanItems <= nbt) {
-#pragma unroll
-        for (int k = 0; k < kScanItems; k += 4) {
-            const int4 v = *reinterpret_cast<const int4*>(counts + base + k);
-            c[k] = v.x; c[k + 1] = v.y; c[k + 2] = v.z; c[k + 3] = v.w;
-        }
+        const int4 v = *reinterpret_cast<const int4*>(counts + base);
+        c[0] = v.x; c[1] = v.y; c[2] = v.z; c[3] = v.w;
     } else {
 #pragma unroll
-        for (int k = 0; k < kScanItems; ++k) c[k] = (base + k < nbt) ? counts[base + k] : 0;
+        for (int k = 0; k < kScanItems; ++k)
+            if (base + k < nbt) c[k] = counts[base + k];
     }
-    // tile start
-    int pre;
-    if (scanned) {
-        pre = tsum[tile];
-    } else {
-        int part = 0;
-        for (int t = threadIdx.x; t < tile; t += blockDim.x) part += tsum[t];
-        int excl;
-        pre = block_excl_scan(part, &excl, s_w);
-    }
-    if (threadIdx.x == 0) {
-        s_pre = pre;
-        tsum_next[tile] = 0;
-    }
-    int s = 0;
+    int part = 0;
+    if (from == SCAN_COUNTS) part = scan_part(counts, nbt, 0, tile * kScanTile);
+    else if (from == SCAN_TOTALS)
+        for (int t = threadIdx.x; t < tile; t += kScanThreads) part += tsum[t];
+    const int s = (c[0] + c[1]) + (c[2] + c[3]);
+    const int inc = wave_incl_scan(s);
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
 #pragma unroll
-    for (int k = 0; k < kScanItems; ++k) s += c[k];
-    int excl;
-    block_excl_scan(s, &excl, s_w);
-    int run = excl + s_pre;
+    for (int o = kWave / 2; o > 0; o >>= 1) part += __shfl_xor(part, o, kWave);
+    if (lane == kWave - 1) {
+        s_cnt[w] = inc;
+        s_pre[w] = part;
+    }
+    __syncthreads();
+    int run = inc - s;
+    if (from == SCAN_PREFIXED) run += tsum[tile];
+#pragma unroll
+    for (int q = 0; q < W; ++q) {
+        if (from != SCAN_PREFIXED) run += s_pre[q];
+        run += q < w ? s_cnt[q] : 0;
+    }
     int o[kScanItems];
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) {
@@ -970,9 +1516,7 @@ __device__ __forceinline__ void scan_tile(const int* __restrict__ counts, int nb
                 tfirst[t] = base + k;
     }
     if (base + kScanItems <= nbt) {
-#pragma unroll
-        for (int k = 0; k < kScanItems; k += 4)
-            *reinterpret_cast<int4*>(offsets + base + k) = make_int4(o[k], o[k + 1], o[k + 2], o[k + 3]);
+        *reinterpret_cast<int4*>(offsets + base) = make_int4(o[0], o[1], o[2], o[3]);
     } else {
 #pragma unroll
         for (int k = 0; k < kScanItems; ++k)
@@ -981,131 +1525,184 @@ __device__ __forceinline__ void scan_tile(const int* __restrict__ counts, int nb
 }
 
 __global__ __launch_bounds__(kScanThreads) void k_scan_apply(const int* __restrict__ counts, int nbt,
-                                                            const int* __restrict__ tsum, int scanned,
-                                                            int* __restrict__ tsum_next, int* __restrict__ offsets,
-                                                            int* __restrict__ tfirst)
+                                                            const int* __restrict__ tsum, int from,
+                                                            int* __restrict__ offsets, int* __restrict__ tfirst)
 {
-    scan_tile(counts, nbt, tsum, scanned, tsum_next, offsets, blockIdx.x, tfirst);
+    scan_tile(counts, nbt, tsum, from, offsets, blockIdx.x, tfirst);
 }
 
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
+// LDS of the block kernels: tables and window histogram, which also holds a
+// tile's implied buckets (FP32 1D-1V).
 template <int PREC>
-static size_t sort_smem(const Geo& g, bool push)
+static size_t sort_smem(const Geo& g)
 {
-    (void)push;
     size_t e = sizeof(typename MarkersOf<PREC>::E) * g.nx;
     size_t r = PREC ? sizeof(RowShift) * (g.nv[0] + 1) : 0;
-    // the histogram's LDS also holds a tile's implied buckets (FP32 1D-1V)
     const int bins = (PREC == 1 && g.vdim == 1) ? std::max(g.hist_bins, kCountTile) : g.hist_bins;
     return ((e + r + 15) & ~(size_t)15) + sizeof(int) * bins;
 }
 
-// LDS of the step's scatter (FP32 1D-1V): a window of at most sbins buckets,
-// and a scatter tile's implied buckets.
-static size_t scatter_step_smem(const Geo& g)
+// Markers a lane (K) of the wave kernels.  Small sorts are latency: four a lane
+// is a shorter chain and twice the waves.  Large ones pay for every claim and
+// flush, and tiles of 512 share each bin among more markers.  Measured, us, 4 /
+// 8 a lane: FP32 count 8.0 / 8.8 at 1.0M markers, 13.3 / 14.1 at 4.2M, 21.4 /
+// 19.4 at 8.4M, 37.5 / 30.3 at 16.8M; FP32 scatter 12.1 / 16.7, 26.4 / 27.6,
+// 43.7 / 45.9, 99.2 / 86.4 (65.2 / 67.8 the other way round at 12.6M); FP64
+// count 8.3 / 9.5, 16.7 / 17.2, 27.1 / 27.5, 55.8 / 53.4.  The FP64 scatter
+// has registers for four only.
+static int count_mpl(const Geo& g) { return g.n < (g.prec ? 5 << 20 : 12 << 20) ? 4 : 8; }
+static int scatter_mpl(const Geo& g) { return g.prec == 0 || g.n < 10 << 20 ? 4 : 8; }
+
+// The FP64 scatter of large, dense sorts goes by blocks of 2048 markers instead:
+// tiles of 256 span 32 columns or fewer at 8 markers a cell, and the bins at
+// their ends are claimed twice (block / wave: 141 / 156 us at 16.8M markers, 16
+// a cell, 77 / 79 us at 8.4M, 8 a cell, on 1024 columns).  Not on sparse rows
+// (85 / 81 us at 8.4M, 4 a cell) nor on wide grids, whose bucket rows leave a
+// block's LDS window less room (179 / 158 us at 16.8M, 8 a cell, on 2048).
+static bool block_scatter64(const Geo& g)
 {
-    size_t e = sizeof(float2) * g.nx;
-    size_t r = sizeof(RowShift) * (g.nv[0] + 1);
-    return ((e + r + 15) & ~(size_t)15) + sizeof(int) * std::max(g.sbins, kSortTile);
+    return g.prec == 0 && g.n >= 1 << 23 && g.nx <= 1024 && g.n / 8 >= g.nb;
+}
+
+// LDS of the wave kernels (1D-1V): tables, and each wave's window (which also
+// holds a tile's implied buckets in FP32).
+template <int PREC>
+static size_t wave_smem(const Geo& g)
+{
+    size_t e = sizeof(typename MarkersOf<PREC>::E) * g.nx;
+    size_t r = PREC ? sizeof(RowShift) * (g.nv[0] + 1) : 0;
+    return ((e + r + 15) & ~(size_t)15) + sizeof(int) * kWaves * g.wbins;
+}
+
+// The 1D-1V kernels of one sort phase (0 count, 2 scatter).
+template <int PREC>
+static hipError_t launch_sort_1v(const Geo& g, const typename MarkersOf<PREC>::T& s, const typename MarkersOf<PREC>::T& d,
+                                 const double* E, const RowShift* rows, double dtk, float bk, int* counts, int* offsets,
+                                 int* flags, bool push, hipStream_t st, int phase, const Prev& pv)
+{
+    constexpr bool F = PREC == 1;                    // the form with implied cells
+    const bool impl = pv.off != nullptr;
+    const dim3 bl(kSortThreads);
+    // Markers whose kicks differ by more rows than a wave's window holds fall
+    // outside it.  Where the loaded state's kicks reach a velocity cell the
+    // step takes the block kernels, whose window follows the kick column by
+    // column.
+    if (push && impl == F && g.follow) {
+        static int granted[2] = {};
+        const size_t smem = sort_smem<PREC>(g);
+        const int tile = phase == 0 ? count_tile_size(PREC) : kSortTile;
+        const dim3 gr((g.n + tile - 1) / tile);
+        hipError_t e = ensure_lds(phase == 0 ? (const void*)k_count<PREC, 1, true, F> : (const void*)k_scatter1<PREC, 1, true, F>,
+                                  smem, granted[phase != 0]);
+        if (e != hipSuccess) return e;
+        if (phase == 0) launch(k_count<PREC, 1, true, F>, gr, bl, smem, st, g, s, E, rows, dtk, bk, counts, flags, pv);
+        else launch(k_scatter1<PREC, 1, true, F>, gr, bl, smem, st, g, s, d, E, rows, dtk, bk, offsets, counts, flags, pv);
+        return hipGetLastError();
+    }
+    const size_t smem = wave_smem<PREC>(g);
+    // blocks of four waves for every tile, at most what is resident
+    auto grid = [&](int mpl, int resident) {
+        const int tiles = (g.n + kWave * mpl - 1) / (kWave * mpl);
+        return dim3(std::min((tiles + kWaves - 1) / kWaves, resident));
+    };
+    if (phase == 0) {
+        using K = decltype(&k_count_w<PREC, 8, true, F>);
+        static const K fns[8] = {k_count_w<PREC, 8, false, false>, k_count_w<PREC, 8, false, F>,
+                                 k_count_w<PREC, 8, true, false>,  k_count_w<PREC, 8, true, F>,
+                                 k_count_w<PREC, 4, false, false>, k_count_w<PREC, 4, false, F>,
+                                 k_count_w<PREC, 4, true, false>,  k_count_w<PREC, 4, true, F>};
+        static int granted[8] = {};
+        const int mpl = count_mpl(g), v = (mpl == 4 ? 4 : 0) + 2 * (push ? 1 : 0) + (impl ? 1 : 0);
+        hipError_t e = ensure_lds((const void*)fns[v], smem, granted[v]);
+        if (e != hipSuccess) return e;
+        launch(fns[v], grid(mpl, g.cblocks), bl, smem, st, g, s, E, rows, dtk, bk, counts, flags, pv);
+        return hipGetLastError();
+    }
+    if (block_scatter64(g)) {
+        static int granted[2] = {};
+        const size_t sb = sort_smem<PREC>(g);
+        hipError_t e = ensure_lds(push ? (const void*)k_scatter1<0, 1, true> : (const void*)k_scatter1<0, 1, false>, sb,
+                                  granted[push ? 1 : 0]);
+        if (e != hipSuccess) return e;
+        const dim3 gr((g.n + kSortTile - 1) / kSortTile);
+        if constexpr (PREC == 0) {
+            if (push) launch(k_scatter1<0, 1, true>, gr, bl, sb, st, g, s, d, E, rows, dtk, bk, offsets, counts, flags, pv);
+            else launch(k_scatter1<0, 1, false>, gr, bl, sb, st, g, s, d, E, rows, dtk, bk, offsets, counts, flags, pv);
+        }
+        return hipGetLastError();
+    }
+    constexpr int KB = PREC ? 8 : 4;
+    using K = decltype(&k_scatter_w<PREC, KB, true, F, true>);
+    static const K fns[16] = {
+        k_scatter_w<PREC, KB, false, false, false>, k_scatter_w<PREC, KB, false, false, true>,
+        k_scatter_w<PREC, KB, false, F, false>,     k_scatter_w<PREC, KB, false, F, true>,
+        k_scatter_w<PREC, KB, true, false, false>,  k_scatter_w<PREC, KB, true, false, true>,
+        k_scatter_w<PREC, KB, true, F, false>,      k_scatter_w<PREC, KB, true, F, true>,
+        k_scatter_w<PREC, 4, false, false, false>,  k_scatter_w<PREC, 4, false, false, true>,
+        k_scatter_w<PREC, 4, false, F, false>,      k_scatter_w<PREC, 4, false, F, true>,
+        k_scatter_w<PREC, 4, true, false, false>,   k_scatter_w<PREC, 4, true, false, true>,
+        k_scatter_w<PREC, 4, true, F, false>,       k_scatter_w<PREC, 4, true, F, true>};
+    static int granted[16] = {};
+    const int mpl = scatter_mpl(g), v = (mpl == 4 ? 8 : 0) + 4 * (push ? 1 : 0) + 2 * (impl ? 1 : 0) + (s.id ? 1 : 0);
+    hipError_t e = ensure_lds((const void*)fns[v], smem, granted[v]);
+    if (e != hipSuccess) return e;
+    launch(fns[v], grid(mpl, s.id ? g.sblocks : g.sblocks_step), bl, smem, st, g, s, d, E, rows, dtk, bk,
+           (const int*)offsets, counts, flags, pv);
+    return hipGetLastError();
 }
 
 template <int PREC, int VD>
 static hipError_t launch_sort_t(const Geo& g, void* src, void* dst, const double* E, const RowShift* rows,
-                                double dtk, float bk, int* counts, int* offsets, int* tile_sums, int* tile_next,
-                                int* flags, bool push, hipStream_t st, int phase, const int* off_old,
-                                const int* tf_old, int* tf_new)
+                                double dtk, float bk, int* counts, int* offsets, int* tile_sums, int* flags, bool push,
+                                hipStream_t st, int phase, const int* off_old, const int* tf_old, int* tf_new)
 {
     using MT = typename MarkersOf<PREC>::T;
     MT s = *reinterpret_cast<MT*>(src);
     MT d = dst ? *reinterpret_cast<MT*>(dst) : s;
-    // The FP32 1D-1V form uses the tiled count and scatter (one block per
-    // resident slot, each walking several tiles; the scatter loads the next
-    // while working on the current one) and implied cells when the markers
-    // are in a sorted order (off_old); the other forms hold more registers
-    // per marker and use one tile per block.
-    constexpr bool tiled = PREC == 1 && VD == 1;
-    const bool impl = tiled && off_old != nullptr;
     const Prev pv{off_old, tf_old};
-    const int ctiles = (g.n + count_tile_size(PREC) - 1) / count_tile_size(PREC);
-    const int cblocks = tiled && g.cblocks > 0 ? std::min(ctiles, g.cblocks) : ctiles;
-    const int stiles = (g.n + kSortTile - 1) / kSortTile;
-    const int sblocks = tiled && g.sblocks > 0 ? std::min(stiles, g.sblocks) : stiles;
-    const size_t smem = sort_smem<PREC>(g, push);
     if (g.n == 0 && phase != 1) return hipSuccess;   // the scan still runs: offsets become zero
-    static int granted[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    {
-        const void* fns[8];
-        if constexpr (tiled) {
-            fns[0] = (const void*)k_count_tiled<PREC, VD, true, false>;
-            fns[1] = (const void*)k_count_tiled<PREC, VD, false, false>;
-            fns[2] = (const void*)k_scatter<PREC, VD, true, false>;
-            fns[3] = (const void*)k_scatter<PREC, VD, false, false>;
-            fns[4] = (const void*)k_count_tiled<PREC, VD, true, true>;
-            fns[5] = (const void*)k_count_tiled<PREC, VD, false, true>;
-            fns[6] = (const void*)k_scatter<PREC, VD, true, true>;
-            fns[7] = (const void*)k_scatter<PREC, VD, false, true>;
-        } else {
-            fns[0] = fns[4] = (const void*)k_count<PREC, VD, true>;
-            fns[1] = fns[5] = (const void*)k_count<PREC, VD, false>;
-            fns[2] = fns[6] = (const void*)k_scatter1<PREC, VD, true>;
-            fns[3] = fns[7] = (const void*)k_scatter1<PREC, VD, false>;
+    if (phase == 1) {
+        const int nbt = g.nb + 1;
+        const int ntiles = (nbt + kScanTile - 1) / kScanTile;
+        int from = SCAN_COUNTS;
+        if (ntiles > kScanDirect) {
+            hipLaunchKernelGGL(k_scan_total, dim3(ntiles), dim3(kScanThreads), 0, st, counts, nbt, tile_sums);
+            from = SCAN_TOTALS;
         }
-        for (int i = 0; i < 8; ++i) {
+        if (ntiles > 1024) {
+            hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(1024), 0, st, tile_sums, ntiles);
+            from = SCAN_PREFIXED;
+        }
+        hipLaunchKernelGGL(k_scan_apply, dim3(ntiles), dim3(kScanThreads), 0, st, counts, nbt, tile_sums, from, offsets,
+                           tf_new);
+        return hipGetLastError();
+    }
+    if constexpr (VD == 1) {
+        return launch_sort_1v<PREC>(g, s, d, E, rows, dtk, bk, counts, offsets, flags, push, st, phase, pv);
+    } else {
+        // the other forms hold more registers a marker: a block a tile
+        const size_t smem = sort_smem<PREC>(g);
+        static int granted[4] = {};
+        const void* fns[4] = {(const void*)k_count<PREC, VD, true>, (const void*)k_count<PREC, VD, false>,
+                              (const void*)k_scatter1<PREC, VD, true>, (const void*)k_scatter1<PREC, VD, false>};
+        for (int i = 0; i < 4; ++i) {
             hipError_t e = ensure_lds(fns[i], smem, granted[i]);
             if (e != hipSuccess) return e;
         }
-    }
-    const dim3 bl(kSortThreads);
-    if (phase == 0) {
-        if constexpr (tiled) {
-            const dim3 gr(cblocks);
-            if (impl) {
-                if (push) launch(k_count_tiled<PREC, VD, true, true>, gr, bl, smem, st, g, s, E, rows, dtk, bk, counts, tile_sums, flags, pv);
-                else launch(k_count_tiled<PREC, VD, false, true>, gr, bl, smem, st, g, s, E, rows, dtk, bk, counts, tile_sums, flags, pv);
-            } else {
-                if (push) launch(k_count_tiled<PREC, VD, true, false>, gr, bl, smem, st, g, s, E, rows, dtk, bk, counts, tile_sums, flags, pv);
-                else launch(k_count_tiled<PREC, VD, false, false>, gr, bl, smem, st, g, s, E, rows, dtk, bk, counts, tile_sums, flags, pv);
-            }
+        const dim3 bl(kSortThreads);
+        const dim3 cg(((g.n + count_tile_size(PREC) - 1) / count_tile_size(PREC) + 7) & ~7), sg(((g.n + kSortTile - 1) / kSortTile + 7) & ~7);
+        if (phase == 0) {
+            if (push) launch(k_count<PREC, VD, true>, cg, bl, smem, st, g, s, E, rows, dtk, bk, counts, flags, pv);
+            else launch(k_count<PREC, VD, false>, cg, bl, smem, st, g, s, E, rows, dtk, bk, counts, flags, pv);
         } else {
-            if (push) launch(k_count<PREC, VD, true>, dim3(cblocks), bl, smem, st, g, s, E, rows, dtk, bk, counts, tile_sums, flags);
-            else launch(k_count<PREC, VD, false>, dim3(cblocks), bl, smem, st, g, s, E, rows, dtk, bk, counts, tile_sums, flags);
+            if (push) launch(k_scatter1<PREC, VD, true>, sg, bl, smem, st, g, s, d, E, rows, dtk, bk, offsets, counts, flags, pv);
+            else launch(k_scatter1<PREC, VD, false>, sg, bl, smem, st, g, s, d, E, rows, dtk, bk, offsets, counts, flags, pv);
         }
-    } else if (phase == 1) {
-        // tile_sums: this sort's totals; tile_next: the other parity, cleared here
-        const int nbt = g.nb + 1;
-        const int ntiles = (nbt + kScanTile - 1) / kScanTile;
-        int scanned = 0;
-        if (ntiles > 1024) {
-            hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(1024), 0, st, tile_sums, ntiles);
-            scanned = 1;
-        }
-        hipLaunchKernelGGL(k_scan_apply, dim3(ntiles), dim3(kScanThreads), 0, st, counts, nbt, tile_sums, scanned,
-                           tile_next, offsets, tf_new);
-    } else {
-        if constexpr (tiled) {
-            const dim3 gr(sblocks);
-            if (impl) {
-                if (push && !s.id) {
-                    static int granted_step = 0;
-                    const size_t sm_step = scatter_step_smem(g);
-                    hipError_t e = ensure_lds((const void*)k_scatter_step<PREC, VD>, sm_step, granted_step);
-                    if (e != hipSuccess) return e;
-                    launch(k_scatter_step<PREC, VD>, dim3(g.sblocks_step > 0 ? std::min(stiles, g.sblocks_step) : stiles),
-                           bl, sm_step, st, g, s, d, E, rows, dtk, bk, offsets, counts, flags, pv);
-                } else if (push) launch(k_scatter<PREC, VD, true, true>, gr, bl, smem, st, g, s, d, E, rows, dtk, bk, offsets, counts, flags, pv);
-                else launch(k_scatter<PREC, VD, false, true>, gr, bl, smem, st, g, s, d, E, rows, dtk, bk, offsets, counts, flags, pv);
-            } else {
-                if (push) launch(k_scatter<PREC, VD, true, false>, gr, bl, smem, st, g, s, d, E, rows, dtk, bk, offsets, counts, flags, pv);
-                else launch(k_scatter<PREC, VD, false, false>, gr, bl, smem, st, g, s, d, E, rows, dtk, bk, offsets, counts, flags, pv);
-            }
-        } else {
-            if (push) launch(k_scatter1<PREC, VD, true>, dim3(sblocks), bl, smem, st, g, s, d, E, rows, dtk, bk, offsets, counts, flags);
-            else launch(k_scatter1<PREC, VD, false>, dim3(sblocks), bl, smem, st, g, s, d, E, rows, dtk, bk, offsets, counts, flags);
-        }
+        return hipGetLastError();
     }
-    return hipGetLastError();
 }
 
 // phase 0 = count, 1 = scan, 2 = scatter.  offsets: the run offsets of the new
@@ -1114,13 +1711,13 @@ static hipError_t launch_sort_t(const Geo& g, void* src, void* dst, const double
 // cell index is stored); tf_new (may be null): the scan's record of the new
 // order's tile starts.
 hipError_t launch_sort(const Geo& g, void* src, void* dst, const double* E, const RowShift* rows,
-                       double dtk, float bk, int* counts, int* offsets, int* tile_sums, int* tile_next, int* flags,
+                       double dtk, float bk, int* counts, int* offsets, int* tile_sums, int* flags,
                        bool push, hipStream_t st, int phase, const int* off_old, const int* tf_old, int* tf_new)
 {
-    if (g.prec == 0 && g.vdim == 1) return launch_sort_t<0, 1>(g, src, dst, E, rows, dtk, bk, counts, offsets, tile_sums, tile_next, flags, push, st, phase, nullptr, nullptr, tf_new);
-    if (g.prec == 0 && g.vdim == 3) return launch_sort_t<0, 3>(g, src, dst, E, rows, dtk, bk, counts, offsets, tile_sums, tile_next, flags, push, st, phase, nullptr, nullptr, tf_new);
-    if (g.prec == 1 && g.vdim == 1) return launch_sort_t<1, 1>(g, src, dst, E, rows, dtk, bk, counts, offsets, tile_sums, tile_next, flags, push, st, phase, off_old, tf_old, tf_new);
-    return launch_sort_t<1, 3>(g, src, dst, E, rows, dtk, bk, counts, offsets, tile_sums, tile_next, flags, push, st, phase, nullptr, nullptr, tf_new);
+    if (g.prec == 0 && g.vdim == 1) return launch_sort_t<0, 1>(g, src, dst, E, rows, dtk, bk, counts, offsets, tile_sums, flags, push, st, phase, nullptr, nullptr, tf_new);
+    if (g.prec == 0 && g.vdim == 3) return launch_sort_t<0, 3>(g, src, dst, E, rows, dtk, bk, counts, offsets, tile_sums, flags, push, st, phase, nullptr, nullptr, tf_new);
+    if (g.prec == 1 && g.vdim == 1) return launch_sort_t<1, 1>(g, src, dst, E, rows, dtk, bk, counts, offsets, tile_sums, flags, push, st, phase, off_old, tf_old, tf_new);
+    return launch_sort_t<1, 3>(g, src, dst, E, rows, dtk, bk, counts, offsets, tile_sums, flags, push, st, phase, nullptr, nullptr, tf_new);
 }
 
 // ---------------------------------------------------------------------------
@@ -1140,8 +1737,17 @@ __global__ __launch_bounds__(kSortThreads) void k_count_b(const BInst* __restric
     const int* pr = pre + BPRE_COUNT * (ninst + 1);
     const int i = find_inst(pr, ninst, blockIdx.x);
     const BInst& I = tab[i];
-    count_block<PREC, 1, true, PREC == 1>(I.g, bmark<PREC>(I, cur), I.E, I.rows, I.dtk, I.bk, I.counts, I.tsum[cur],
-                                          I.flags, blockIdx.x - pr[i], Prev{I.offsets[cur], I.tfirst[cur]});
+    count_waves<PREC, PREC ? 8 : 4, true, PREC == 1>(I.g, bmark<PREC>(I, cur), I.E, I.rows, I.dtk, I.bk, I.counts, I.flags,
+                                       Prev{I.offsets[cur], I.tfirst[cur]}, blockIdx.x - pr[i], pr[i + 1] - pr[i]);
+}
+
+__global__ __launch_bounds__(kScanThreads) void k_scan_total_b(const BInst* __restrict__ tab, const int* __restrict__ pre,
+                                                               int ninst)
+{
+    const int* pr = pre + BPRE_SCAN * (ninst + 1);
+    const int i = find_inst(pr, ninst, blockIdx.x);
+    const BInst& I = tab[i];
+    scan_total(I.counts, I.g.nb + 1, I.tsum, blockIdx.x - pr[i]);
 }
 
 __global__ __launch_bounds__(kScanThreads) void k_scan_b(const BInst* __restrict__ tab, const int* __restrict__ pre,
@@ -1150,10 +1756,10 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_b(const BInst* __restrict
     const int* pr = pre + BPRE_SCAN * (ninst + 1);
     const int i = find_inst(pr, ninst, blockIdx.x);
     const BInst& I = tab[i];
-    scan_tile(I.counts, I.g.nb + 1, I.tsum[cur], 0, I.tsum[1 - cur], I.offsets[1 - cur], blockIdx.x - pr[i],
-              I.tfirst[1 - cur]);
+    scan_tile(I.counts, I.g.nb + 1, I.tsum, SCAN_TOTALS, I.offsets[1 - cur], blockIdx.x - pr[i], I.tfirst[1 - cur]);
 }
 
+// Batch instances carry no marker identities.
 template <int PREC>
 __global__ __launch_bounds__(kSortThreads) void k_scatter_b(const BInst* __restrict__ tab,
                                                             const int* __restrict__ pre, int ninst, int cur)
@@ -1161,82 +1767,58 @@ __global__ __launch_bounds__(kSortThreads) void k_scatter_b(const BInst* __restr
     const int* pr = pre + BPRE_SCATTER * (ninst + 1);
     const int i = find_inst(pr, ninst, blockIdx.x);
     const BInst& I = tab[i];
-    // batch instances carry no marker identities: with the null pointers
-    // known at compile time the payload holds no id register
-    typename MarkersOf<PREC>::T src = bmark<PREC>(I, cur), dst = bmark<PREC>(I, 1 - cur);
-    src.id = nullptr;
-    dst.id = nullptr;
-    scatter_block<PREC, 1, true, PREC == 1>(I.g, src, dst, I.E, I.rows, I.dtk, I.bk, I.offsets[1 - cur], I.counts,
-                                            I.flags, blockIdx.x - pr[i], Prev{I.offsets[cur], I.tfirst[cur]},
-                                            PREC == 1 ? I.g.sbins : I.g.hist_bins);
+    scatter_waves<PREC, PREC ? 8 : 4, true, PREC == 1, false>(I.g, bmark<PREC>(I, cur), bmark<PREC>(I, 1 - cur), I.E, I.rows, I.dtk, I.bk,
+                                                I.offsets[1 - cur], I.counts, I.flags,
+                                                Prev{I.offsets[cur], I.tfirst[cur]}, blockIdx.x - pr[i],
+                                                pr[i + 1] - pr[i]);
 }
 
-// Blocks of a batched pass for one instance (host side).
+// Blocks of a batched pass for one instance (host side): a scan tile each, or
+// four waves with a tile each.
 int sort_blocks(const Geo& g, int phase)
 {
-    if (phase == 0) return (g.n + count_tile_size(g.prec) - 1) / count_tile_size(g.prec);
     if (phase == 1) return (g.nb + 1 + kScanTile - 1) / kScanTile;
-    return (g.n + kSortTile - 1) / kSortTile;
+    const int tile = kWaves * (g.prec ? kWTile<8> : kWTile<4>);
+    return (g.n + tile - 1) / tile;
 }
 
-// Blocks of the tiled scatter that fit on one CU at once for g's LDS size
-// (0 where the form has no tiled scatter); host side.
-// Resident blocks per CU of the tiled count pass (FP32 1D-1V) for this
-// geometry's LDS; 0 (a tile per block) for the other forms.
-int count_blocks_per_cu(const Geo& g)
+// Resident blocks per CU of a wave kernel for this geometry's LDS (1D-1V).
+static int wave_blocks_per_cu(const Geo& g, const void* f64, const void* f32, int (&granted)[2])
 {
-    if (!(g.prec == 1 && g.vdim == 1)) return 0;
-    const size_t smem = sort_smem<1>(g, true);
-    static int granted = 0;
+    if (g.vdim != 1) return 0;
+    const void* fn = g.prec ? f32 : f64;
+    const size_t smem = g.prec ? wave_smem<1>(g) : wave_smem<0>(g);
     int per_cu = 0;
-    if (ensure_lds((const void*)k_count_tiled<1, 1, true, true>, smem, granted) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)k_count_tiled<1, 1, true, true>,
-                                                     kSortThreads, smem) != hipSuccess ||
-        per_cu <= 0) {
+    if (ensure_lds(fn, smem, granted[g.prec]) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kSortThreads, smem) != hipSuccess || per_cu <= 0) {
         (void)hipGetLastError();
-        per_cu = 0;
+        per_cu = 4;
     }
     return per_cu;
+}
+
+int count_blocks_per_cu(const Geo& g)
+{
+    static int granted[2] = {};
+    return wave_blocks_per_cu(g, (const void*)k_count_w<0, 8, true, false>, (const void*)k_count_w<1, 8, true, true>, granted);
 }
 
 int scatter_step_blocks_per_cu(const Geo& g)
 {
-    if (!(g.prec == 1 && g.vdim == 1)) return 0;
-    const size_t smem = scatter_step_smem(g);
-    static int granted = 0;
-    int per_cu = 0;
-    if (ensure_lds((const void*)k_scatter_step<1, 1>, smem, granted) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)k_scatter_step<1, 1>, kSortThreads,
-                                                     smem) != hipSuccess ||
-        per_cu <= 0) {
-        (void)hipGetLastError();
-        per_cu = 4;
-    }
-    return per_cu;
+    static int granted[2] = {};
+    return wave_blocks_per_cu(g, (const void*)k_scatter_w<0, 4, true, false, false>,
+                              (const void*)k_scatter_w<1, 8, true, true, false>, granted);
 }
 
 int scatter_blocks_per_cu(const Geo& g)
 {
-    if (!(g.prec == 1 && g.vdim == 1)) return 0;
-    const size_t smem = sort_smem<1>(g, true);
-    static int granted = 0;
-    int per_cu = 0;
-    if (ensure_lds((const void*)k_scatter<1, 1, true, true>, smem, granted) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)k_scatter<1, 1, true, true>, kSortThreads,
-                                                     smem) != hipSuccess ||
-        per_cu <= 0) {
-        (void)hipGetLastError();
-        per_cu = 4;
-    }
-    return per_cu;
+    static int granted[2] = {};
+    return wave_blocks_per_cu(g, (const void*)k_scatter_w<0, 4, true, false, true>,
+                              (const void*)k_scatter_w<1, 8, true, true, true>, granted);
 }
 
-// LDS of the count and scatter blocks for one instance (host side).
-size_t sort_lds(const Geo& g) { return g.prec ? sort_smem<1>(g, true) : sort_smem<0>(g, true); }
-
-// LDS of the batched scatter for one instance: the FP32 form's window is the
-// step scatter's (sbins buckets), the FP64 form's the count's.
-size_t scatter_lds(const Geo& g) { return g.prec ? scatter_step_smem(g) : sort_smem<0>(g, true); }
+// LDS of the batched count and scatter for one instance (host side).
+size_t sort_lds(const Geo& g) { return g.prec ? wave_smem<1>(g) : wave_smem<0>(g); }
 
 // phase 0 = count (with push), 1 = scan, 2 = scatter, over `blocks` blocks
 hipError_t launch_sort_batch(int prec, const BInst* tab, const int* pre, int ninst, int blocks, size_t smem, int cur,
@@ -1256,6 +1838,7 @@ hipError_t launch_sort_batch(int prec, const BInst* tab, const int* pre, int nin
         if (prec == 0) hipLaunchKernelGGL(k_count_b<0>, gr, dim3(kSortThreads), smem, st, tab, pre, ninst, cur);
         else hipLaunchKernelGGL(k_count_b<1>, gr, dim3(kSortThreads), smem, st, tab, pre, ninst, cur);
     } else if (phase == 1) {
+        hipLaunchKernelGGL(k_scan_total_b, gr, dim3(kScanThreads), 0, st, tab, pre, ninst);
         hipLaunchKernelGGL(k_scan_b, gr, dim3(kScanThreads), 0, st, tab, pre, ninst, cur);
     } else {
         if (prec == 0) hipLaunchKernelGGL(k_scatter_b<0>, gr, dim3(kSortThreads), smem, st, tab, pre, ninst, cur);

@@ -9,7 +9,7 @@ choices already made for the earlier ones):
 * ``TUNE_RECON_FORM``, the FP32 reconstruction's row form: dense rows issue
   every register load of a row segment, sparse rows skip the loads past it
   (worth it when segments are well below the register capacity);
-* ``TUNE_SORT_BLOCKS``, resident blocks per compute unit of the tiled count
+* ``TUNE_SORT_BLOCKS``, resident blocks per compute unit of the wave count
   and scatter passes of a single FP32 instance (fewer blocks each walk more
   tiles; a batch's sort passes take a block per tile and ignore it).
 
