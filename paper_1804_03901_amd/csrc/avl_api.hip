@@ -62,6 +62,7 @@ hipError_t launch_scale_f64(double* p, int n, double s, hipStream_t st);
 int sort_blocks(const Geo& g, int phase);
 size_t sort_lds(const Geo& g);
 int recon_waves_per_cu(int prec, int lds_per_cu);
+int recon3_waves_per_cu(int prec);
 int scatter_blocks_per_cu(const Geo& g);
 int scatter_step_blocks_per_cu(const Geo& g);
 int count_blocks_per_cu(const Geo& g);
@@ -268,11 +269,24 @@ int make_geo(const avl_config* c, Geo* g)
         if (c->precision == AVL_FP32 &&
             (int64_t)jr * (c->nv[1] + 1) * (c->nv[2] + 1) * c->nx >= (int64_t)INT32_MAX)
             return AVL_ESIZE;
-        // one wave task per 63-column strip and target (vy, vz) plane; the rho
-        // partials are per plane
-        g->nstrip = (c->nx + kReconCols - 1) / kReconCols;
-        g->rc = 1;
-        g->nchunk = c->nv[1] * c->nv[2];
+        // one wave task per 63-column strip (one strip for grids of up to 64
+        // columns), 2x2 block of target (vy, vz) planes and chunk of vx rows;
+        // one rho partial per plane and chunk.  A chunk's first dual row is
+        // walked by the chunk before it too.  A grid with fewer blocks than
+        // the GPU holds waves is cut until it has one task a wave (64 x 24^3
+        // FP64: 736 us whole, 112 us in chunks of two rows); a larger one into
+        // five tasks a wave, in chunks of 16 rows or more, so that the last
+        // round of waves is a small part (256 x 64^3 FP32: 6.00 ms whole,
+        // 5.93, 5.48 and 5.52 ms in 2, 3 and 4 chunks)
+        g->nstrip = c->nx <= kWave ? 1 : (c->nx + kReconCols - 1) / kReconCols;
+        const int64_t blocks = (int64_t)g->nstrip * ((c->nv[1] + 1) / 2) * ((c->nv[2] + 1) / 2);
+        const int64_t slots = (int64_t)recon3_waves_per_cu(c->precision == AVL_FP32 ? 1 : 0) * device_cus();
+        const int64_t one = std::min<int64_t>((c->nv[0] + 1) / 2, slots / blocks);
+        const int64_t five = std::min<int64_t>(c->nv[0] / 16, (5 * slots + blocks - 1) / blocks);
+        g->vchunk = (int)std::max<int64_t>(1, std::max(one, five));
+        g->rc = (c->nv[0] + g->vchunk - 1) / g->vchunk;
+        g->vchunk = (c->nv[0] + g->rc - 1) / g->rc;
+        g->nchunk = c->nv[1] * c->nv[2] * g->vchunk;
         g->cap = 0;
     }
     return AVL_OK;

@@ -51,7 +51,8 @@ struct Geo {
     int nb;              // in-range buckets nrow*nx; bucket nb collects the rest
     int n;               // markers
     int np;              // stride between velocity components in marker storage (n padded to 64)
-    int rc;              // target velocity rows per reconstruct chunk (1D-1V)
+    int rc;              // target velocity (1D-3V: x-velocity) rows per reconstruct chunk
+    int vchunk;          // 1D-3V: chunks of x-velocity rows
     int nchunk, nstrip;  // reconstruct chunks along v and column strips along x
     int hist_bins;       // LDS histogram bins per sort block
     int follow;          // 1D-1V: the loaded state's kicks reach a velocity cell

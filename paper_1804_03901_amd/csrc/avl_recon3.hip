@@ -8,9 +8,10 @@
 // from four dual planes (jy-cy, jz-cz), cy, cz in {0, 1}, each contributing a
 // 1D-1V-like (x, vx) reconstruction with per-marker weight w.
 //
-// One wave owns a strip of 63 target x columns, all vx rows, and a 2x2 block
-// of target (vy, vz) planes; the block draws on a 3x3 block of dual planes.
-// For every dual vx row the wave walks the nine dual-plane row segments; each
+// One wave owns a strip of 63 target x columns (a grid of up to 64 columns is
+// one strip, whose last lane is the first one's left neighbour), a chunk of vx
+// rows, and a 2x2 block of target (vy, vz) planes; the block draws on a 3x3
+// block of dual planes.  For every dual vx row the wave walks the nine dual-plane row segments; each
 // is loaded from memory once into registers (the next segment's loads go out
 // once the last staging of the current one has read them) and serves every
 // target plane of the block it reaches (one, two or four): per (segment,
@@ -26,6 +27,15 @@
 // instead of four times with one target plane per wave; tasks are dealt so
 // that each XCD takes consecutive blocks (vy fastest), which keeps most of
 // these re-reads in its L2 or in the memory-side cache.
+//
+// What bounds it: FP64 issue in lanes that wait for the longest of their 64
+// runs (4 markers a cell: about 10), at two to three waves a SIMD.  So what
+// counts is that every SIMD has its waves to the end: the chunks of vx rows
+// (make_geo) took 64 x 24^3 FP64, ppc 4, 144 waves as one chunk, from 736 to
+// 112 us, and 256 x 64^3 FP32, ppc 4, from 6.00 to 5.48 ms.  Staging each
+// segment once for all its targets (raw, weights formed per run) cut the LDS
+// traffic to a third but moved the conversions and weights into the runs'
+// lanes: 6.9 to 7.7 ms; separate LDS arrays for w and f w 5.6 to 5.9 ms.
 #include "avl_device.h"
 
 namespace avl {
@@ -134,30 +144,47 @@ void k_recon_3v(Geo g, typename R3<PREC>::M m, const int* __restrict__ offsets, 
     __shared__ St3 st[SLOTS];
     const int lane = threadIdx.x;
     const int nby = (g.nv[1] + 1) >> 1, nbz = (g.nv[2] + 1) >> 1;
-    const int ntask = g.nstrip * nby * nbz;
+    const int ntask = g.nstrip * g.vchunk * nby * nbz;
     const int task = (blockIdx.x & 7) * tasks_per_xcd + (blockIdx.x >> 3);
     if ((blockIdx.x >> 3) >= tasks_per_xcd || task >= ntask) return;
-    // task = (strip * nbz + bz) * nby + by: consecutive tasks are neighbouring blocks
+    // task = ((strip * vchunk + chunk) * nbz + bz) * nby + by: consecutive tasks
+    // are neighbouring blocks
     const int by = task % nby;
     const int bz = (task / nby) % nbz;
-    const int strip = task / (nby * nbz);
+    const int chunk = (task / (nby * nbz)) % g.vchunk;
+    const int strip = task / (nby * nbz * g.vchunk);
     // target planes (jy0 + ty, jz0 + tz), ty < nyt, tz < nzt; dual planes
     // (jy0 - 1 + iy, jz0 - 1 + iz), iy < ndy = nyt + 1, iz < ndz = nzt + 1
     const int jy0 = 2 * by, jz0 = 2 * bz;
     const int nyt = min(2, g.nv[1] - jy0), nzt = min(2, g.nv[2] - jz0);
     const int ndy = nyt + 1, ndz = nzt + 1;
     const int nx = g.nx, nvx = g.nv[0];
-    const int col = strip * kReconCols - 1 + lane;
+    // target vx rows [j_lo, j_hi) of the chunk, from dual rows r = jd + 1 = j_lo .. j_hi
+    const int j_lo = chunk * g.rc, j_hi = min(j_lo + g.rc, nvx);
+    // a grid of up to 64 columns is one strip without a halo: lane l owns run
+    // and target column l
+    const bool ring = nx <= kWave;
+    const int col = ring ? lane : strip * kReconCols - 1 + lane;
     const bool run_ok = col < nx;
     const int colw = col < 0 ? nx - 1 : col;
-    const bool tgt_ok = lane >= 1 && col < nx;
-    const bool wrapped = (strip == 0);
+    const bool tgt_ok = (ring || lane >= 1) && col < nx;
+    const bool wrapped = !ring && strip == 0;
     const int first_lane = wrapped ? 1 : 0;
-    const int last_col = min(strip * kReconCols + kReconCols - 1, nx - 1);
-    const int last_lane = last_col - (strip * kReconCols - 1);
+    const int last_col = ring ? nx - 1 : min(strip * kReconCols + kReconCols - 1, nx - 1);
+    const int last_lane = ring ? nx - 1 : last_col - (strip * kReconCols - 1);
     const int rowsy = g.nv[1] + 1, rowsx = nvx + 1;
+    auto left = [&](double v) {
+        double l = from_left3(v);
+        if (ring) {
+            const long long b = __double_as_longlong(v);
+            const double e = __hiloint2double(__builtin_amdgcn_readlane((int)(b >> 32), nx - 1),
+                                              __builtin_amdgcn_readlane((int)b, nx - 1));
+            if (lane == 0) l = e;
+        }
+        return l;
+    };
 
-    // Segments are visited row by row (dual vx row r = jd + 1 in [0, nvx]),
+    // Segments are visited row by row (dual vx row r = jd + 1 in [j_lo, j_hi]),
     // and within a row plane by plane (iy fastest).  A cursor names a
     // segment; run bounds are fetched two segments ahead, markers one.
     struct Cur {
@@ -175,7 +202,7 @@ void k_recon_3v(Geo g, typename R3<PREC>::M m, const int* __restrict__ offsets, 
     auto seg_bounds = [&](const Cur& c, int& beg, int& end) {
         beg = 0;
         end = 0;
-        if (c.r <= nvx && run_ok) {
+        if (c.r <= j_hi && run_ok) {
             const int row = ((jz0 + c.iz) * rowsy + (jy0 + c.iy)) * rowsx + c.r;
             const int bk = row * nx + colw;
             beg = offsets[bk];
@@ -205,7 +232,7 @@ void k_recon_3v(Geo g, typename R3<PREC>::M m, const int* __restrict__ offsets, 
         if (lane < s.wlen) wreg.load(m, g, s.wbeg + lane);
     };
 
-    Cur cur{0, 0, 0}, ahead{0, 0, 0};
+    Cur cur{j_lo, 0, 0}, ahead{j_lo, 0, 0};
     int beg, end, nbeg, nend;
     seg_bounds(ahead, beg, end);
     Seg3 seg = make(beg, end);
@@ -219,10 +246,10 @@ void k_recon_3v(Geo g, typename R3<PREC>::M m, const int* __restrict__ offsets, 
     double uN[4] = {0.0, 0.0, 0.0, 0.0}, uD[4] = {0.0, 0.0, 0.0, 0.0};
     double rp[4] = {0.0, 0.0, 0.0, 0.0};
 
-    while (cur.r <= nvx) {
+    while (cur.r <= j_hi) {
         // issue priority from progress (the FP32 form; the FP64 form's three
         // waves a compute unit ran slower with it)
-        if constexpr (PREC == 1) prio_by_progress(cur.r, nvx + 1);
+        if constexpr (PREC == 1) prio_by_progress(cur.r - j_lo, j_hi - j_lo + 1);
         const int iy = cur.iy, iz = cur.iz;
         const bool staged = fits(seg);
         const int p0 = staged ? ((wrapped && lane == 0) ? seg.nmain : beg - seg.lo) : beg;
@@ -327,10 +354,10 @@ void k_recon_3v(Geo g, typename R3<PREC>::M m, const int* __restrict__ offsets, 
             Sf -= Cf; Saf -= Cf; Sbf -= Cf; Sabf -= Cf;
             const double n11 = Sabf, n10 = Saf - Sabf, n01 = Sbf - Sabf, n00 = (Sf - Saf) - n01;
             const double d11 = Sabw, d10 = Saw - Sabw, d01 = Sbw - Sabw, d00 = (Sw - Saw) - d01;
-            cN[t] += n00 + from_left3(n10);
-            cD[t] += d00 + from_left3(d10);
-            uN[t] += n01 + from_left3(n11);
-            uD[t] += d01 + from_left3(d11);
+            cN[t] += n00 + left(n10);
+            cD[t] += d00 + left(d10);
+            uN[t] += n01 + left(n11);
+            uD[t] += d01 + left(d11);
         }
 
         if (iy == ndy - 1 && iz == ndz - 1) {
@@ -339,7 +366,7 @@ void k_recon_3v(Geo g, typename R3<PREC>::M m, const int* __restrict__ offsets, 
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
                 const int ty = t & 1, tz = t >> 1;
-                if (ty < nyt && tz < nzt && jd >= 0 && tgt_ok) {
+                if (ty < nyt && tz < nzt && jd >= j_lo && tgt_ok) {
                     const double fv = cD[t] > 0.0 ? cN[t] / cD[t] : 0.0;
                     const size_t gi = (((size_t)(jz0 + tz) * g.nv[1] + (jy0 + ty)) * nvx + jd) * nx + col;
                     fgrid[gi] = (T)fv;
@@ -365,17 +392,31 @@ void k_recon_3v(Geo g, typename R3<PREC>::M m, const int* __restrict__ offsets, 
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             const int ty = t & 1, tz = t >> 1;
-            if (ty < nyt && tz < nzt) rho_part[((size_t)(jz0 + tz) * g.nv[1] + (jy0 + ty)) * nx + col] = rp[t];
+            if (ty < nyt && tz < nzt) 
+                rho_part[(((size_t)chunk * g.nv[2] + (jz0 + tz)) * g.nv[1] + (jy0 + ty)) * nx + col] = rp[t];
         }
     }
 }
 
 size_t recon3_scratch_bytes(const Geo&) { return 0; }
 
+// Reconstruction waves resident per compute unit, from the occupancy query
+// (without a device, the register budget's).
+int recon3_waves_per_cu(int prec)
+{
+    const void* fn = prec ? (const void*)k_recon_3v<1> : (const void*)k_recon_3v<0>;
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kWave, 0) != hipSuccess || per_cu <= 0) {
+        (void)hipGetLastError();
+        per_cu = 4 * (prec ? R3<1>::WAVES : R3<0>::WAVES);
+    }
+    return per_cu;
+}
+
 hipError_t launch_recon3(const Geo& g, void* m, const int* offsets, void* fgrid, void* Dgrid, double* rho_part,
                          void*, hipStream_t st)
 {
-    const int tasks = g.nstrip * ((g.nv[1] + 1) / 2) * ((g.nv[2] + 1) / 2);
+    const int tasks = g.nstrip * g.vchunk * ((g.nv[1] + 1) / 2) * ((g.nv[2] + 1) / 2);
     const int per_xcd = (tasks + 7) / 8;
     const int blocks = per_xcd * 8;
     if (g.prec == 0)
