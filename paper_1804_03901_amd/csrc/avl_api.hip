@@ -23,7 +23,7 @@ hipError_t launch_push(const Geo& g, void* m, const double* E, const RowShift* r
                        int* flags, hipStream_t st);
 hipError_t launch_recon(const Geo& g, void* m, const int* offsets, void* fgrid, void* Dgrid, double* rho_part,
                         hipStream_t st);
-int recon_capacity(int prec);
+int recon_capacity(const Geo& g);
 hipError_t launch_recon3(const Geo& g, void* m, const int* offsets, void* fgrid, void* Dgrid, double* rho_part,
                          void* scratch, hipStream_t st);
 hipError_t launch_field(const Geo& g, const double* rho_part, const double* rho_in, double* rho_slices, double* rho,
@@ -61,7 +61,7 @@ hipError_t launch_fill_f64(double* p, int n, double value, hipStream_t st);
 hipError_t launch_scale_f64(double* p, int n, double s, hipStream_t st);
 int sort_blocks(const Geo& g, int phase);
 size_t sort_lds(const Geo& g);
-int recon_waves_per_cu(int prec, int lds_per_cu);
+int recon_waves_per_cu(const Geo& g, int lds_per_cu);
 int recon3_waves_per_cu(int prec);
 int scatter_blocks_per_cu(const Geo& g);
 int scatter_step_blocks_per_cu(const Geo& g);
@@ -71,8 +71,9 @@ hipError_t launch_diag(const Geo& g, const void* fgrid, const double* rho, const
                        double* part, double* out, double* j_out, double* drho_out, hipStream_t st);
 hipError_t launch_sort_batch(int prec, const BInst* tab, const int* pre, int ninst, int blocks, size_t smem, int cur,
                              hipStream_t st, int phase);
-bool recon_sparse(const Geo& g);
-hipError_t launch_recon_batch(int prec, int kahan, int sparse, const BInst* tab, const int* pre, int ninst, int tasks, int cur,
+int recon_form(const Geo& g);
+int recon_form_wider(int a, int b);
+hipError_t launch_recon_batch(int form, int kahan, const BInst* tab, const int* pre, int ninst, int tasks, int cur,
                               hipStream_t st);
 hipError_t launch_field_batch(const BInst* tab, const int* pre, int ninst, int rho_blocks, int max_nx, int write_diag,
                               hipStream_t st);
@@ -249,16 +250,16 @@ int make_geo(const avl_config* c, Geo* g)
         // rows per task such that all tasks are resident at once (as many
         // waves as the reconstruction's registers and LDS let a compute unit
         // hold), so there is no partial second round; tune[0] overrides rc
-        g->nstrip = (c->nx + kReconCols - 1) / kReconCols;
+        g->rform = c->tune[1];
+        g->nstrip = c->nx <= kWave ? 1 : (c->nx + kReconCols - 1) / kReconCols;
         const int64_t slots =
-            (int64_t)recon_waves_per_cu(c->precision == AVL_FP32 ? 1 : 0, device_lds_per_cu()) * device_cus();
+            (int64_t)recon_waves_per_cu(*g, device_lds_per_cu()) * device_cus();
         int rc = 2;
         while (rc < 32 && (int64_t)g->nstrip * ((c->nv[0] + rc - 1) / rc) > slots) ++rc;
         if (c->tune[0]) rc = c->tune[0];
         g->rc = rc;
-        g->rform = c->tune[1];
         g->nchunk = (c->nv[0] + rc - 1) / rc;
-        g->cap = recon_capacity(c->precision);
+        g->cap = recon_capacity(*g);
     } else {
         // 1D-3V FP32 encoding of the x-velocity dual index: jrange is a power
         // of two (the kernels decode it with a mask and a shift)
@@ -335,7 +336,7 @@ void make_layout(const avl_config* c, const Geo& g, Layout* L)
 void fit_lds(Geo* g, int lds)
 {
     const int esz = 8;                    // staged field: double, or the FP32 form's (kick, difference) pair
-    if (g->vdim == 1) g->cap = recon_capacity(g->prec);
+    if (g->vdim == 1) g->cap = recon_capacity(*g);
     const int fixed = esz * g->nx + (g->prec ? (int)sizeof(RowShift) * (g->nv[0] + 1) : 0) + 64;
     int bins = (lds - fixed) / 4;
     bins = (bins >> g->lognx) << g->lognx;
@@ -771,7 +772,7 @@ int avl_init(const avl_config* cfg, void* workspace, size_t ws_bytes, void* stre
                          "[avl] lds limit %d B, recon cap %d, hist bins %d, rc %d, chunks %d, strips %d, "
                          "recon waves per CU %d\n",
                          lds, h->g.cap, h->g.prec ? h->g.wbins : h->g.hist_bins, h->g.rc, h->g.nchunk, h->g.nstrip,
-                         h->g.vdim == 1 ? recon_waves_per_cu(h->g.prec, device_lds_per_cu()) : 0);
+                         h->g.vdim == 1 ? recon_waves_per_cu(h->g, device_lds_per_cu()) : 0);
     }
     if (hipMemsetAsync(h->flags, 0, sizeof(int), h->st) != hipSuccess || (rc = upload_tables(h)) != AVL_OK) {
         delete h;
@@ -1168,12 +1169,12 @@ int batch_launch(avl_batch* b, int cur, hipStream_t st)
     AVL_TRY(launch_sort_batch(b->prec, b->tab, b->pre, b->n, b->tot[BPRE_COUNT], b->lds, cur, st, 0));
     AVL_TRY(launch_sort_batch(b->prec, b->tab, b->pre, b->n, b->tot[BPRE_SCAN], b->lds, cur, st, 1));
     AVL_TRY(launch_sort_batch(b->prec, b->tab, b->pre, b->n, b->tot[BPRE_SCATTER], b->lds, cur, st, 2));
-    // the sparse-row kernels when every instance with markers has sparse rows
-    bool sparse = true;
+    // the reconstruction kernel of the widest rows
+    int form = -1;
     for (avl_handle* hi : b->h)
-        if (hi->g.n > 0 && !recon_sparse(hi->g)) sparse = false;
-    AVL_TRY(launch_recon_batch(b->prec, b->kahan, sparse ? 1 : 0, b->tab, b->pre, b->n, b->tot[BPRE_RECON], 1 - cur,
-                               st));
+        if (hi->g.n > 0) form = form < 0 ? recon_form(hi->g) : recon_form_wider(form, recon_form(hi->g));
+    if (form < 0) form = recon_form(b->h[0]->g);
+    AVL_TRY(launch_recon_batch(form, b->kahan, b->tab, b->pre, b->n, b->tot[BPRE_RECON], 1 - cur, st));
     AVL_TRY(launch_field_batch(b->tab, b->pre, b->n, b->tot[BPRE_RHO], b->max_nx, 1, st));
     return AVL_OK;
 }

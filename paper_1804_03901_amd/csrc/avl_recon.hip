@@ -28,6 +28,8 @@
 // rho: each lane also sums f over the rows of its chunk for its column and
 // writes one partial per (chunk, column); the field kernel adds the chunk
 // partials in chunk order, in FP64.
+#include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "avl_device.h"
@@ -74,17 +76,6 @@ struct FixMoments {
         bf = fma(b_, f_, bf);
         ab = fma(a_, b_, ab);
         abf = fma(ab_, f_, abf);
-    }
-    // default rounding: each term is rounded down onto its grid explicitly
-    __device__ void add_floor(const FixGrid& gf, const FixGrid& gd, double a_, double b_, double f_) {
-        const double ab_ = a_ * b_;
-        f += fixsum_floor(gf, f_);
-        a += fixsum_floor(gd, a_);
-        b += fixsum_floor(gd, b_);
-        af += fixsum_floor(gf, a_ * f_);
-        bf += fixsum_floor(gf, b_ * f_);
-        ab += fixsum_floor(gd, ab_);
-        abf += fixsum_floor(gf, ab_ * f_);
     }
     __device__ void pin() {
         fixsum_pin(f); fixsum_pin(af); fixsum_pin(bf); fixsum_pin(abf);
@@ -144,6 +135,13 @@ __device__ __forceinline__ double from_left(double v)
     return __hiloint2double(hi, lo);
 }
 
+// One lane's value, for every lane.
+__device__ __forceinline__ double from_lane(double v, int lane)
+{
+    const long long b = __double_as_longlong(v);
+    return __hiloint2double(__builtin_amdgcn_readlane((int)(b >> 32), lane), __builtin_amdgcn_readlane((int)b, lane));
+}
+
 // Largest and smallest of a value over the wavefront: DPP steps within quads,
 // half rows and rows of 16 lanes, then row broadcasts, leave the result in
 // lane 63.  Lanes a step does not write take the identity (0 for the maximum,
@@ -180,22 +178,18 @@ template <int PREC> struct RT;
 template <> struct RT<0> {
     using T = double;
     using M = M64;
-    // register prefetch depth per lane (markers); 18 keeps the staging buffer
-    // at 29 KB, so five waves fit in a compute unit's LDS
-    static constexpr int KU = 18;
 };
 template <> struct RT<1> {
     using T = float;
     using M = M32;
-    static constexpr int KU = 20;
 };
 
-// LDS capacity per wave: KU markers per lane of the main range plus one
-// wrapped run of at most a wavefront.
-template <int PREC> constexpr int recon_cap() { return kWave * (RT<PREC>::KU + 1); }
-
-// bytes of LDS per wave: a, b, f as three arrays of the storage type
-template <int PREC> constexpr size_t recon_lds() { return 3 * sizeof(typename RT<PREC>::T) * recon_cap<PREC>(); }
+// The kernels come in several capacities KU: markers a lane holds in registers
+// and stages at once (the choice: recon_form()).  LDS per wave: KU markers per
+// lane of the main range plus one wrapped run of at most a wavefront, as a, b,
+// f in the storage type.
+template <int KU> constexpr int recon_cap() { return kWave * (KU + 1); }
+template <int PREC, int KU> constexpr size_t recon_lds() { return 3 * sizeof(typename RT<PREC>::T) * recon_cap<KU>(); }
 
 // Descriptors cover exactly one range of markers [first, first+count): lanes
 // past the end read zero and cost no memory traffic.
@@ -276,13 +270,13 @@ template <> struct Src<1> {           // a, b (first component), f
 // Staged row segment in LDS.  FP32 form: a, b, f as three float arrays
 // (12 bytes a marker, so more waves fit per CU).  FP64: (a, b) pairs and f,
 // read with one 16-byte and one 8-byte access.
-template <int PREC> struct Lds;
-template <> struct Lds<1> {
+template <int PREC, int KU> struct Lds;
+template <int KU> struct Lds<1, KU> {
     float *a, *b, *f;
     __device__ void init(unsigned char* base) {
         a = reinterpret_cast<float*>(base);
-        b = a + recon_cap<1>();
-        f = b + recon_cap<1>();
+        b = a + recon_cap<KU>();
+        f = b + recon_cap<KU>();
     }
     __device__ void put(const Geo&, int p, const Src<1>::Raw& r) {
         a[p] = r.a;
@@ -301,12 +295,12 @@ template <> struct Lds<1> {
         ff = f[p];
     }
 };
-template <> struct Lds<0> {
+template <int KU> struct Lds<0, KU> {
     double2* ab;
     double* f;
     __device__ void init(unsigned char* base) {
         ab = reinterpret_cast<double2*>(base);
-        f = reinterpret_cast<double*>(base + sizeof(double2) * recon_cap<0>());
+        f = reinterpret_cast<double*>(base + sizeof(double2) * recon_cap<KU>());
     }
     __device__ void put(const Geo& g, int p, const Src<0>::Raw& r) {
         int ix, jp[1];
@@ -329,22 +323,10 @@ template <> struct Lds<0> {
 };
 
 template <int PREC>
-__device__ __forceinline__ void load_global(const Geo& g, const typename RT<PREC>::M& m, int q,
-                                            typename RT<PREC>::T& a, typename RT<PREC>::T& b,
-                                            typename RT<PREC>::T& f)
+__device__ __forceinline__ typename Src<PREC>::Raw load_raw(const typename RT<PREC>::M& m, int q)
 {
-    if constexpr (PREC == 0) {
-        int ix, jp[1];
-        double bb[1];
-        double vv[1] = {m.v[q]};
-        locate64<1>(g, m.x[q], vv, ix, jp, a, bb);
-        b = bb[0];
-        f = m.f[q];
-    } else {
-        a = m.a[q];
-        b = m.b[q];
-        f = m.f[q];
-    }
+    if constexpr (PREC == 0) return {m.x[q], m.v[q], m.f[q]};
+    else return {m.a[q], m.b[q], m.f[q]};
 }
 
 // Marker range of one dual-row segment: the contiguous runs of lanes
@@ -377,11 +359,10 @@ __device__ __forceinline__ Seg make_seg(int beg, int end, int first_lane, int la
 // SPARSE (rows well below the register capacity): loads of whole vectors past
 // the segment are not issued at all (a wave-uniform test per vector); their
 // registers keep stale values that are never staged.
-template <int PREC, bool SPARSE = false>
+template <int PREC, int KU, bool SPARSE>
 __device__ __forceinline__ void prefetch(const typename RT<PREC>::M& m, const Seg& s, int lane,
                                          typename Src<PREC>::Vec* r, typename Src<PREC>::Raw& w)
 {
-    constexpr int KU = RT<PREC>::KU;
     constexpr int V = Src<PREC>::V;
     constexpr int esz = sizeof(typename RT<PREC>::T);
     const bool fit = s.fits(kWave * KU);
@@ -404,12 +385,9 @@ __device__ __forceinline__ void prefetch(const typename RT<PREC>::M& m, const Se
     }
 }
 
-// Register prefetch depth: rows of markers in flight per wave while one row
-// is summed.  The FP32 form holds two rows ahead (its rows take 60 registers);
-// the FP64 form one.
-template <int PREC> constexpr int recon_depth() { return PREC ? 2 : 1; }
-
-template <int PREC, bool KAHAN, bool SPARSE, bool PRIO = false>
+// DEPTH: rows of markers in flight per wave (register prefetch) while one row
+// is summed.
+template <int PREC, int KU, int DEPTH, bool KAHAN, bool SPARSE, bool PRIO = false>
 __device__ __forceinline__ void recon_task(const Geo& g, const typename RT<PREC>::M& m,
                                            const int* __restrict__ offsets, typename RT<PREC>::T* __restrict__ fgrid,
                                            typename RT<PREC>::T* __restrict__ Dgrid, double* __restrict__ rho_part,
@@ -419,25 +397,26 @@ __device__ __forceinline__ void recon_task(const Geo& g, const typename RT<PREC>
     using Raw = typename Src<PREC>::Raw;
     using Vec = typename Src<PREC>::Vec;
     constexpr int V = Src<PREC>::V;
-    constexpr int KU = RT<PREC>::KU;
     constexpr int MAIN = kWave * KU;
-    constexpr int DEPTH = recon_depth<PREC>();
     extern __shared__ __align__(16) unsigned char smem[];
     const int lane = threadIdx.x;
-    Lds<PREC> lds;
+    Lds<PREC, KU> lds;
     lds.init(smem);
 
     const int strip = task / g.nchunk;
     const int chunk = task - strip * g.nchunk;
     const int nx = g.nx;
-    const int col = strip * kReconCols - 1 + lane;        // -1 is the wrapped column nx-1
+    // a grid of up to 64 columns is one strip without a halo: lane l owns run
+    // and target column l, and the last lane is lane 0's left neighbour
+    const bool ring = nx <= kWave;
+    const int col = ring ? lane : strip * kReconCols - 1 + lane;   // -1 is the wrapped column nx-1
     const bool run_ok = col < nx;
     const int colw = col < 0 ? nx - 1 : col;
-    const bool tgt_ok = lane >= 1 && col < nx;
-    const bool wrapped = (strip == 0);
+    const bool tgt_ok = (ring || lane >= 1) && col < nx;
+    const bool wrapped = !ring && strip == 0;
     const int first_lane = wrapped ? 1 : 0;
-    const int last_col = min(strip * kReconCols + kReconCols - 1, nx - 1);
-    const int last_lane = last_col - (strip * kReconCols - 1);
+    const int last_col = ring ? nx - 1 : min(strip * kReconCols + kReconCols - 1, nx - 1);
+    const int last_lane = ring ? nx - 1 : last_col - (strip * kReconCols - 1);
     const int j_begin = chunk * g.rc;
     const int j_end = min(j_begin + g.rc, g.nv[0]);
     // the chunk walks dual rows j_begin-1 .. j_end-1, upwards for even chunks
@@ -471,7 +450,7 @@ __device__ __forceinline__ void recon_task(const Geo& g, const typename RT<PREC>
 #pragma unroll
     for (int q = 0; q < DEPTH; ++q) {
         sg[q] = make_seg(rb[q], re[q], first_lane, last_lane, wrapped);
-        prefetch<PREC, SPARSE>(m, sg[q], lane, regs[q], wreg[q]);
+        prefetch<PREC, KU, SPARSE>(m, sg[q], lane, regs[q], wreg[q]);
     }
 
     // carried from the previous row of the walk: the up terms (upward) or
@@ -515,7 +494,7 @@ __device__ __forceinline__ void recon_task(const Geo& g, const typename RT<PREC>
             }
         }
         wave_sync_lds();
-        const int p0 = staged ? ((wrapped && lane == 0) ? seg.nmain : beg - seg.lo) : beg;
+        const int p0 = (wrapped && lane == 0) ? seg.nmain : beg - seg.lo;   // of the lane's run in the segment
         const int len = end - beg;
         // fetch the run bounds of row k+DEPTH+1, then refill the buffer just
         // staged with row k+DEPTH (an empty range past the last row).  The
@@ -523,11 +502,24 @@ __device__ __forceinline__ void recon_task(const Geo& g, const typename RT<PREC>
         // for it later must not also wait for this prefetch.
         row_offsets(k + DEPTH + 1, rb[DEPTH + 1], re[DEPTH + 1]);
         sg[DEPTH] = make_seg(rb[DEPTH], re[DEPTH], first_lane, last_lane, wrapped);
-        prefetch<PREC, SPARSE>(m, sg[DEPTH], lane, R, W);
+        prefetch<PREC, KU, SPARSE>(m, sg[DEPTH], lane, R, W);
 
-        // Separate loops for staged and global rows: a single loop with a
-        // per-iteration choice makes the compiler fall back to generic (flat)
-        // loads, whose waits would also stall on the prefetch of the next rows.
+        // A segment beyond the capacity is staged piece by piece, straight from
+        // memory (256 x 256 at 40 markers a cell, every row beyond it: FP64 115 us
+        // with a lane's loop over its run in memory, 82 us in pieces; FP32 86, 76):
+        // piece(base) fills LDS with its positions [base, base + MAIN)
+        // (the wrapped run follows the main range), lo to hi of them the lane's.
+        const int tot = seg.nmain + seg.wlen;
+        auto source = [&](int p) { return p < seg.nmain ? seg.lo + p : seg.wbeg + (p - seg.nmain); };
+        auto piece = [&](int base, int& lo, int& hi) {
+            wave_sync_lds();
+#pragma unroll 4
+            for (int q = lane; q < MAIN; q += kWave)
+                if (base + q < tot) lds.put(g, q, load_raw<PREC>(m, source(base + q)));
+            wave_sync_lds();
+            lo = max(p0 - base, 0);
+            hi = min(p0 + len - base, MAIN);
+        };
         Corners c;
         if constexpr (KAHAN) {
             CornerKahan32 K;
@@ -539,10 +531,14 @@ __device__ __forceinline__ void recon_task(const Geo& g, const typename RT<PREC>
                     K.add(a, b, f);
                 }
             } else {
-                for (int u = 0; u < len; ++u) {
-                    T a, b, f;
-                    load_global<PREC>(g, m, p0 + u, a, b, f);
-                    K.add(a, b, f);
+                for (int base = 0; base < tot; base += MAIN) {
+                    int lo, hi;
+                    piece(base, lo, hi);
+                    for (int u = lo; u < hi; ++u) {
+                        T a, b, f;
+                        lds.get(u, a, b, f);
+                        K.add(a, b, f);
+                    }
                 }
             }
             c.from(K);
@@ -553,24 +549,33 @@ __device__ __forceinline__ void recon_task(const Geo& g, const typename RT<PREC>
             // marker the f grid is then c times the offset grid, every N sum is
             // c times its D sum, and f = c comes out exactly
             //
-            // A staged segment whose nonzero |f| all share one binary exponent
+            // A segment whose nonzero |f| all share one binary exponent
             // or two (a factor below 4, as along x in a smooth distribution)
             // takes the segment's largest |f| as every run's bound: each run's
             // own largest |f| is at least the segment's smallest, so its grid is
             // at most twice as coarse as its own bound would give, and the pass
             // over the run is saved.  Otherwise each run takes its own bound.
             unsigned kmax = 0;
-            bool narrow = false;
-            if (staged) {
-                const unsigned gmax = wave_max_u32(smax), gmin = wave_min_u32(smin1) + 1u;
-                narrow = gmax == 0u || fix_exp_of_key(gmax, T()) - fix_exp_of_key(gmin, T()) <= 1;
-                if (narrow) kmax = gmax;
+            if (!staged) {
+#pragma unroll 8
+                for (int p = lane; p < tot; p += kWave) {
+                    const unsigned kf = fix_key(m.f[source(p)]);
+                    smax = max(smax, kf);
+                    smin1 = min(smin1, kf - 1u);
+                }
             }
+            const unsigned gmax = wave_max_u32(smax), gmin = wave_min_u32(smin1) + 1u;
+            const bool narrow = gmax == 0u || fix_exp_of_key(gmax, T()) - fix_exp_of_key(gmin, T()) <= 1;
+            if (narrow) kmax = gmax;
             if (!narrow) {
                 if (staged) {
                     for (int u = 0; u < len; ++u) kmax = max(kmax, fix_key(lds.f[p0 + u]));
                 } else {
-                    for (int u = 0; u < len; ++u) kmax = max(kmax, fix_key(m.f[p0 + u]));
+                    for (int base = 0; base < tot; base += MAIN) {
+                        int lo, hi;
+                        piece(base, lo, hi);
+                        for (int u = lo; u < hi; ++u) kmax = max(kmax, fix_key(lds.f[u]));
+                    }
                 }
             }
             const int emax = len > 0 ? fix_exp_of_key(kmax, T()) : -1100;
@@ -589,11 +594,19 @@ __device__ __forceinline__ void recon_task(const Geo& g, const typename RT<PREC>
                 fixsum_round_nearest();
                 M.pin();
             } else {
-                // the FP64 form locates each marker here, in the default rounding
-                for (int u = 0; u < len; ++u) {
-                    T a, b, f;
-                    load_global<PREC>(g, m, p0 + u, a, b, f);
-                    M.add_floor(gf, gd, (double)a, (double)b, (double)f);
+                for (int base = 0; base < tot; base += MAIN) {
+                    int lo, hi;
+                    piece(base, lo, hi);
+                    fixsum_round_down();
+                    M.pin();
+                    for (int u = lo; u < hi; ++u) {
+                        T a, b, f;
+                        lds.get(u, a, b, f);
+                        M.add_rd((double)a, (double)b, (double)f);
+                    }
+                    M.pin();
+                    fixsum_round_nearest();
+                    M.pin();
                 }
             }
             c.from(M, len);
@@ -601,10 +614,20 @@ __device__ __forceinline__ void recon_task(const Geo& g, const typename RT<PREC>
         wave_sync_lds();
 
         // corner partials of the left neighbour run (lane - 1)
-        const double n10l = from_left(c.n10);
-        const double d10l = from_left(c.d10);
-        const double n11l = from_left(c.n11);
-        const double d11l = from_left(c.d11);
+        double n10l = from_left(c.n10);
+        double d10l = from_left(c.d10);
+        double n11l = from_left(c.n11);
+        double d11l = from_left(c.d11);
+        if (ring) {
+            const double e0 = from_lane(c.n10, nx - 1), e1 = from_lane(c.d10, nx - 1);
+            const double e2 = from_lane(c.n11, nx - 1), e3 = from_lane(c.d11, nx - 1);
+            if (lane == 0) {
+                n10l = e0;
+                d10l = e1;
+                n11l = e2;
+                d11l = e3;
+            }
+        }
 
         // target row j = ((up01 + up11 of dual row j-1) + down00) + down10 of
         // dual row j, in this order in both walk directions
@@ -654,15 +677,14 @@ __device__ __forceinline__ int dealt_task(int tasks_per_xcd, int ntask)
     return ((blockIdx.x >> 3) >= tasks_per_xcd || task >= ntask) ? -1 : task;
 }
 
-template <int PREC, bool KAHAN, bool SPARSE>
-__global__ __launch_bounds__(kWave) void k_recon_1v(Geo g, typename RT<PREC>::M m, const int* __restrict__ offsets,
-                                                    typename RT<PREC>::T* __restrict__ fgrid,
-                                                    typename RT<PREC>::T* __restrict__ Dgrid,
-                                                    double* __restrict__ rho_part, int tasks_per_xcd)
+template <int PREC, int KU, int DEPTH, bool KAHAN, bool SPARSE>
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(PREC == 0 && DEPTH == 2 ? 3 : 1)))
+void k_recon_1v(Geo g, typename RT<PREC>::M m, const int* __restrict__ offsets, typename RT<PREC>::T* __restrict__ fgrid,
+                typename RT<PREC>::T* __restrict__ Dgrid, double* __restrict__ rho_part, int tasks_per_xcd)
 {
     const int task = dealt_task(tasks_per_xcd, g.nstrip * g.nchunk);
     if (task < 0) return;
-    recon_task<PREC, KAHAN, SPARSE, true>(g, m, offsets, fgrid, Dgrid, rho_part, task);
+    recon_task<PREC, KU, DEPTH, KAHAN, SPARSE, true>(g, m, offsets, fgrid, Dgrid, rho_part, task);
 }
 
 // Batched reconstruction: the tasks of every instance form one list, dealt
@@ -671,7 +693,7 @@ template <int PREC> __device__ __forceinline__ const typename RT<PREC>::M& rmark
 template <> __device__ __forceinline__ const M64& rmark<0>(const BInst& I, int b) { return I.m64[b]; }
 template <> __device__ __forceinline__ const M32& rmark<1>(const BInst& I, int b) { return I.m32[b]; }
 
-template <int PREC, bool KAHAN, bool SPARSE>
+template <int PREC, int KU, int DEPTH, bool KAHAN, bool SPARSE>
 __global__ __launch_bounds__(kWave) void k_recon_b(const BInst* __restrict__ tab, const int* __restrict__ pre,
                                                    int ninst, int cur, int tasks_per_xcd)
 {
@@ -680,44 +702,79 @@ __global__ __launch_bounds__(kWave) void k_recon_b(const BInst* __restrict__ tab
     if (task < 0) return;
     const int i = find_inst(pr, ninst, task);
     const BInst& I = tab[i];
-    recon_task<PREC, KAHAN, SPARSE>(I.g, rmark<PREC>(I, cur), I.offsets[cur], (typename RT<PREC>::T*)I.fgrid, nullptr,
+    recon_task<PREC, KU, DEPTH, KAHAN, SPARSE>(I.g, rmark<PREC>(I, cur), I.offsets[cur], (typename RT<PREC>::T*)I.fgrid, nullptr,
                             I.rho_part, task - pr[i]);
 }
 
-// Rows of the FP32 form well below the register capacity (on average at most
-// 60% of it, e.g. 8 markers a cell) take the SPARSE kernels: at 8 markers a
-// cell they are 8-10% faster, at 16 about as fast as the dense ones.
-bool recon_sparse(const Geo& g)
+// Which kernel a grid takes, by the markers of an average strip row.  A
+// capacity leaves a smooth placement's rows room: up to 75% of it on average
+// for the small ones, four standard deviations of a random placement's below
+// it for the large.  A segment beyond it is staged in pieces.  Smaller staging
+// buffers and fewer registers mean more waves a compute unit, which is what
+// hides the loads of rows this short (before: 18 a lane in FP64, 20 in FP32 for
+// every grid).  Reconstruction times, us:
+//   FP64, 6 a lane (10 KB of LDS): 512 x 6600, ppc 4: 232 -> 108, and 98 with
+//     two rows in flight at three waves a SIMD; 2048 x 2048, ppc 4: 140 and 122;
+//     1024 x 512, ppc 4: 14 and 19, hence two rows from 2^23 markers up;
+//   FP64, 12 a lane (20 KB): 512 x 2048, ppc 6: 64 -> 39; 1024 x 512, ppc 8:
+//     31 -> 23;
+//   FP64, 24 a lane (38 KB): 512 x 512, ppc 20: 135 -> 33 (with 18 half of the
+//     rows were beyond the capacity);
+//   FP32, 8 a lane: 1024 x 2048, ppc 6: 45 -> 36; 2048 x 1024, ppc 4: 34 -> 28;
+//     512 x 512, ppc 3: 8.8 -> 9.2, hence from 2^21 markers up;
+//   FP32, 28 a lane, one row in flight: 512 x 512, ppc 20: 57 -> 18;
+//   FP32, 20 a lane, in rows of up to 60% of it without the loads past a row's
+//     end (8-10% faster at 8 markers a cell, about even at 16).
+enum { F64_24, F64_18, F64_12, F64_6D, F64_6, F32_28, F32_20, F32_20S, F32_8S };
+int recon_form(const Geo& g)
 {
-    if (g.prec != 1 || g.nb <= 0) return false;
-    if (g.rform) return g.rform == 2;
-    const double per_row = (double)g.n / (double)g.nb * kReconCols;
-    return per_row <= 0.6 * kWave * RT<1>::KU;
+    const double per_row = g.nb > 0 ? (double)g.n / (double)g.nb * std::min(g.nx, kWave) : 1e30;
+    const double full = per_row + 4.0 * std::sqrt(per_row);
+    if (g.prec != 1) return per_row <= 0.75 * kWave * 6 ? (g.n < 1 << 23 ? F64_6 : F64_6D) : per_row <= 0.75 * kWave * 12 ? F64_12 : full <= kWave * 18 ? F64_18 : F64_24;
+    if (full > kWave * 20) return F32_28;
+    if (g.rform == 1) return F32_20;
+    if (per_row <= 0.75 * kWave * 8 && g.n >= 1 << 21) return F32_8S;
+    return g.rform == 2 || per_row <= 0.6 * kWave * 20 ? F32_20S : F32_20;
 }
 
-hipError_t launch_recon_batch(int prec, int kahan, int sparse, const BInst* tab, const int* pre, int ninst, int tasks,
-                              int cur, hipStream_t st)
+// fn(PREC, KU, DEPTH, SPARSE) of a form, as integral constants
+template <int N> using Int = std::integral_constant<int, N>;
+template <class Fn> auto with_form(int form, Fn fn)
+{
+    using Sparse = std::true_type;
+    using Dense = std::false_type;
+    switch (form) {
+    case F64_24: return fn(Int<0>(), Int<24>(), Int<1>(), Dense());
+    case F64_18: return fn(Int<0>(), Int<18>(), Int<1>(), Dense());
+    case F64_12: return fn(Int<0>(), Int<12>(), Int<1>(), Sparse());
+    case F64_6D: return fn(Int<0>(), Int<6>(), Int<2>(), Sparse());
+    case F64_6: return fn(Int<0>(), Int<6>(), Int<1>(), Sparse());
+    case F32_28: return fn(Int<1>(), Int<28>(), Int<1>(), Dense());
+    case F32_20: return fn(Int<1>(), Int<20>(), Int<2>(), Dense());
+    case F32_20S: return fn(Int<1>(), Int<20>(), Int<2>(), Sparse());
+    default: return fn(Int<1>(), Int<8>(), Int<2>(), Sparse());
+    }
+}
+
+// One form serves every instance of a batch: the one of the widest rows.
+int recon_form_wider(int a, int b) { return std::min(a, b); }
+
+hipError_t launch_recon_batch(int form, int kahan, const BInst* tab, const int* pre, int ninst, int tasks, int cur,
+                              hipStream_t st)
 {
     if (tasks <= 0) return hipSuccess;
     const int per_xcd = (tasks + 7) / 8;
-    const int blocks = per_xcd * 8;
-    const size_t smem = prec ? recon_lds<1>() : recon_lds<0>();
-    static int granted[5] = {0, 0, 0, 0, 0};
-    const int var = prec == 0 ? 0 : 1 + (kahan ? 1 : 0) + (sparse ? 2 : 0);
-    const void* fns[5] = {(const void*)k_recon_b<0, false, false>, (const void*)k_recon_b<1, false, false>,
-                          (const void*)k_recon_b<1, true, false>, (const void*)k_recon_b<1, false, true>,
-                          (const void*)k_recon_b<1, true, true>};
-    hipError_t e = ensure_lds(fns[var], smem, granted[var]);
-    if (e != hipSuccess) return e;
-    const dim3 gr(blocks), bl(kWave);
-    switch (var) {
-    case 0: hipLaunchKernelGGL((k_recon_b<0, false, false>), gr, bl, smem, st, tab, pre, ninst, cur, per_xcd); break;
-    case 1: hipLaunchKernelGGL((k_recon_b<1, false, false>), gr, bl, smem, st, tab, pre, ninst, cur, per_xcd); break;
-    case 2: hipLaunchKernelGGL((k_recon_b<1, true, false>), gr, bl, smem, st, tab, pre, ninst, cur, per_xcd); break;
-    case 3: hipLaunchKernelGGL((k_recon_b<1, false, true>), gr, bl, smem, st, tab, pre, ninst, cur, per_xcd); break;
-    default: hipLaunchKernelGGL((k_recon_b<1, true, true>), gr, bl, smem, st, tab, pre, ninst, cur, per_xcd); break;
-    }
-    return hipGetLastError();
+    return with_form(form, [&](auto prec, auto ku, auto depth, auto sparse) {
+        constexpr int P = decltype(prec)::value, KU = decltype(ku)::value, D = decltype(depth)::value;
+        constexpr bool S = decltype(sparse)::value;
+        auto* fn = P && kahan ? &k_recon_b<P, KU, D, P == 1, S> : &k_recon_b<P, KU, D, false, S>;
+        constexpr size_t smem = recon_lds<P, KU>();
+        static int granted[2] = {0, 0};
+        hipError_t e = ensure_lds((const void*)fn, smem, granted[P && kahan]);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(fn, dim3(per_xcd * 8), dim3(kWave), smem, st, tab, pre, ninst, cur, per_xcd);
+        return hipGetLastError();
+    });
 }
 
 hipError_t launch_recon(const Geo& g, void* m, const int* offsets, void* fgrid, void* Dgrid,
@@ -726,49 +783,43 @@ hipError_t launch_recon(const Geo& g, void* m, const int* offsets, void* fgrid, 
     if (g.vdim != 1) return hipErrorNotSupported;
     const int tasks = g.nstrip * g.nchunk;
     const int per_xcd = (tasks + 7) / 8;
-    const int blocks = per_xcd * 8;
-    const size_t smem = g.prec ? recon_lds<1>() : recon_lds<0>();
-    static int granted[5] = {0, 0, 0, 0, 0};
-    const int var = g.prec == 0 ? 0 : 1 + (g.kahan ? 1 : 0) + (recon_sparse(g) ? 2 : 0);
-    const void* fns[5] = {(const void*)k_recon_1v<0, false, false>, (const void*)k_recon_1v<1, false, false>,
-                          (const void*)k_recon_1v<1, true, false>, (const void*)k_recon_1v<1, false, true>,
-                          (const void*)k_recon_1v<1, true, true>};
-    hipError_t e = ensure_lds(fns[var], smem, granted[var]);
-    if (e != hipSuccess) return e;
-    const dim3 gr(blocks), bl(kWave);
-    if (var == 0) {
-        launch(k_recon_1v<0, false, false>, gr, bl, smem, st, g, *reinterpret_cast<M64*>(m), offsets, (double*)fgrid,
-               (double*)Dgrid, rho_part, per_xcd);
+    return with_form(recon_form(g), [&](auto prec, auto ku, auto depth, auto sparse) {
+        constexpr int P = decltype(prec)::value, KU = decltype(ku)::value, D = decltype(depth)::value;
+        constexpr bool S = decltype(sparse)::value;
+        using T = typename RT<P>::T;
+        using M = typename RT<P>::M;
+        auto* fn = P && g.kahan ? &k_recon_1v<P, KU, D, P == 1, S> : &k_recon_1v<P, KU, D, false, S>;
+        constexpr size_t smem = recon_lds<P, KU>();
+        static int granted[2] = {0, 0};
+        hipError_t e = ensure_lds((const void*)fn, smem, granted[P && g.kahan]);
+        if (e != hipSuccess) return e;
+        launch(fn, dim3(per_xcd * 8), dim3(kWave), smem, st, g, *reinterpret_cast<M*>(m), offsets, (T*)fgrid, (T*)Dgrid,
+               rho_part, per_xcd);
         return hipGetLastError();
-    }
-    const M32 m32 = *reinterpret_cast<M32*>(m);
-    float* fg = (float*)fgrid;
-    float* Dg = (float*)Dgrid;
-    switch (var) {
-    case 1: launch(k_recon_1v<1, false, false>, gr, bl, smem, st, g, m32, offsets, fg, Dg, rho_part, per_xcd); break;
-    case 2: launch(k_recon_1v<1, true, false>, gr, bl, smem, st, g, m32, offsets, fg, Dg, rho_part, per_xcd); break;
-    case 3: launch(k_recon_1v<1, false, true>, gr, bl, smem, st, g, m32, offsets, fg, Dg, rho_part, per_xcd); break;
-    default: launch(k_recon_1v<1, true, true>, gr, bl, smem, st, g, m32, offsets, fg, Dg, rho_part, per_xcd); break;
-    }
-    return hipGetLastError();
+    });
 }
 
-int recon_capacity(int prec) { return prec ? recon_cap<1>() : recon_cap<0>(); }
-
-// Reconstruction waves resident per compute unit, from the occupancy query:
-// two per SIMD by the register budget, fewer where a compute unit's LDS holds
-// fewer staging buffers (the FP64 form's 29 KB a wave: five).  Without a device,
-// the LDS arithmetic on lds_per_cu bytes.
-int recon_waves_per_cu(int prec, int lds_per_cu)
+int recon_capacity(const Geo& g)
 {
-    const size_t per_wave = prec ? recon_lds<1>() : recon_lds<0>();
-    const void* fn = prec ? (const void*)k_recon_1v<1, false, false> : (const void*)k_recon_1v<0, false, false>;
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kWave, per_wave) != hipSuccess || per_cu <= 0) {
-        (void)hipGetLastError();
-        per_cu = (int)std::max<size_t>(1, std::min<size_t>(8, (size_t)lds_per_cu / per_wave));
-    }
-    return per_cu;
+    return with_form(recon_form(g), [](auto, auto ku, auto, auto) { return recon_cap<decltype(ku)::value>(); });
+}
+
+// Reconstruction waves resident per compute unit, from the occupancy query: by
+// the registers and by the staging buffers in a compute unit's LDS.  Without a
+// device, the LDS arithmetic on lds_per_cu bytes.
+int recon_waves_per_cu(const Geo& g, int lds_per_cu)
+{
+    return with_form(recon_form(g), [&](auto prec, auto ku, auto depth, auto sparse) {
+        constexpr int P = decltype(prec)::value, KU = decltype(ku)::value, D = decltype(depth)::value;
+        constexpr size_t per_wave = recon_lds<P, KU>();
+        const void* fn = (const void*)&k_recon_1v<P, KU, D, false, decltype(sparse)::value>;
+        int per_cu = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kWave, per_wave) != hipSuccess || per_cu <= 0) {
+            (void)hipGetLastError();
+            per_cu = (int)std::max<size_t>(1, std::min<size_t>(KU <= 12 ? 12 : 8, (size_t)lds_per_cu / per_wave));
+        }
+        return per_cu;
+    });
 }
 
 }  // namespace avl
