@@ -1250,6 +1250,18 @@ int avl_batch_init(const avl_config* cfgs, int32_t count, void* workspace, size_
     b->kahan = (cfgs[0].options & AVL_OPT_KAHAN32) ? 1 : 0;
     b->max_nx = 0;
     b->lds = 0;
+    // Reconstruction chunks of a batch: an instance's own rule cuts its rows
+    // until they alone fill the GPU, and every chunk walks one dual row more
+    // than it has; together the instances need no more than two tasks a wave.
+    // (64 instances of 262k to 4.2M markers, FP32, ppc 8: 473 us with their own
+    // chunks of 2 to 5 rows, 312, 325 and 320 us at two, five and eight tasks.)
+    int64_t strip_rows = 0, waves = 0;
+    for (const avl_handle* h : b->h) {
+        strip_rows += (int64_t)h->g.nstrip * h->g.nv[0];
+        const int64_t w = recon_waves_per_cu(h->g, device_lds_per_cu());
+        waves = waves ? std::min(waves, w) : w;
+    }
+    const int batch_rc = (int)std::min<int64_t>(32, strip_rows / (2 * waves * device_cus()));
     for (int i = 0; i < count; ++i) {
         avl_handle* h = b->h[i];
         const Geo& g = h->g;
@@ -1279,8 +1291,10 @@ int avl_batch_init(const avl_config* cfgs, int32_t count, void* workspace, size_
         I.flags = h->flags;
         I.dtk = g.dt;
         I.bk = g.bscale;
-        I.nslice = field_slices(g);
-        const int items[BPRE_KINDS] = {sort_blocks(g, 0), sort_blocks(g, 1), sort_blocks(g, 2), g.nstrip * g.nchunk,
+        I.g.rc = h->cfg.tune[0] ? g.rc : std::max(g.rc, batch_rc);
+        I.g.nchunk = (g.nv[0] + I.g.rc - 1) / I.g.rc;
+        I.nslice = field_slices(I.g);
+        const int items[BPRE_KINDS] = {sort_blocks(g, 0), sort_blocks(g, 1), sort_blocks(g, 2), g.nstrip * I.g.nchunk,
                                        ((g.nx + 63) / 64) * I.nslice};
         for (int k = 0; k < BPRE_KINDS; ++k)
             pre[(size_t)k * (count + 1) + i + 1] = pre[(size_t)k * (count + 1) + i] + (g.n > 0 || k == BPRE_SCAN ||

@@ -4,6 +4,7 @@
 of up to 64 columns as one ring of lanes, and rows beyond the capacity, staged
 in pieces: by a concentrated placement, by many markers a cell, and by a wrapped
 run longer than a wavefront; f spread over many exponents and over few.
+Batches: chunks of rows longer than an instance's own.
 1D-3V: velocity rows cut into chunks of two rows (small grids, with a ragged
 last chunk) and of 16 and more, grids of up to 64 columns as one ring of lanes
 and wider ones in strips with a halo, rows that are staged and rows that are
@@ -73,3 +74,24 @@ def test_1v_capacities_and_pieces(nx, nv, ppc, placement, form):
 
 def test_1v_two_rows_in_flight():
     _check(inputs.bump_on_tail(nx=1024, nv=2050, ppc=4, seed=34), avl.AVL_FP64, steps=1)
+
+
+@pytest.mark.parametrize("precision", [avl.AVL_FP64, avl.AVL_FP32])
+def test_batch_chunks_longer_than_an_instances_own(precision):
+    """Rows enough for a batch to walk them in longer chunks than each instance
+    alone would: rho to the rounding of its chunk sums, f from the same markers."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    ws = [inputs.bump_on_tail(nx=nx, nv=nv, ppc=2, seed=41 + i).replace(name=f"b{i}")
+          for i, (nx, nv) in enumerate([(256, 2000), (256, 1801), (64, 900), (512, 1300), (256, 2400)])]
+    mk = [inputs.markers(w) for w in ws]
+    print(f"[case] batch of {len(ws)} prec={precision}", flush=True)
+    b = avl.Batch(ws, [(x, v.reshape(-1), f) for x, v, f in mk], precision=precision)
+    b.step(1)
+    b.check()
+    for i, w in enumerate(ws):
+        sim = avl.Simulation(w, mk[i][0], mk[i][1].reshape(-1), mk[i][2], precision=precision)
+        sim.step(1)
+        rho_s, rho_b = (t.double().cpu().numpy() for t in (sim.field()[1], b.instance(i).field()[1]))
+        assert nrel(rho_b, rho_s) <= 1e-12, w.name
+        sim.close()
