@@ -23,6 +23,7 @@ int lds_limit() { return g_lds_limit; }
 
 constexpr int kFT = kFieldThreads;            // threads of a field block
 constexpr int kFieldGroups = kFT / 64;         // chunk groups per 64-column block
+constexpr int kFusedNx = 256, kFusedPart = 1 << 14;   // widest grid and most chunk partials of the fused form
 
 __device__ __forceinline__ double2 cmul(double2 a, double2 b)
 {
@@ -148,6 +149,10 @@ __global__ __launch_bounds__(kFT) void k_rho(Geo g, const double* __restrict__ r
 // * (sum of the slices in order) or the caller's rho, then the spectral solve
 // and the diagnostics.  Every global read the block needs is issued up front
 // so that their latencies overlap.
+//
+// FUSED: the grid is small enough for this block to sum the chunk partials
+// itself, in rho_block's groups and order, and part 1 is not launched.
+template <bool FUSED>
 __device__ __forceinline__ void solve_block(const Geo& g, const double* __restrict__ rho_slices, int nslice,
                                             const double* __restrict__ rho_in, double* __restrict__ rho,
                                             double* __restrict__ E_out, const double2* __restrict__ tw,
@@ -166,6 +171,29 @@ __device__ __forceinline__ void solve_block(const Geo& g, const double* __restri
     const long long ctr = (write_diag && tid == 0) ? *step_ctr : 0;
     double rv[Q], gv[Q];
     double2 twv[Q];
+    __shared__ double colsum[FUSED ? kFusedNx * kFieldGroups : 1];
+    if constexpr (FUSED) {
+        const double* __restrict__ rho_part = rho_slices;
+        const int c = tid & 63, grp = tid >> 6;
+        double acc[kFusedNx / 64] = {};
+        for (int ch = grp; ch < g.nchunk; ch += 4 * kFieldGroups) {
+            double v[4][kFusedNx / 64];
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int q = 0; q < kFusedNx / 64; ++q) {
+                    const int i = c + 64 * q, cc = ch + k * kFieldGroups;
+                    v[k][q] = i < nx && cc < g.nchunk ? rho_part[(size_t)cc * nx + i] : 0.0;
+                }
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int q = 0; q < kFusedNx / 64; ++q) acc[q] += v[k][q];
+        }
+#pragma unroll
+        for (int q = 0; q < kFusedNx / 64; ++q) colsum[grp * kFusedNx + c + 64 * q] = acc[q];
+        __syncthreads();
+    }
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
         const int i = tid + q * kFT;
@@ -173,7 +201,9 @@ __device__ __forceinline__ void solve_block(const Geo& g, const double* __restri
         gv[q] = 0.0;
         twv[q] = make_double2(0.0, 0.0);
         if (i < nx) {
-            if (rho_in) {
+            if constexpr (FUSED) {
+                for (int k = 0; k < kFieldGroups; ++k) rv[q] += colsum[k * kFusedNx + (i & (kFusedNx - 1))];
+            } else if (rho_in) {
                 rv[q] = rho_in[i];
             } else {
                 for (int s = 0; s < nslice; ++s) rv[q] += rho_slices[(size_t)s * nx + i];
@@ -267,6 +297,7 @@ __device__ __forceinline__ void solve_block(const Geo& g, const double* __restri
     }
 }
 
+template <bool FUSED>
 __global__ __launch_bounds__(kFT) void k_solve(Geo g, const double* __restrict__ rho_slices, int nslice,
                                                const double* __restrict__ rho_in, double* __restrict__ rho,
                                                double* __restrict__ E_out, const double2* __restrict__ tw,
@@ -274,7 +305,8 @@ __global__ __launch_bounds__(kFT) void k_solve(Geo g, const double* __restrict__
                                                long long* __restrict__ step_ctr, int write_diag,
                                                double* __restrict__ W_out, int* __restrict__ flags)
 {
-    solve_block(g, rho_slices, nslice, rho_in, rho, E_out, tw, green, diag_ring, step_ctr, write_diag, W_out, flags);
+    solve_block<FUSED>(g, rho_slices, nslice, rho_in, rho, E_out, tw, green, diag_ring, step_ctr, write_diag, W_out,
+                       flags);
 }
 
 // Batched charge density and field solve: rho blocks of every instance in one
@@ -290,7 +322,7 @@ __global__ __launch_bounds__(kFT) void k_rho_b(const BInst* __restrict__ tab, co
 __global__ __launch_bounds__(kFT) void k_solve_b(const BInst* __restrict__ tab, int write_diag)
 {
     const BInst& I = tab[blockIdx.x];
-    solve_block(I.g, I.rho_slices, I.nslice, nullptr, I.rho, I.E, I.tw, I.green, I.diag, I.ctr, write_diag, nullptr,
+    solve_block<false>(I.g, I.rho_slices, I.nslice, nullptr, I.rho, I.E, I.tw, I.green, I.diag, I.ctr, write_diag, nullptr,
                 I.flags);
 }
 
@@ -371,14 +403,25 @@ hipError_t launch_field(const Geo& g, const double* rho_part, const double* rho_
                         long long* step_ctr, int write_diag, double* W_out, int* flags, hipStream_t st)
 {
     const size_t smem = (sizeof(double2) + sizeof(double2) / 2) * g.nx;
-    static int granted = 0;
-    hipError_t e = ensure_lds((const void*)k_solve, smem, granted);
-    if (e != hipSuccess) return e;
+    static int granted[2] = {0, 0};
+    hipError_t e;
     const int nslice = field_slices(g);
+    // up to 2^14 chunk partials (128 KB, for one compute unit to read) one launch
+    // does both parts; a step of 64 x 64 FP64 took 36.5 us in two launches and
+    // 35.0 in one, 256 x 128 FP32 40.1 and 39.5, 256 x 256 (2^15) 41.9 and 42.8
+    if (!rho_in && nslice == 1 && g.nx <= kFusedNx && (int64_t)g.nchunk * g.nx <= kFusedPart) {
+        e = ensure_lds((const void*)k_solve<true>, smem, granted[1]);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_solve<true>, dim3(1), dim3(kFT), smem, st, g, rho_part, 1, rho_in, rho, E_out, tw, green,
+                           diag_ring, step_ctr, write_diag, W_out, flags);
+        return hipGetLastError();
+    }
+    e = ensure_lds((const void*)k_solve<false>, smem, granted[0]);
+    if (e != hipSuccess) return e;
     if (!rho_in)
         hipLaunchKernelGGL(k_rho, dim3(((g.nx + 63) / 64) * nslice), dim3(kFT), 0, st, g, rho_part, rho_slices,
                            nslice);
-    hipLaunchKernelGGL(k_solve, dim3(1), dim3(kFT), smem, st, g, rho_slices, nslice, rho_in, rho, E_out, tw, green,
+    hipLaunchKernelGGL(k_solve<false>, dim3(1), dim3(kFT), smem, st, g, rho_slices, nslice, rho_in, rho, E_out, tw, green,
                        diag_ring, step_ctr, write_diag, W_out, flags);
     return hipGetLastError();
 }
