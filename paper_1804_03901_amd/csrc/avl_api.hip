@@ -38,7 +38,7 @@ hipError_t launch_validate(const Geo& g, const double* x, const double* v, const
 hipError_t launch_to32(const Geo& g, const double* x, const double* v, const double* f, M32 m, int* flags,
                        hipStream_t st);
 hipError_t launch_to64(const Geo& g, M32 m, double* x, double* v, double* f, hipStream_t st,
-                       const int* id = nullptr);
+                       const int* id = nullptr, const int* off = nullptr, const int* tfirst = nullptr);
 hipError_t launch_by_id64(int n, const double* x, const double* v, const int* id, double* xo, double* vo,
                           hipStream_t st);
 hipError_t launch_copy(const void* src, void* dst, size_t bytes, hipStream_t st);
@@ -1520,10 +1520,11 @@ int adj_save(avl_handle* h, char* S, const AdjLayout& A)
         const M64& m = h->m64[h->cur];
         AVL_TRY(launch_by_id64(g.n, m.x, m.v, m.id, (double*)(S + A.st_x), (double*)(S + A.st_v), h->st));
     } else {
-        const int rc = ensure_cells(h);
-        if (rc) return rc;
         const M32& m = h->m32[h->cur];
-        if (n) AVL_TRY(launch_to64(g, m, (double*)(S + A.st_x), (double*)(S + A.st_v), nullptr, h->st, m.id));
+        const bool impl = implied_cells(h) && !h->cells_ok;
+        if (n)
+            AVL_TRY(launch_to64(g, m, (double*)(S + A.st_x), (double*)(S + A.st_v), nullptr, h->st, m.id,
+                                impl ? h->offs[h->cur] : nullptr, impl ? h->tfirst[h->cur] : nullptr));
     }
     const size_t esz = g.prec == AVL_FP64 ? 8 : 4;
     AVL_TRY(hipMemcpyAsync(S + A.st_fg, h->fgrid, esz * (size_t)g.nx * g.nv[0], hipMemcpyDeviceToDevice, h->st));

@@ -484,6 +484,21 @@ __device__ __forceinline__ void fixsum_round_nearest() { asm volatile("s_setreg_
 // in the default rounding mode; the multiplication by 2^-e is exact).
 __device__ __forceinline__ double fixsum_floor(const FixGrid& gr, double t) { return floor(t * gr.inv_q) * gr.q; }
 
+// Bucket of position p of a sorted FP32 1D-1V order of n markers: the largest b
+// with off[b] <= p, between the buckets tfirst holds for the neighbouring
+// positions that are multiples of kTfStride (at most nb, the overflow run).
+__device__ __forceinline__ int run_at(const int* __restrict__ off, const int* __restrict__ tfirst, int nb, int n, int p)
+{
+    const int t = p >> kTfLog;
+    int lo = tfirst[t], hi = ((t + 1) << kTfLog) < n ? tfirst[t + 1] : nb;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (off[mid] <= p) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
 // Host side: kernel launches that can carry timing events.  The library's
 // timer may leave a (start, stop) pair here for the next launch made through
 // launch() on this host thread; the pair then records that kernel's own start
