@@ -252,10 +252,14 @@ int make_geo(const avl_config* c, Geo* g)
         // hold), so there is no partial second round; tune[0] overrides rc
         g->rform = c->tune[1];
         g->nstrip = c->nx <= kWave ? 1 : (c->nx + kReconCols - 1) / kReconCols;
-        const int64_t slots =
-            (int64_t)recon_waves_per_cu(*g, device_lds_per_cu()) * device_cus();
+        // In the FP32 form the chunks group rho's partial sums, whose last bit
+        // decides how a kicked marker rounds: they are those of the dense form's
+        // two waves a SIMD and of 63-column strips, whatever kernel runs
+        const bool fp32 = c->precision == AVL_FP32;
+        const int64_t slots = (fp32 ? 8 : (int64_t)recon_waves_per_cu(*g, device_lds_per_cu())) * device_cus();
+        const int64_t strips = fp32 ? (c->nx + kReconCols - 1) / kReconCols : g->nstrip;
         int rc = 2;
-        while (rc < 32 && (int64_t)g->nstrip * ((c->nv[0] + rc - 1) / rc) > slots) ++rc;
+        while (rc < 32 && strips * ((c->nv[0] + rc - 1) / rc) > slots) ++rc;
         if (c->tune[0]) rc = c->tune[0];
         g->rc = rc;
         g->nchunk = (c->nv[0] + rc - 1) / rc;
@@ -1252,16 +1256,17 @@ int avl_batch_init(const avl_config* cfgs, int32_t count, void* workspace, size_
     b->lds = 0;
     // Reconstruction chunks of a batch: an instance's own rule cuts its rows
     // until they alone fill the GPU, and every chunk walks one dual row more
-    // than it has; together the instances need no more than two tasks a wave.
-    // (64 instances of 262k to 4.2M markers, FP32, ppc 8: 473 us with their own
-    // chunks of 2 to 5 rows, 312, 325 and 320 us at two, five and eight tasks.)
+    // than it has; together FP64 instances need no more than two tasks a wave.
+    // FP32 instances keep their own chunks (64 of them, 91M markers, ppc 8: 473
+    // us, 312 at two tasks a wave), for the grouping of rho: its last bit moves
+    // FP32 markers, and E by 1e-8 in five steps.
     int64_t strip_rows = 0, waves = 0;
     for (const avl_handle* h : b->h) {
         strip_rows += (int64_t)h->g.nstrip * h->g.nv[0];
         const int64_t w = recon_waves_per_cu(h->g, device_lds_per_cu());
         waves = waves ? std::min(waves, w) : w;
     }
-    const int batch_rc = (int)std::min<int64_t>(32, strip_rows / (2 * waves * device_cus()));
+    const int batch_rc = b->prec == AVL_FP32 ? 0 : (int)std::min<int64_t>(32, strip_rows / (2 * waves * device_cus()));
     for (int i = 0; i < count; ++i) {
         avl_handle* h = b->h[i];
         const Geo& g = h->g;
