@@ -720,12 +720,12 @@ __global__ __launch_bounds__(kWave) void k_recon_b(const BInst* __restrict__ tab
 //     31 -> 23;
 //   FP64, 24 a lane (38 KB): 512 x 512, ppc 20: 135 -> 33 (with 18 half of the
 //     rows were beyond the capacity);
-//   FP32, 8 a lane: 1024 x 2048, ppc 6: 45 -> 36; 2048 x 1024, ppc 4: 34 -> 28;
-//     512 x 512, ppc 3: 8.8 -> 9.2, hence from 2^21 markers up;
+//   FP32, 8 or 12 a lane: no gain in chunks of the same length (1024 x 2048,
+//     ppc 6: 44 against 46; 2048 x 1024, ppc 4: 33 against 37), so there is none;
 //   FP32, 28 a lane, one row in flight: 512 x 512, ppc 20: 57 -> 18;
 //   FP32, 20 a lane, in rows of up to 60% of it without the loads past a row's
 //     end (8-10% faster at 8 markers a cell, about even at 16).
-enum { F64_24, F64_18, F64_12, F64_6D, F64_6, F32_28, F32_20, F32_20S, F32_8S };
+enum { F64_24, F64_18, F64_12, F64_6D, F64_6, F32_28, F32_20, F32_20S };
 int recon_form(const Geo& g)
 {
     const double per_row = g.nb > 0 ? (double)g.n / (double)g.nb * std::min(g.nx, kWave) : 1e30;
@@ -733,7 +733,6 @@ int recon_form(const Geo& g)
     if (g.prec != 1) return per_row <= 0.75 * kWave * 6 ? (g.n < 1 << 23 ? F64_6 : F64_6D) : per_row <= 0.75 * kWave * 12 ? F64_12 : full <= kWave * 18 ? F64_18 : F64_24;
     if (full > kWave * 20) return F32_28;
     if (g.rform == 1) return F32_20;
-    if (per_row <= 0.75 * kWave * 8 && g.n >= 1 << 21) return F32_8S;
     return g.rform == 2 || per_row <= 0.6 * kWave * 20 ? F32_20S : F32_20;
 }
 
@@ -751,8 +750,7 @@ template <class Fn> auto with_form(int form, Fn fn)
     case F64_6: return fn(Int<0>(), Int<6>(), Int<1>(), Sparse());
     case F32_28: return fn(Int<1>(), Int<28>(), Int<1>(), Dense());
     case F32_20: return fn(Int<1>(), Int<20>(), Int<2>(), Dense());
-    case F32_20S: return fn(Int<1>(), Int<20>(), Int<2>(), Sparse());
-    default: return fn(Int<1>(), Int<8>(), Int<2>(), Sparse());
+    default: return fn(Int<1>(), Int<20>(), Int<2>(), Sparse());
     }
 }
 
