@@ -1951,7 +1951,7 @@ extern "C" int avl_reconstruct_noalloc(const avl_config* cfg, void* stream, cons
     if (((uintptr_t)x | (uintptr_t)v | (uintptr_t)f) & 7) return AVL_EALIGN;
     if (((uintptr_t)f_out | (uintptr_t)D_out) & 7) return AVL_EALIGN;
     // the slice of the handle layout this call needs: two marker buffers,
-    // counts, offsets, per-scan-tile totals, the rho partials and the flags
+    // counts, offsets, per-scan-tile totals and the flags (no rho partials)
     const size_t np = (size_t)g.np;
     const size_t mbytes = (g.prec == AVL_FP64 ? sizeof(double) * np * (2 + g.vdim) : 4 * np * (3 + g.vdim)) +
                           64 * (3 + g.vdim);
@@ -1962,7 +1962,6 @@ extern "C" int avl_reconstruct_noalloc(const avl_config* cfg, void* stream, cons
     const size_t o_m0 = take(mbytes), o_m1 = take(mbytes);
     const size_t o_counts = take(sizeof(int) * nbt), o_offsets = take(sizeof(int) * (nbt + 1));
     const size_t o_tsum = take(sizeof(int) * (ntiles + 64));
-    const size_t o_rho = take(sizeof(double) * (size_t)std::max(1, g.nchunk) * g.nx);
     const size_t o_flags = take(sizeof(int));
     if (off > (size_t)AVL_NOALLOC_SCRATCH_BYTES) return AVL_ESIZE;
     char* base = (char*)scratch_address();
@@ -1994,11 +1993,10 @@ extern "C" int avl_reconstruct_noalloc(const avl_config* cfg, void* stream, cons
     int* counts = (int*)(base + o_counts);
     int* offsets = (int*)(base + o_offsets);
     int* tsum = (int*)(base + o_tsum);
-    double* rho_part = (double*)(base + o_rho);
     int* flags = (int*)(base + o_flags);
     // the array keeps the previous call's contents: clear what the passes
-    // accumulate into (counts, flags) and set
-    // the end offset, all with kernels (no memset or host copy)
+    // accumulate into (counts, flags) and set the end offset, all with kernels
+    // (no memset or host copy)
     AVL_TRY(fill_int(counts, nbt, 0, st));
     AVL_TRY(fill_int(flags, 1, 0, st));
     AVL_TRY(fill_int(offsets + nbt, 1, g.n, st));
@@ -2013,8 +2011,9 @@ extern "C" int avl_reconstruct_noalloc(const avl_config* cfg, void* stream, cons
     void* src = g.prec == AVL_FP64 ? (void*)&m64[0] : (void*)&m32[0];
     void* dst = g.prec == AVL_FP64 ? (void*)&m64[1] : (void*)&m32[1];
     for (int phase = 0; phase < 3; ++phase)
-        AVL_TRY(launch_sort(g, src, dst, nullptr, nullptr, g.dt, g.bscale, counts, offsets, tsum, flags, false, st, phase, nullptr, nullptr, nullptr));
-    if (g.vdim == 1) AVL_TRY(launch_recon(g, dst, offsets, f_out, D_out, rho_part, st));
-    else AVL_TRY(launch_recon3(g, dst, offsets, f_out, D_out, rho_part, nullptr, st));
+        AVL_TRY(launch_sort(g, src, dst, nullptr, nullptr, g.dt, g.bscale, counts, offsets, tsum, flags, false, st,
+                            phase, nullptr, nullptr, nullptr));
+    if (g.vdim == 1) AVL_TRY(launch_recon(g, dst, offsets, f_out, D_out, nullptr, st));
+    else AVL_TRY(launch_recon3(g, dst, offsets, f_out, D_out, nullptr, nullptr, st));
     return AVL_OK;
 }

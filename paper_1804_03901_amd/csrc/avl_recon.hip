@@ -27,7 +27,7 @@
 //
 // rho: each lane also sums f over the rows of its chunk for its column and
 // writes one partial per (chunk, column); the field kernel adds the chunk
-// partials in chunk order, in FP64.
+// partials in chunk order, in FP64.  A caller that needs no rho passes none.
 #include <algorithm>
 #include <cmath>
 #include <type_traits>
@@ -674,7 +674,7 @@ __device__ __forceinline__ void recon_task(const Geo& g, const typename RT<PREC>
         for (int q = 0; q < DEPTH; ++q) row(k + q, regs[q], wreg[q]);
     }
     if constexpr (PRIO) __builtin_amdgcn_s_setprio(0);
-    if (tgt_ok) rho_part[(size_t)chunk * nx + col] = rp;
+    if (tgt_ok && rho_part) rho_part[(size_t)chunk * nx + col] = rp;
 }
 
 // XCD-aware dealing: blocks go round-robin over the 8 XCDs; give each XCD a

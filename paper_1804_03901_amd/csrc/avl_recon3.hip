@@ -388,11 +388,11 @@ void k_recon_3v(Geo g, typename R3<PREC>::M m, const int* __restrict__ offsets, 
         advance(ahead);
     }
     if constexpr (PREC == 1) __builtin_amdgcn_s_setprio(0);
-    if (tgt_ok) {
+    if (tgt_ok && rho_part) {
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             const int ty = t & 1, tz = t >> 1;
-            if (ty < nyt && tz < nzt) 
+            if (ty < nyt && tz < nzt)
                 rho_part[(((size_t)chunk * g.nv[2] + (jz0 + tz)) * g.nv[1] + (jy0 + ty)) * nx + col] = rp[t];
         }
     }
