@@ -202,7 +202,7 @@ int make_geo(const avl_config* c, Geo* g)
     g->nrow = (int)rows;
     g->nb = (int)(rows * c->nx);
     g->n = (int)c->n_markers;
-    g->np = (int)((c->n_markers + 63) / 64 * 64);
+    g->np = (unsigned)((c->n_markers + 63) / 64 * 64);
     g->L = c->L;
     g->inv_L = 1.0 / c->L;
     g->dx = c->L / c->nx;

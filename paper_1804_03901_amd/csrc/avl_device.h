@@ -35,6 +35,43 @@ constexpr int kScanItems = 4;
 constexpr int kScanTile = kScanThreads * kScanItems;
 constexpr int kTfLog = 8;                                 // the scan records the bucket of every 2^kTfLog-th position
 constexpr int kTfStride = 1 << kTfLog;
+
+// Index arithmetic of tiles.  In 1D-3V markers and buckets number up to 2^31 - 3,
+// so a tile's end, a thread's offset past its tile's start and the tiles that
+// round a grid up pass 2^31: the sums are formed in unsigned, which holds them.
+__host__ __device__ inline bool tile_starts(int tile, int size, int n) { return (unsigned)tile * (unsigned)size < (unsigned)n; }
+__host__ __device__ inline int tile_count(int size, int n) { return n / size + (n % size != 0); }
+// last item of the tile that starts at base < n
+__host__ __device__ inline int tile_last(int base, int size, int n) { return base + (n - base < size ? n - base : size) - 1; }
+// item of a tile at `off` from its start (compared with tile_last, unsigned)
+__host__ __device__ inline unsigned tile_item(int base, int off) { return (unsigned)base + (unsigned)off; }
+
+// Thread `thread`'s part of the sum of the items [first, last), first a multiple
+// of 4: four at a time, eight such loads in flight.
+template <class Quad, class One>
+__host__ __device__ __forceinline__ int scan_part(Quad quad, One one, unsigned first, unsigned last, unsigned thread)
+{
+    int s = 0;
+    for (unsigned i = first + 4 * thread; i < last; i += 8 * 4 * kScanThreads) {
+        int4 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const unsigned b = i + u * 4 * kScanThreads;
+            v[u] = make_int4(0, 0, 0, 0);
+            if (b + 4 <= last) {
+                v[u] = quad(b);
+            } else if (b < last) {
+                v[u].x = one(b);
+                if (b + 1 < last) v[u].y = one(b + 1);
+                if (b + 2 < last) v[u].z = one(b + 2);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += (v[u].x + v[u].y) + (v[u].z + v[u].w);
+    }
+    return s;
+}
+
 constexpr int kReconCols = kWave - 1;                     // target columns per reconstruct wave
 constexpr int kDiagCap = 4096;                            // per-step diagnostics ring
 constexpr int kFieldThreads = 1024;                      // threads of a field-solve block
@@ -50,7 +87,7 @@ struct Geo {
     int nrow;            // number of bucket rows: prod(nv[d] + 1)
     int nb;              // in-range buckets nrow*nx; bucket nb collects the rest
     int n;               // markers
-    int np;              // stride between velocity components in marker storage (n padded to 64)
+    unsigned np;         // stride between velocity components in marker storage (n padded to 64)
     int rc;              // target velocity (1D-3V: x-velocity) rows per reconstruct chunk
     int vchunk;          // 1D-3V: chunks of x-velocity rows
     int nchunk, nstrip;  // reconstruct chunks along v and column strips along x

@@ -435,7 +435,8 @@ __global__ void k_validate(Geo g, const double* __restrict__ x, const double* __
                            const double* __restrict__ f, int* __restrict__ bad)
 {
     int local = 0;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < g.n; i += gridDim.x * blockDim.x) {
+    for (unsigned u = blockIdx.x * blockDim.x + threadIdx.x; u < (unsigned)g.n; u += gridDim.x * blockDim.x) {
+        const int i = (int)u;
         const double xi = x[i];
         if (!(xi >= 0.0 && xi < g.L)) local = 1;
         if (!isfinite(f[i])) local = 1;
@@ -449,7 +450,8 @@ __global__ void k_validate(Geo g, const double* __restrict__ x, const double* __
 __global__ void k_to32(Geo g, const double* __restrict__ x, const double* __restrict__ v,
                        const double* __restrict__ f, M32 m, int* __restrict__ flags)
 {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < g.n; i += gridDim.x * blockDim.x) {
+    for (unsigned u = blockIdx.x * blockDim.x + threadIdx.x; u < (unsigned)g.n; u += gridDim.x * blockDim.x) {
+        const int i = (int)u;
         double s = x[i] * g.inv_dx - 0.5;
         double fs = floor(s);
         float a = (float)(s - fs);
@@ -512,7 +514,8 @@ __global__ __launch_bounds__(256) void k_to64(Geo g, M32 m, double* __restrict__
                        const int* __restrict__ id, const int* __restrict__ off, const int* __restrict__ tfirst)
 {
     const int sorted = off ? off[g.nb] : 0;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < g.n; i += gridDim.x * blockDim.x) {
+    for (unsigned u = blockIdx.x * blockDim.x + threadIdx.x; u < (unsigned)g.n; u += gridDim.x * blockDim.x) {
+        const int i = (int)u;
         const int o = id ? id[i] : i;
         const float ma = m.a[i], mb = m.b[i];      // under way before the search for the cell
         const int cell = i < sorted ? run_at(off, tfirst, g.nb, g.n, i) : m.cell[i];
@@ -557,7 +560,7 @@ __global__ __launch_bounds__(256) void k_copy(const float4* __restrict__ src, fl
 hipError_t launch_validate(const Geo& g, const double* x, const double* v, const double* f, int* bad, hipStream_t st)
 {
     if (g.n == 0) return hipSuccess;
-    int blocks = min((g.n + 255) / 256, 4096);
+    int blocks = min(tile_count(256, g.n), 4096);
     hipLaunchKernelGGL(k_validate, dim3(blocks), dim3(256), 0, st, g, x, v, f, bad);
     return hipGetLastError();
 }
@@ -566,7 +569,7 @@ hipError_t launch_to32(const Geo& g, const double* x, const double* v, const dou
                        hipStream_t st)
 {
     if (g.n == 0) return hipSuccess;
-    int blocks = min((g.n + 255) / 256, 8192);
+    int blocks = min(tile_count(256, g.n), 8192);
     hipLaunchKernelGGL(k_to32, dim3(blocks), dim3(256), 0, st, g, x, v, f, m, flags);
     return hipGetLastError();
 }
@@ -575,7 +578,7 @@ hipError_t launch_to64(const Geo& g, M32 m, double* x, double* v, double* f, hip
                        const int* off, const int* tfirst)
 {
     if (g.n == 0) return hipSuccess;
-    int blocks = min((g.n + 255) / 256, 8192);
+    int blocks = min(tile_count(256, g.n), 8192);
     hipLaunchKernelGGL(k_to64, dim3(blocks), dim3(256), 0, st, g, m, x, v, f, id, off, tfirst);
     return hipGetLastError();
 }

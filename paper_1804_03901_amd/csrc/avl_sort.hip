@@ -133,8 +133,8 @@ template <int PREC, int VD, int K> struct Group;
 
 template <int VD, int K> struct Group<0, VD, K> {
     Pay<0, VD> p[K];
-    __device__ void load(const M64& m, const Geo& g, int first, int last, bool with_f, int = VD, int = -1) {
-        if (first + K - 1 <= last) {
+    __device__ void load(const M64& m, const Geo& g, unsigned first, int last, bool with_f, int = VD, int = -1) {
+        if (first + K - 1 <= (unsigned)last) {
             double t[K];
             vload<double, K>(m.x + first, t);
 #pragma unroll
@@ -152,7 +152,7 @@ template <int VD, int K> struct Group<0, VD, K> {
             }
         } else {
 #pragma unroll
-            for (int k = 0; k < K; ++k) p[k].load(m, g, min(first + k, last), with_f);
+            for (int k = 0; k < K; ++k) p[k].load(m, g, (int)min(first + k, (unsigned)last), with_f);
         }
     }
 };
@@ -163,8 +163,8 @@ template <int VD, int K> struct Group<1, VD, K> {
     // needs the cell index, a and the x-velocity offset only).  ovf >= 0:
     // implied cells, read from memory only at positions >= ovf (the
     // overflow run of the previous order); the rest are filled in later.
-    __device__ void load(const M32& m, const Geo& g, int first, int last, bool with_f, int nvel = VD, int ovf = -1) {
-        if (first + K - 1 <= last) {
+    __device__ void load(const M32& m, const Geo& g, unsigned first, int last, bool with_f, int nvel = VD, int ovf = -1) {
+        if (first + K - 1 <= (unsigned)last) {
             int ti[K];
             float t[K];
             if (ovf < 0) {
@@ -174,10 +174,10 @@ template <int VD, int K> struct Group<1, VD, K> {
             } else {
 #pragma unroll
                 for (int k = 0; k < K; ++k) p[k].cell = 0;
-                if (first + K - 1 >= ovf) {
+                if (first + K - 1 >= (unsigned)ovf) {
 #pragma unroll
                     for (int k = 0; k < K; ++k)
-                        if (first + k >= ovf) p[k].cell = m.cell[first + k];
+                        if (first + k >= (unsigned)ovf) p[k].cell = m.cell[first + k];
                 }
             }
             vload<float, K>(m.a + first, t);
@@ -202,7 +202,7 @@ template <int VD, int K> struct Group<1, VD, K> {
         } else {
 #pragma unroll
             for (int k = 0; k < K; ++k) {
-                const int i = min(first + k, last);
+                const int i = (int)min(first + k, (unsigned)last);
                 p[k].load(m, g, i, with_f, nvel, ovf < 0 || i >= ovf);
             }
         }
@@ -498,7 +498,7 @@ __device__ __forceinline__ void count_tile(const Geo& g, const SortSmem<PREC>& s
                                            const Prev& pv, int ovf, int* s_aux, const unsigned* s_shear, int* s_ovf)
 {
     constexpr int K = count_mpt<PREC>();
-    const int first = base + threadIdx.x * K;
+    const unsigned first = tile_item(base, threadIdx.x * K);
     if constexpr (IMPL) {
         // implied cells: this thread's K consecutive positions are its own slots
         int ob[K];
@@ -506,7 +506,7 @@ __device__ __forceinline__ void count_tile(const Geo& g, const SortSmem<PREC>& s
             tile_buckets<K, false>(g, pv, base, min(last + 1, ovf), sm.hist, s_aux, ob);
 #pragma unroll
             for (int k = 0; k < K; ++k)
-                if (first + k < ovf) grp.p[k].cell = ob[k];
+                if (first + k < (unsigned)ovf) grp.p[k].cell = ob[k];
         }
     }
 #pragma unroll
@@ -540,13 +540,13 @@ __device__ __forceinline__ void count_tile(const Geo& g, const SortSmem<PREC>& s
         for (int k = 0; k < K; ++k) bkt[k] = (unsigned)row[k] < (unsigned)g.nrow ? (row[k] << g.lognx) + col[k] : g.nb;
 #pragma unroll
         for (int k = 0; k < K; ++k)
-            if (first + k > last) bkt[k] = kNoBucket;
+            if (first + k > (unsigned)last) bkt[k] = kNoBucket;
     } else {
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             // FP32 form: as above, copies of the last marker are pushed too
-            if (PUSH && (PREC == 1 || first + k <= last)) grp.p[k].push(g, sm.sE, sm.sRow, dtk, bk, fl);
-            bkt[k] = first + k <= last ? grp.p[k].bucket(g) : kNoBucket;
+            if (PUSH && (PREC == 1 || first + k <= (unsigned)last)) grp.p[k].push(g, sm.sE, sm.sRow, dtk, bk, fl);
+            bkt[k] = first + k <= (unsigned)last ? grp.p[k].bucket(g) : kNoBucket;
         }
     }
     // outside the window: the overflow bucket's own counter, or a global atomic
@@ -594,15 +594,6 @@ __device__ __forceinline__ void count_tile(const Geo& g, const SortSmem<PREC>& s
     if (threadIdx.x == 0 && *s_ovf) atomicAdd(&counts[g.nb], *s_ovf);
 }
 
-// Tile t of the count pass covers markers [t*T, ...), T = count_tile_size; in
-// the FP32 form the push needs the velocity offset b[0] only.
-template <int PREC>
-__device__ __forceinline__ int count_tile_last(const Geo& g, int t)
-{
-    constexpr int T = kSortThreads * count_mpt<PREC>();
-    return min(t * T + T, g.n) - 1;
-}
-
 // count pass of one block over one tile (1D-3V, kicks of velocity cells, and
 // large dense FP64 sorts)
 template <int PREC, int VD, bool PUSH, bool IMPL>
@@ -620,9 +611,10 @@ __device__ __forceinline__ void count_block(const Geo& g, const typename Markers
     constexpr int K = count_mpt<PREC>();
     Group<PREC, VD, K> grp;
     const int base = blk * (kSortThreads * K);
-    const int last = count_tile_last<PREC>(g, blk);
+    const int last = tile_last(base, kSortThreads * K, g.n);
     const int ovf = IMPL ? pv.off[g.nb] : -1;
-    grp.load(m, g, base + threadIdx.x * K, last, false, PREC ? 1 : VD, ovf);
+    // the FP32 form's push needs the velocity offset b[0] only
+    grp.load(m, g, tile_item(base, threadIdx.x * K), last, false, PREC ? 1 : VD, ovf);
     int fl = 0;
     count_tile<PREC, VD, PUSH, IMPL>(g, sm, grp, dtk, bk, counts, base, last, s_b, fl, pv,
                                      ovf, s_aux, &s_shear, &s_ovf);
@@ -648,7 +640,7 @@ __global__ __launch_bounds__(kSortThreads) void k_count(Geo g, typename MarkersO
                                                          int* __restrict__ counts, int* __restrict__ flags, Prev pv)
 {
     const int t = block_tile<VD>(blockIdx.x, gridDim.x);
-    if (t * (kSortThreads * count_mpt<PREC>()) >= g.n) return;
+    if (!tile_starts(t, kSortThreads * count_mpt<PREC>(), g.n)) return;
     count_block<PREC, VD, PUSH, IMPL>(g, m, E, rows_g, dtk, bk, counts, flags, t, pv);
 }
 
@@ -777,7 +769,7 @@ __device__ __forceinline__ void scatter_block(const Geo& g, const typename Marke
     __shared__ int s_b[2], s_flags, s_aux[kSortThreads / kWave + 1], s_ovf;
     __shared__ unsigned s_shear;
     const int base = blk * kSortTile;
-    const int last = min(base + kSortTile, g.n) - 1;
+    const int last = tile_last(base, kSortTile, g.n);
     const int ovf = IMPL ? pv.off[g.nb] : -1;
     if (threadIdx.x == 0) s_flags = 0;
     if (PUSH) note_shear(stage_tables<PREC>(g, sm.sE, sm.sRow, E, rows_g, dtk, bk), &s_shear);
@@ -801,7 +793,7 @@ __global__ __launch_bounds__(kSortThreads) void k_scatter1(Geo g, typename Marke
                                                            int* __restrict__ counts, int* __restrict__ flags, Prev pv)
 {
     const int t = block_tile<VD>(blockIdx.x, gridDim.x);
-    if (t * kSortTile >= g.n) return;
+    if (!tile_starts(t, kSortTile, g.n)) return;
     scatter_block<PREC, VD, PUSH, IMPL>(g, src, dst, E, rows_g, dtk, bk, offsets, counts, flags, t, pv, g.hist_bins);
 }
 
@@ -1418,36 +1410,19 @@ __global__ __launch_bounds__(1024) void k_scan_tiles(int* __restrict__ tile_sums
 enum : int { SCAN_TOTALS = 0, SCAN_PREFIXED = 1, SCAN_COUNTS = 2 };
 constexpr int kScanDirect = 24;                      // tiles up to which the counts are summed
 
-// This thread's part of the sum of counts [first, last), first a multiple of
-// 4: 16-byte loads, eight in flight.
-__device__ __forceinline__ int scan_part(const int* __restrict__ counts, int nbt, int first, int last)
+// This thread's part of the sum of the counts [first, last).
+__device__ __forceinline__ int count_part(const int* __restrict__ counts, unsigned first, unsigned last)
 {
-    int s = 0;
-    for (int i = first + 4 * (int)threadIdx.x; i < last; i += 8 * 4 * kScanThreads) {
-        int4 v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int b = i + u * 4 * kScanThreads;
-            v[u] = make_int4(0, 0, 0, 0);
-            if (b + 4 <= last) {
-                v[u] = *reinterpret_cast<const int4*>(counts + b);
-            } else if (b < last) {
-                v[u].x = counts[b];
-                if (b + 1 < last) v[u].y = counts[b + 1];
-                if (b + 2 < last) v[u].z = counts[b + 2];
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) s += (v[u].x + v[u].y) + (v[u].z + v[u].w);
-    }
-    return s;
+    return scan_part([=](unsigned b) { return *reinterpret_cast<const int4*>(counts + b); },
+                     [=](unsigned b) { return counts[b]; }, first, last, threadIdx.x);
 }
 
 // Total of one tile of kScanTile bucket counts.
 __device__ __forceinline__ void scan_total(const int* __restrict__ counts, int nbt, int* __restrict__ tsum, int tile)
 {
     __shared__ int s_w[kScanThreads / kWave];
-    const int inc = wave_incl_scan(scan_part(counts, nbt, tile * kScanTile, min((tile + 1) * kScanTile, nbt)));
+    const int base = tile * kScanTile;
+    const int inc = wave_incl_scan(count_part(counts, base, tile_last(base, kScanTile, nbt) + 1));
     if ((threadIdx.x & (kWave - 1)) == kWave - 1) s_w[threadIdx.x / kWave] = inc;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -1472,18 +1447,18 @@ __device__ __forceinline__ void scan_tile(const int* __restrict__ counts, int nb
     constexpr int W = kScanThreads / kWave;
     __shared__ int s_pre[W], s_cnt[W];
     // the tile's counts first, so their loads overlap the tile-start sum
-    const int base = tile * kScanTile + threadIdx.x * kScanItems;
+    const unsigned base = tile_item(tile * kScanTile, threadIdx.x * kScanItems), end = nbt;
     int c[kScanItems] = {0, 0, 0, 0};
-    if (base + kScanItems <= nbt) {
+    if (base + kScanItems <= end) {
         const int4 v = *reinterpret_cast<const int4*>(counts + base);
         c[0] = v.x; c[1] = v.y; c[2] = v.z; c[3] = v.w;
     } else {
 #pragma unroll
         for (int k = 0; k < kScanItems; ++k)
-            if (base + k < nbt) c[k] = counts[base + k];
+            if (base + k < end) c[k] = counts[base + k];
     }
     int part = 0;
-    if (from == SCAN_COUNTS) part = scan_part(counts, nbt, 0, tile * kScanTile);
+    if (from == SCAN_COUNTS) part = count_part(counts, 0, tile * kScanTile);
     else if (from == SCAN_TOTALS)
         for (int t = threadIdx.x; t < tile; t += kScanThreads) part += tsum[t];
     const int s = (c[0] + c[1]) + (c[2] + c[3]);
@@ -1513,14 +1488,14 @@ __device__ __forceinline__ void scan_tile(const int* __restrict__ counts, int nb
 #pragma unroll
         for (int k = 0; k < kScanItems; ++k)
             for (int t = (o[k] + kTfStride - 1) >> kTfLog; c[k] > 0 && t <= (o[k] + c[k] - 1) >> kTfLog; ++t)
-                tfirst[t] = base + k;
+                tfirst[t] = (int)(base + k);
     }
-    if (base + kScanItems <= nbt) {
+    if (base + kScanItems <= end) {
         *reinterpret_cast<int4*>(offsets + base) = make_int4(o[0], o[1], o[2], o[3]);
     } else {
 #pragma unroll
         for (int k = 0; k < kScanItems; ++k)
-            if (base + k < nbt) offsets[base + k] = o[k];
+            if (base + k < end) offsets[base + k] = o[k];
     }
 }
 
@@ -1666,7 +1641,7 @@ static hipError_t launch_sort_t(const Geo& g, void* src, void* dst, const double
     if (g.n == 0 && phase != 1) return hipSuccess;   // the scan still runs: offsets become zero
     if (phase == 1) {
         const int nbt = g.nb + 1;
-        const int ntiles = (nbt + kScanTile - 1) / kScanTile;
+        const int ntiles = tile_count(kScanTile, nbt);
         int from = SCAN_COUNTS;
         if (ntiles > kScanDirect) {
             hipLaunchKernelGGL(k_scan_total, dim3(ntiles), dim3(kScanThreads), 0, st, counts, nbt, tile_sums);
@@ -1693,7 +1668,7 @@ static hipError_t launch_sort_t(const Geo& g, void* src, void* dst, const double
             if (e != hipSuccess) return e;
         }
         const dim3 bl(kSortThreads);
-        const dim3 cg(((g.n + count_tile_size(PREC) - 1) / count_tile_size(PREC) + 7) & ~7), sg(((g.n + kSortTile - 1) / kSortTile + 7) & ~7);
+        const dim3 cg((tile_count(count_tile_size(PREC), g.n) + 7) & ~7), sg((tile_count(kSortTile, g.n) + 7) & ~7);
         if (phase == 0) {
             if (push) launch(k_count<PREC, VD, true>, cg, bl, smem, st, g, s, E, rows, dtk, bk, counts, flags, pv);
             else launch(k_count<PREC, VD, false>, cg, bl, smem, st, g, s, E, rows, dtk, bk, counts, flags, pv);
@@ -1869,7 +1844,7 @@ hipError_t launch_push(const Geo& g, void* m, const double* E, const RowShift* r
                        int* flags, hipStream_t st)
 {
     if (g.n == 0) return hipSuccess;
-    const int blocks = (g.n + kSortTile - 1) / kSortTile;
+    const int blocks = tile_count(kSortTile, g.n);
     const size_t smem = (g.prec ? sizeof(float2) : sizeof(double)) * g.nx + (g.prec ? sizeof(RowShift) * (g.nv[0] + 1) : 0);
     if (g.prec == 0 && g.vdim == 1) hipLaunchKernelGGL((k_push<0, 1>), dim3(blocks), dim3(kSortThreads), smem, st, g, *reinterpret_cast<M64*>(m), E, rows, dtk, bk, flags);
     else if (g.prec == 0) hipLaunchKernelGGL((k_push<0, 3>), dim3(blocks), dim3(kSortThreads), smem, st, g, *reinterpret_cast<M64*>(m), E, rows, dtk, bk, flags);
