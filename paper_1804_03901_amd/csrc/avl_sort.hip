@@ -1152,10 +1152,12 @@ __device__ __forceinline__ void scatter_wave(const Geo& g, const SortSmem<PREC>&
         if (base < ovf) {
             int ob[K];
             wave_buckets<K>(g, pv, base, min(last + 1, ovf), lane, map, ob, ahead);
-            // past the end of the tile the map holds its last run
+            // past the end of the tile the map holds its last run, and the
+            // lanes copies of its last marker: pushed like it, they raise no
+            // flag that it does not raise
 #pragma unroll
             for (int k = 0; k < K; ++k)
-                if (base + k * kWave + lane < ovf) p[k].cell = map[k * kWave + lane];
+                if (min(base + k * kWave + lane, last) < ovf) p[k].cell = map[k * kWave + lane];
         }
     }
     int b0, b1;
