@@ -61,6 +61,7 @@ hipError_t launch_fill_f64(double* p, int n, double value, hipStream_t st);
 hipError_t launch_scale_f64(double* p, int n, double s, hipStream_t st);
 int sort_blocks(const Geo& g, int phase);
 size_t sort_lds(const Geo& g);
+bool block_sort_fits(const Geo& g);
 int recon_waves_per_cu(const Geo& g, int lds_per_cu);
 int recon3_waves_per_cu(int prec);
 int scatter_blocks_per_cu(const Geo& g);
@@ -672,12 +673,12 @@ int load_markers(avl_handle* h, const double* x, const double* v, const double* 
     if (g.vdim == 1) {
         // which sort kernels the steps take (results do not depend on it): the
         // loaded field's largest kick, in velocity cells
-        std::vector<double> E(g.nx);
-        AVL_TRY(hipMemcpyAsync(E.data(), h->E, sizeof(double) * g.nx, hipMemcpyDeviceToHost, h->st));
+        double E[kMaxNx];
+        AVL_TRY(hipMemcpyAsync(E, h->E, sizeof(double) * g.nx, hipMemcpyDeviceToHost, h->st));
         AVL_TRY(hipStreamSynchronize(h->st));
-        h->g.follow = 0;
-        for (double e : E)
-            if (std::fabs(e * (g.qm * g.dt * g.inv_dv[0])) >= 1.0) h->g.follow = 1;
+        bool cells = false;
+        for (int i = 0; i < g.nx; ++i) cells = cells || std::fabs(E[i] * (g.qm * g.dt * g.inv_dv[0])) >= 1.0;
+        h->g.follow = cells && block_sort_fits(g) ? 1 : 0;
     }
     return AVL_OK;
 }

@@ -1544,6 +1544,11 @@ static bool block_scatter64(const Geo& g)
     return g.prec == 0 && g.n >= 1 << 23 && g.nx <= 1024 && g.n / 8 >= g.nb;
 }
 
+// Whether the block kernels fit a block's LDS (64 bytes of it static).  In FP32
+// their map of a tile's buckets does not shrink, and the wave kernels' does: with
+// tables of over 147,392 bytes (18,416 velocity rows on 8 columns) only those fit.
+bool block_sort_fits(const Geo& g) { return (g.prec ? sort_smem<1>(g) : sort_smem<0>(g)) + 64 <= (size_t)lds_limit(); }
+
 // LDS of the wave kernels (1D-1V): tables, and each wave's window (which also
 // holds a tile's implied buckets in FP32).
 template <int PREC>

@@ -1,0 +1,51 @@
+"""Which sort kernels a step takes: every choice against the oracle.
+
+The sums N = f D and D of a state against the oracle's, from the exported markers,
+hold only if each marker lies in the run of its cell; bounds as for a step
+elsewhere, 1e-12 normwise in FP64 and 1e-5 in the FP32 form.
+"""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle
+from checks import nrel
+from paper_1804_03901_amd import avl, inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def _sim(w, markers, precision, **kw):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    x, v, f = markers
+    print(f"[case] {w.name} nx={w.nx} nv={w.nv} n={x.size} prec={precision}", flush=True)
+    return avl.Simulation(w, x, v.reshape(-1), f, precision=precision, **kw)
+
+
+def _check(sim, w, precision):
+    sim.check()
+    xs, vs, fs = (t.double().cpu().numpy() for t in sim.markers())
+    fg, Dg = (t.double().cpu().numpy() for t in sim.reconstruct(want_D=True))
+    No, Do, _ = oracle.reconstruct(oracle.Grid.from_workload(w), xs, vs.reshape(w.vdim, -1), fs)
+    tol = 1e-12 if precision == avl.AVL_FP64 else 1e-5
+    assert nrel(Dg, Do) <= tol and nrel(fg * Dg, No) <= tol
+
+
+def _kick(sim, w):
+    """Largest kick of the current field, in velocity cells."""
+    return float(sim.field()[0].abs().max()) * abs(w.q / w.m) * w.dt / w.dv(0)
+
+
+@pytest.mark.parametrize("nx,nv", [(8, 18300), (8, 18420), (8, 18500), (512, 17950)])
+def test_drift_table_that_leaves_the_block_kernels_no_room(nx, nv):
+    # FP32 drift and field tables of 146 to 148 KB: the wave kernels' maps still fit a
+    # block's 160 KB, the block kernels' map fits the first case only
+    w = inputs.paper_landau(ppc=1).replace(nx=nx, nv=(nv, 1, 1))
+    sim = _sim(w, inputs.markers(w), avl.AVL_FP32)
+    assert _kick(sim, w) > 1.0
+    for graph in (False, True):
+        sim.step(2, graph=graph)
+        _check(sim, w, avl.AVL_FP32)
+    sim.close()
