@@ -1155,9 +1155,10 @@ __device__ __forceinline__ void scatter_wave(const Geo& g, const SortSmem<PREC>&
             // past the end of the tile the map holds its last run, and the
             // lanes copies of its last marker: pushed like it, they raise no
             // flag that it does not raise
+            const int end = last < ovf ? base + kWTile<K> : ovf;
 #pragma unroll
             for (int k = 0; k < K; ++k)
-                if (min(base + k * kWave + lane, last) < ovf) p[k].cell = map[k * kWave + lane];
+                if (base + k * kWave + lane < end) p[k].cell = map[k * kWave + lane];
         }
     }
     int b0, b1;
