@@ -61,7 +61,6 @@ hipError_t launch_fill_f64(double* p, int n, double value, hipStream_t st);
 hipError_t launch_scale_f64(double* p, int n, double s, hipStream_t st);
 int sort_blocks(const Geo& g, int phase);
 size_t sort_lds(const Geo& g);
-bool block_sort_fits(const Geo& g);
 int recon_waves_per_cu(const Geo& g, int lds_per_cu);
 int recon3_waves_per_cu(int prec);
 int scatter_blocks_per_cu(const Geo& g);
@@ -222,7 +221,7 @@ int make_geo(const avl_config* c, Geo* g)
         int64_t want = (int64_t)(std::ceil(span) + 3) * c->nx;
         want = std::max<int64_t>(want, 4 * (int64_t)c->nx);
         // one more row, which a window that follows the kick asks for, where it
-        // fits in what the FP32 1D-1V form holds anyway
+        // costs no more than 16 KB
         if (want + c->nx <= kCountTile) want += c->nx;
         if (g->magnetic) {
             // the window also covers the neighbouring vy and vz planes a
@@ -670,7 +669,7 @@ int load_markers(avl_handle* h, const double* x, const double* v, const double* 
     if ((rc = do_sort(h, false, 1.0))) return rc;
     if ((rc = do_recon(h, nullptr))) return rc;
     if ((rc = do_field(h, nullptr, false, nullptr))) return rc;
-    if (g.vdim == 1) {
+    if (g.vdim == 1 && g.prec == AVL_FP64) {
         // which sort kernels the steps take (results do not depend on it): the
         // loaded field's largest kick, in velocity cells
         double E[kMaxNx];
@@ -678,7 +677,7 @@ int load_markers(avl_handle* h, const double* x, const double* v, const double* 
         AVL_TRY(hipStreamSynchronize(h->st));
         bool cells = false;
         for (int i = 0; i < g.nx; ++i) cells = cells || std::fabs(E[i] * (g.qm * g.dt * g.inv_dv[0])) >= 1.0;
-        h->g.follow = cells && block_sort_fits(g) ? 1 : 0;
+        h->g.follow = cells ? 1 : 0;
     }
     return AVL_OK;
 }

@@ -92,7 +92,7 @@ struct Geo {
     int vchunk;          // 1D-3V: chunks of x-velocity rows
     int nchunk, nstrip;  // reconstruct chunks along v and column strips along x
     int hist_bins;       // LDS histogram bins per sort block
-    int follow;          // 1D-1V: the loaded state's kicks reach a velocity cell
+    int follow;          // FP64 1D-1V: the loaded state's kicks reach a velocity cell
     int wbins;           // 1D-1V: LDS bins of a wave's window in the count and scatter
     int cap;             // markers staged in LDS per reconstruct wave
     int jpad, jrange;    // FP32 1D-3V: x-velocity dual index stored with offset jpad, range jrange

@@ -14,7 +14,7 @@
 //
 // Counting uses integer atomics only.  Consecutive markers of the previous
 // order land in few buckets after the push, so a wave (1D-1V) or a block
-// (1D-3V, and kicks of velocity cells) counts its markers in an LDS window of
+// (1D-3V, and FP64 kicks of velocity cells) counts its markers in an LDS window of
 // the buckets it expects and issues one global atomic per touched bucket.  The
 // windows follow the markers: by the drift and kick of the tile, by the kick
 // column by column, or over the planes a gyration reaches.  Markers that miss
@@ -31,9 +31,9 @@
 // bucket is the run its position falls in.  So the scatter stores the cell
 // index only for markers of the overflow bucket, and the next sort recovers
 // every other cell from the previous run offsets: per tile, the starts of the
-// runs inside it are marked in LDS and a running maximum over the wave (or
-// block) fills in the rest (the scan also records the bucket of every
-// kTfStride-th position, where each tile starts).  That is 4 bytes a marker less to read in the count
+// runs inside it are marked in LDS and a running maximum over the wave fills in
+// the rest (the scan also records the bucket of every kTfStride-th position,
+// where each tile starts).  That is 4 bytes a marker less to read in the count
 // and the scatter and to write in the scatter.
 #include <algorithm>
 #include <type_traits>
@@ -213,7 +213,6 @@ template <int VD, int K> struct Group<1, VD, K> {
 // Implied cells: the previous order's buckets of one tile's positions.
 // ---------------------------------------------------------------------------
 constexpr int kNoBucket = 0x7fffffff;        // past the last marker
-static_assert(kSortTile % kTfStride == 0 && kCountTile % kTfStride == 0, "tiles start at recorded positions");
 
 // The order the markers are in, for implied cells: its run offsets (nb + 2
 // entries) and the bucket of every kTfStride-th position.  off == nullptr:
@@ -224,69 +223,6 @@ struct Prev {
 };
 
 __device__ __forceinline__ int tile_first_run(const Prev& pv, int base) { return pv.tfirst[base >> kTfLog]; }
-
-// Buckets of the positions [base, end) of a tile (base a multiple of
-// kTfStride, end at most the start of the overflow run): the largest b with
-// off[b] <= p.  Thread t owns the SL slots [t SL, t SL + SL) of `map` (T =
-// kSortThreads SL ints of LDS, free on entry) and gets their buckets in bk[]
-// (undefined past end); with WRITE they are also left in map for other
-// threads, after a barrier.  s_aux: kSortThreads / kWave + 1 ints of LDS.
-template <int SL, bool WRITE>
-__device__ __forceinline__ void tile_buckets(const Geo& g, const Prev& pv, int base, int end, int* map, int* s_aux,
-                                             int (&bk)[SL])
-{
-    static_assert(SL % 4 == 0, "slots are cleared and read as 16-byte vectors");
-    const int tid = threadIdx.x;
-    const int b0 = tile_first_run(pv, base);       // the run that holds position base
-#pragma unroll
-    for (int k = 0; k < SL; k += 4) *reinterpret_cast<int4*>(map + tid * SL + k) = make_int4(-1, -1, -1, -1);
-    if (tid == 0) map[0] = b0;
-    __syncthreads();
-    // mark the start of every later run that begins inside the tile
-    for (int bs = b0 + 1;; bs += kSortThreads) {
-        const int b = bs + tid;
-        int lo = end;
-        if (b < g.nb) {
-            lo = pv.off[b];
-            const int hi = pv.off[b + 1];
-            if (lo < hi && lo > base && lo < end) map[lo - base] = b;
-        }
-        if (tid == kSortThreads - 1) s_aux[kSortThreads / kWave] = (b < g.nb && lo < end) ? 1 : 0;
-        __syncthreads();
-        const int more = s_aux[kSortThreads / kWave];
-        if (!more) break;
-        // the flag is written again by the next pass
-        __syncthreads();
-    }
-    // running maximum over the slots: within the thread, then across threads
-#pragma unroll
-    for (int k = 0; k < SL; k += 4) {
-        const int4 v = *reinterpret_cast<const int4*>(map + tid * SL + k);
-        bk[k] = v.x; bk[k + 1] = v.y; bk[k + 2] = v.z; bk[k + 3] = v.w;
-    }
-#pragma unroll
-    for (int k = 1; k < SL; ++k) bk[k] = max(bk[k], bk[k - 1]);
-    const int lane = tid & (kWave - 1), w = tid / kWave;
-    int inc = bk[SL - 1];
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const int t = __shfl_up(inc, o, kWave);
-        if (lane >= o) inc = max(inc, t);
-    }
-    int carry = __shfl_up(inc, 1, kWave);
-    if (lane == 0) carry = -1;
-    if (lane == kWave - 1) s_aux[w] = inc;
-    __syncthreads();
-    for (int q = 0; q < w; ++q) carry = max(carry, s_aux[q]);
-#pragma unroll
-    for (int k = 0; k < SL; ++k) bk[k] = max(bk[k], carry);
-    if constexpr (WRITE) {
-#pragma unroll
-        for (int k = 0; k < SL; k += 4)
-            *reinterpret_cast<int4*>(map + tid * SL + k) = make_int4(bk[k], bk[k + 1], bk[k + 2], bk[k + 3]);
-        __syncthreads();
-    }
-}
 
 // The LDS window of a sort block: the buckets its markers are expected to
 // land in, counted in LDS slots 0 .. nbw-1.  The block's first and last marker
@@ -491,24 +427,13 @@ struct SortSmem {
 // One tile of the count pass: the thread's group of K consecutive markers
 // [first, first+K) of the tile [base, last] is in grp (previous order), the
 // field and drift table staged in LDS.
-template <int PREC, int VD, bool PUSH, bool IMPL>
+template <int PREC, int VD, bool PUSH>
 __device__ __forceinline__ void count_tile(const Geo& g, const SortSmem<PREC>& sm, Group<PREC, VD, count_mpt<PREC>()>& grp,
                                            double dtk, float bk, int* __restrict__ counts,
-                                           int base, int last, int* s_b, int& fl,
-                                           const Prev& pv, int ovf, int* s_aux, const unsigned* s_shear, int* s_ovf)
+                                           int base, int last, int* s_b, int& fl, const unsigned* s_shear, int* s_ovf)
 {
     constexpr int K = count_mpt<PREC>();
     const unsigned first = tile_item(base, threadIdx.x * K);
-    if constexpr (IMPL) {
-        // implied cells: this thread's K consecutive positions are its own slots
-        int ob[K];
-        if (base < ovf) {
-            tile_buckets<K, false>(g, pv, base, min(last + 1, ovf), sm.hist, s_aux, ob);
-#pragma unroll
-            for (int k = 0; k < K; ++k)
-                if (first + k < (unsigned)ovf) grp.p[k].cell = ob[k];
-        }
-    }
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         if (first + k == base) s_b[0] = grp.p[k].bucket(g);
@@ -521,33 +446,12 @@ __device__ __forceinline__ void count_tile(const Geo& g, const SortSmem<PREC>& s
     if (threadIdx.x == 0) *s_ovf = 0;
     __syncthreads();
     int bkt[K];
-    if constexpr (PUSH && PREC == 1 && VD == 1) {
-        // 1D-1V FP32 form: only the new buckets; past the last marker the
-        // group holds copies of it, pushed too (the markers' LDS round trips
-        // interleave) and not counted.  The flags are raised by the scatter,
-        // which pushes the same markers with the same field.
-        int c[K];
-        float a[K], b[K];
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-            c[k] = grp.p[k].cell;
-            a[k] = grp.p[k].a;
-            b[k] = grp.p[k].b[0];
-        }
-        int row[K], col[K];
-        push32_cells<K>(g, sm.sE, sm.sRow, c, a, b, row, col);
-#pragma unroll
-        for (int k = 0; k < K; ++k) bkt[k] = (unsigned)row[k] < (unsigned)g.nrow ? (row[k] << g.lognx) + col[k] : g.nb;
-#pragma unroll
-        for (int k = 0; k < K; ++k)
-            if (first + k > (unsigned)last) bkt[k] = kNoBucket;
-    } else {
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            // FP32 form: as above, copies of the last marker are pushed too
-            if (PUSH && (PREC == 1 || first + k <= (unsigned)last)) grp.p[k].push(g, sm.sE, sm.sRow, dtk, bk, fl);
-            bkt[k] = first + k <= (unsigned)last ? grp.p[k].bucket(g) : kNoBucket;
-        }
+    for (int k = 0; k < K; ++k) {
+        // FP32 form: past the last marker the group holds copies of it, pushed
+        // too (the markers' LDS round trips interleave) and not counted
+        if (PUSH && (PREC == 1 || first + k <= (unsigned)last)) grp.p[k].push(g, sm.sE, sm.sRow, dtk, bk, fl);
+        bkt[k] = first + k <= (unsigned)last ? grp.p[k].bucket(g) : kNoBucket;
     }
     // outside the window: the overflow bucket's own counter, or a global atomic
     auto add_outside = [&](int b, int c) {
@@ -594,17 +498,16 @@ __device__ __forceinline__ void count_tile(const Geo& g, const SortSmem<PREC>& s
     if (threadIdx.x == 0 && *s_ovf) atomicAdd(&counts[g.nb], *s_ovf);
 }
 
-// count pass of one block over one tile (1D-3V, kicks of velocity cells, and
-// large dense FP64 sorts)
-template <int PREC, int VD, bool PUSH, bool IMPL>
+// count pass of one block over one tile (1D-3V, and FP64 kicks of velocity cells)
+template <int PREC, int VD, bool PUSH>
 __device__ __forceinline__ void count_block(const Geo& g, const typename MarkersOf<PREC>::T& m,
                                             const double* __restrict__ E, const RowShift* __restrict__ rows_g,
                                             double dtk, float bk, int* __restrict__ counts,
-                                            int* __restrict__ flags, int blk, const Prev& pv)
+                                            int* __restrict__ flags, int blk)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     SortSmem<PREC> sm(smem, g);
-    __shared__ int s_b[2], s_flags, s_aux[kSortThreads / kWave + 1], s_ovf;
+    __shared__ int s_b[2], s_flags, s_ovf;
     __shared__ unsigned s_shear;
     if (threadIdx.x == 0) s_flags = 0;
     if (PUSH) note_shear(stage_tables<PREC>(g, sm.sE, sm.sRow, E, rows_g, dtk, bk), &s_shear);
@@ -612,12 +515,10 @@ __device__ __forceinline__ void count_block(const Geo& g, const typename Markers
     Group<PREC, VD, K> grp;
     const int base = blk * (kSortThreads * K);
     const int last = tile_last(base, kSortThreads * K, g.n);
-    const int ovf = IMPL ? pv.off[g.nb] : -1;
     // the FP32 form's push needs the velocity offset b[0] only
-    grp.load(m, g, tile_item(base, threadIdx.x * K), last, false, PREC ? 1 : VD, ovf);
+    grp.load(m, g, tile_item(base, threadIdx.x * K), last, false, PREC ? 1 : VD);
     int fl = 0;
-    count_tile<PREC, VD, PUSH, IMPL>(g, sm, grp, dtk, bk, counts, base, last, s_b, fl, pv,
-                                     ovf, s_aux, &s_shear, &s_ovf);
+    count_tile<PREC, VD, PUSH>(g, sm, grp, dtk, bk, counts, base, last, s_b, fl, &s_shear, &s_ovf);
     if (fl) atomicOr(&s_flags, fl);
     __syncthreads();
     if (threadIdx.x == 0 && s_flags) atomicOr(flags, s_flags);
@@ -632,16 +533,16 @@ __device__ __forceinline__ void count_block(const Geo& g, const typename Markers
 template <int VD>
 __device__ __forceinline__ int block_tile(int b, int n) { return VD == 3 ? (b & 7) * (n >> 3) + (b >> 3) : b; }
 
-template <int PREC, int VD, bool PUSH, bool IMPL = false>
+template <int PREC, int VD, bool PUSH>
 __global__ __launch_bounds__(kSortThreads) void k_count(Geo g, typename MarkersOf<PREC>::T m,
                                                          const double* __restrict__ E,
                                                          const RowShift* __restrict__ rows_g,
                                                          double dtk, float bk,
-                                                         int* __restrict__ counts, int* __restrict__ flags, Prev pv)
+                                                         int* __restrict__ counts, int* __restrict__ flags)
 {
     const int t = block_tile<VD>(blockIdx.x, gridDim.x);
     if (!tile_starts(t, kSortThreads * count_mpt<PREC>(), g.n)) return;
-    count_block<PREC, VD, PUSH, IMPL>(g, m, E, rows_g, dtk, bk, counts, flags, t, pv);
+    count_block<PREC, VD, PUSH>(g, m, E, rows_g, dtk, bk, counts, flags, t);
 }
 
 // ---------------------------------------------------------------------------
@@ -659,26 +560,14 @@ static_assert(kSortTile <= 1 << kRankBits && kOverflowSlot > 160 * 1024 / 4, "sl
 
 // One tile of the scatter: the markers [base, last] of the previous order are
 // in p[] (lane-strided), the field and drift table staged in LDS.
-template <int PREC, int VD, bool PUSH, bool IMPL>
+template <int PREC, int VD, bool PUSH>
 __device__ __forceinline__ void scatter_tile(const Geo& g, const SortSmem<PREC>& sm, Pay<PREC, VD>* p,
                                              const typename MarkersOf<PREC>::T& dst, double dtk, float bk,
                                              const int* __restrict__ offsets, int* __restrict__ counts,
                                              int base, int last, int* s_b, int& fl,
-                                             const Prev& pv, int ovf, int* s_aux, const unsigned* s_shear, int* s_ovf, int maxbins)
+                                             const unsigned* s_shear, int* s_ovf)
 {
     constexpr int K = kSortMPT;
-    if constexpr (IMPL) {
-        // implied cells: the tile's buckets are left in LDS, read lane-strided
-        if (base < ovf) {
-            int ob[K];
-            tile_buckets<K, true>(g, pv, base, min(last + 1, ovf), sm.hist, s_aux, ob);
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const int i = base + k * kSortThreads + threadIdx.x;
-                if (i <= last && i < ovf) p[k].cell = sm.hist[i - base];
-            }
-        }
-    }
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const int i = base + k * kSortThreads + threadIdx.x;
@@ -687,7 +576,7 @@ __device__ __forceinline__ void scatter_tile(const Geo& g, const SortSmem<PREC>&
     }
     __syncthreads();
     // every thread forms the window from the tile's two end buckets itself
-    const Window w = set_window<PREC, VD>(g, s_b[0], s_b[1], PUSH && *s_shear != 0, sm.sRow, maxbins);
+    const Window w = set_window<PREC, VD>(g, s_b[0], s_b[1], PUSH && *s_shear != 0, sm.sRow, g.hist_bins);
     for (int i = threadIdx.x; i < w.nbw; i += blockDim.x) sm.hist[i] = 0;
     if (threadIdx.x == 0) *s_ovf = 0;
     __syncthreads();
@@ -742,59 +631,53 @@ __device__ __forceinline__ void scatter_tile(const Geo& g, const SortSmem<PREC>&
     }
 }
 
-// ovf >= 0: implied cells, stored only at positions >= ovf
 template <int PREC, int VD>
 __device__ __forceinline__ void load_tile(const typename MarkersOf<PREC>::T& src, const Geo& g, Pay<PREC, VD>* p,
-                                          int base, int last, int ovf = -1, bool with_f = true)
+                                          int base, int last)
 {
 #pragma unroll
-    for (int k = 0; k < kSortMPT; ++k) {
-        const int i = min(base + k * kSortThreads + (int)threadIdx.x, last);
-        p[k].load(src, g, i, with_f, VD, ovf < 0 || i >= ovf);
-    }
+    for (int k = 0; k < kSortMPT; ++k)
+        p[k].load(src, g, min(base + k * kSortThreads + (int)threadIdx.x, last), true);
 }
 
-// scatter pass of one block over one tile (1D-3V, kicks of velocity cells, and
-// large dense FP64 sorts)
-template <int PREC, int VD, bool PUSH, bool IMPL>
+// scatter pass of one block over one tile (1D-3V, and in FP64 kicks of velocity
+// cells and large dense sorts)
+template <int PREC, int VD, bool PUSH>
 __device__ __forceinline__ void scatter_block(const Geo& g, const typename MarkersOf<PREC>::T& src,
                                               const typename MarkersOf<PREC>::T& dst,
                                               const double* __restrict__ E, const RowShift* __restrict__ rows_g,
                                               double dtk, float bk, const int* __restrict__ offsets,
-                                              int* __restrict__ counts, int* __restrict__ flags, int blk, const Prev& pv,
-                                              int maxbins)
+                                              int* __restrict__ counts, int* __restrict__ flags, int blk)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     SortSmem<PREC> sm(smem, g);
-    __shared__ int s_b[2], s_flags, s_aux[kSortThreads / kWave + 1], s_ovf;
+    __shared__ int s_b[2], s_flags, s_ovf;
     __shared__ unsigned s_shear;
     const int base = blk * kSortTile;
     const int last = tile_last(base, kSortTile, g.n);
-    const int ovf = IMPL ? pv.off[g.nb] : -1;
     if (threadIdx.x == 0) s_flags = 0;
     if (PUSH) note_shear(stage_tables<PREC>(g, sm.sE, sm.sRow, E, rows_g, dtk, bk), &s_shear);
     Pay<PREC, VD> p[kSortMPT];
-    load_tile<PREC, VD>(src, g, p, base, last, ovf);
+    load_tile<PREC, VD>(src, g, p, base, last);
     int fl = 0;
-    scatter_tile<PREC, VD, PUSH, IMPL>(g, sm, p, dst, dtk, bk, offsets, counts, base, last, s_b, fl,
-                                       pv, ovf, s_aux, &s_shear, &s_ovf, maxbins);
+    scatter_tile<PREC, VD, PUSH>(g, sm, p, dst, dtk, bk, offsets, counts, base, last, s_b, fl, &s_shear, &s_ovf);
     if (fl) atomicOr(&s_flags, fl);
     __syncthreads();
     if (threadIdx.x == 0 && s_flags) atomicOr(flags, s_flags);
 }
 
-template <int PREC, int VD, bool PUSH, bool IMPL = false>
+template <int PREC, int VD, bool PUSH>
 __global__ __launch_bounds__(kSortThreads) void k_scatter1(Geo g, typename MarkersOf<PREC>::T src,
                                                            typename MarkersOf<PREC>::T dst,
                                                            const double* __restrict__ E,
                                                            const RowShift* __restrict__ rows_g,
                                                            double dtk, float bk,
                                                            const int* __restrict__ offsets,
-                                                           int* __restrict__ counts, int* __restrict__ flags, Prev pv)
+                                                           int* __restrict__ counts, int* __restrict__ flags)
 {
     const int t = block_tile<VD>(blockIdx.x, gridDim.x);
     if (!tile_starts(t, kSortTile, g.n)) return;
-    scatter_block<PREC, VD, PUSH, IMPL>(g, src, dst, E, rows_g, dtk, bk, offsets, counts, flags, t, pv, g.hist_bins);
+    scatter_block<PREC, VD, PUSH>(g, src, dst, E, rows_g, dtk, bk, offsets, counts, flags, t);
 }
 
 // ---------------------------------------------------------------------------
@@ -1512,15 +1395,13 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_apply(const int* __restri
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-// LDS of the block kernels: tables and window histogram, which also holds a
-// tile's implied buckets (FP32 1D-1V).
+// LDS of the block kernels: tables and window histogram.
 template <int PREC>
 static size_t sort_smem(const Geo& g)
 {
     size_t e = sizeof(typename MarkersOf<PREC>::E) * g.nx;
     size_t r = PREC ? sizeof(RowShift) * (g.nv[0] + 1) : 0;
-    const int bins = (PREC == 1 && g.vdim == 1) ? std::max(g.hist_bins, kCountTile) : g.hist_bins;
-    return ((e + r + 15) & ~(size_t)15) + sizeof(int) * bins;
+    return ((e + r + 15) & ~(size_t)15) + sizeof(int) * g.hist_bins;
 }
 
 // Markers a lane (K) of the wave kernels.  Small sorts are latency: four a lane
@@ -1545,11 +1426,6 @@ static bool block_scatter64(const Geo& g)
     return g.prec == 0 && g.n >= 1 << 23 && g.nx <= 1024 && g.n / 8 >= g.nb;
 }
 
-// Whether the block kernels fit a block's LDS (64 bytes of it static).  In FP32
-// their map of a tile's buckets does not shrink, and the wave kernels' does: with
-// tables of over 147,392 bytes (18,416 velocity rows on 8 columns) only those fit.
-bool block_sort_fits(const Geo& g) { return (g.prec ? sort_smem<1>(g) : sort_smem<0>(g)) + 64 <= (size_t)lds_limit(); }
-
 // LDS of the wave kernels (1D-1V): tables, and each wave's window (which also
 // holds a tile's implied buckets in FP32).
 template <int PREC>
@@ -1570,20 +1446,27 @@ static hipError_t launch_sort_1v(const Geo& g, const typename MarkersOf<PREC>::T
     const bool impl = pv.off != nullptr;
     const dim3 bl(kSortThreads);
     // Markers whose kicks differ by more rows than a wave's window holds fall
-    // outside it.  Where the loaded state's kicks reach a velocity cell the
+    // outside it.  Where the loaded state's kicks reach a velocity cell the FP64
     // step takes the block kernels, whose window follows the kick column by
-    // column.
-    if (push && impl == F && g.follow) {
-        static int granted[2] = {};
-        const size_t smem = sort_smem<PREC>(g);
-        const int tile = phase == 0 ? count_tile_size(PREC) : kSortTile;
-        const dim3 gr((g.n + tile - 1) / tile);
-        hipError_t e = ensure_lds(phase == 0 ? (const void*)k_count<PREC, 1, true, F> : (const void*)k_scatter1<PREC, 1, true, F>,
-                                  smem, granted[phase != 0]);
-        if (e != hipSuccess) return e;
-        if (phase == 0) launch(k_count<PREC, 1, true, F>, gr, bl, smem, st, g, s, E, rows, dtk, bk, counts, flags, pv);
-        else launch(k_scatter1<PREC, 1, true, F>, gr, bl, smem, st, g, s, d, E, rows, dtk, bk, offsets, counts, flags, pv);
-        return hipGetLastError();
+    // column (13.5M markers on 512 x 6600 at kicks of 8 cells: 446 us a step, by
+    // waves 702); when the field has weakened since, the two are even (376 us at
+    // 0.05 cells).  The FP32 form has its wave kernels only: in a weak field its
+    // block kernels took 458 us there against 370 by waves, 300 against 245 for
+    // 16.8M markers on 1024 x 1024, and what they won at kicks of 8 cells (494
+    // against 747, but 380 against 344) can turn into that loss in any run.
+    if constexpr (PREC == 0) {
+        if (push && g.follow) {
+            static int granted[2] = {};
+            const size_t smem = sort_smem<0>(g);
+            const int tile = phase == 0 ? count_tile_size(0) : kSortTile;
+            const dim3 gr(tile_count(tile, g.n));
+            hipError_t e = ensure_lds(phase == 0 ? (const void*)k_count<0, 1, true> : (const void*)k_scatter1<0, 1, true>,
+                                      smem, granted[phase != 0]);
+            if (e != hipSuccess) return e;
+            if (phase == 0) launch(k_count<0, 1, true>, gr, bl, smem, st, g, s, E, rows, dtk, bk, counts, flags);
+            else launch(k_scatter1<0, 1, true>, gr, bl, smem, st, g, s, d, E, rows, dtk, bk, offsets, counts, flags);
+            return hipGetLastError();
+        }
     }
     const size_t smem = wave_smem<PREC>(g);
     // blocks of four waves for every tile, at most what is resident
@@ -1612,8 +1495,8 @@ static hipError_t launch_sort_1v(const Geo& g, const typename MarkersOf<PREC>::T
         if (e != hipSuccess) return e;
         const dim3 gr((g.n + kSortTile - 1) / kSortTile);
         if constexpr (PREC == 0) {
-            if (push) launch(k_scatter1<0, 1, true>, gr, bl, sb, st, g, s, d, E, rows, dtk, bk, offsets, counts, flags, pv);
-            else launch(k_scatter1<0, 1, false>, gr, bl, sb, st, g, s, d, E, rows, dtk, bk, offsets, counts, flags, pv);
+            if (push) launch(k_scatter1<0, 1, true>, gr, bl, sb, st, g, s, d, E, rows, dtk, bk, offsets, counts, flags);
+            else launch(k_scatter1<0, 1, false>, gr, bl, sb, st, g, s, d, E, rows, dtk, bk, offsets, counts, flags);
         }
         return hipGetLastError();
     }
@@ -1678,11 +1561,11 @@ static hipError_t launch_sort_t(const Geo& g, void* src, void* dst, const double
         const dim3 bl(kSortThreads);
         const dim3 cg((tile_count(count_tile_size(PREC), g.n) + 7) & ~7), sg((tile_count(kSortTile, g.n) + 7) & ~7);
         if (phase == 0) {
-            if (push) launch(k_count<PREC, VD, true>, cg, bl, smem, st, g, s, E, rows, dtk, bk, counts, flags, pv);
-            else launch(k_count<PREC, VD, false>, cg, bl, smem, st, g, s, E, rows, dtk, bk, counts, flags, pv);
+            if (push) launch(k_count<PREC, VD, true>, cg, bl, smem, st, g, s, E, rows, dtk, bk, counts, flags);
+            else launch(k_count<PREC, VD, false>, cg, bl, smem, st, g, s, E, rows, dtk, bk, counts, flags);
         } else {
-            if (push) launch(k_scatter1<PREC, VD, true>, sg, bl, smem, st, g, s, d, E, rows, dtk, bk, offsets, counts, flags, pv);
-            else launch(k_scatter1<PREC, VD, false>, sg, bl, smem, st, g, s, d, E, rows, dtk, bk, offsets, counts, flags, pv);
+            if (push) launch(k_scatter1<PREC, VD, true>, sg, bl, smem, st, g, s, d, E, rows, dtk, bk, offsets, counts, flags);
+            else launch(k_scatter1<PREC, VD, false>, sg, bl, smem, st, g, s, d, E, rows, dtk, bk, offsets, counts, flags);
         }
         return hipGetLastError();
     }

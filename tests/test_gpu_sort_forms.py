@@ -49,3 +49,21 @@ def test_drift_table_that_leaves_the_block_kernels_no_room(nx, nv):
         sim.step(2, graph=graph)
         _check(sim, w, avl.AVL_FP32)
     sim.close()
+
+
+@pytest.mark.parametrize("precision", [avl.AVL_FP64, avl.AVL_FP32])
+@pytest.mark.parametrize("nx,nv,ppc", [(64, 700, 4), (512, 1500, 3), (16, 300, 7)])
+def test_field_that_weakens_and_grows_after_loading(nx, nv, ppc, precision):
+    # loaded with kicks of more than a velocity cell, then stepped by fields on
+    # both sides of one cell, directly and by graph replay
+    w = inputs.paper_landau(ppc=ppc).replace(nx=nx, nv=(nv, 1, 1), mode_amplitude=0.5)
+    sim = _sim(w, inputs.markers(w), precision)
+    loaded = _kick(sim, w)
+    assert loaded > 1.0
+    rho = sim.field()[1].clone()
+    for kick, graph in ((0.05, False), (1.5, False), (0.99, True), (6.0, True), (0.3, True)):
+        sim.poisson(rho * (kick / loaded))
+        assert abs(_kick(sim, w) - kick) < 1e-9 * kick
+        sim.step(1, graph=graph)
+        _check(sim, w, precision)
+    sim.close()
