@@ -86,13 +86,11 @@ typedef enum { AVL_FP64 = 0, AVL_FP32 = 1 } avl_precision;
  * to the run, so that the sums do not depend on the order of the run's markers
  * and every result is reproducible bit for bit.
  *  AVL_OPT_KAHAN32: FP32 form of 1D-1V only: accumulate the four corner sums
- *                   of N and D directly in FP32 with compensated (two-word)
- *                   summation instead; rho is then summed from the quotients
- *                   N/D before they are rounded for the FP32 grid.
- *                   Reproducible to rounding, not bit for bit: the order of a
- *                   run's markers varies from run to run, and moves its sums
- *                   by the square of the FP32 rounding (AVL_ENOTSUP for
- *                   1D-3V, whose reconstruction always sums in FP64). */
+ *                   of N and D directly in FP32 with compensated (Kahan)
+ *                   summation instead (reproducible to rounding, not bit for
+ *                   bit: the order of a run's markers varies from run to run;
+ *                   AVL_ENOTSUP for 1D-3V, whose reconstruction always sums in
+ *                   FP64). */
 typedef enum { AVL_OPT_KAHAN32 = 1 } avl_option;
 
 typedef struct avl_config {

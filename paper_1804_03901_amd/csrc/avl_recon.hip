@@ -36,22 +36,16 @@
 
 namespace avl {
 
-// Compensated sum: s is the plain sum and c the sum of what each addition to s
-// rounded away, exactly (Knuth's two-sum, whichever of s and x is the larger).
-// The value is both words, taken together in FP64: its error is of the order
-// of the square of the format's, so it does not move with the order of the
-// terms, which the sort's atomics set (of the first word alone the last bit
-// does, and E with it by 1e-6 in five steps).
-template <typename T> struct Compensated {
+template <typename T> struct Kahan {
     T s, c;
     __device__ void zero() { s = T(0); c = T(0); }
     __device__ void add(T x) {
-        const T t = s + x;
-        const T z = t - s;
-        c += (s - (t - z)) + (x - z);
+        T y = x - c;
+        T t = s + y;
+        c = (t - s) - y;
         s = t;
     }
-    __device__ double value() const { return (double)s + (double)c; }
+    __device__ T value() const { return s - c; }
 };
 
 // Per-run moments of the marker offsets: with them the four cloud-in-cell
@@ -95,7 +89,7 @@ struct FixMoments {
 // no corner is a difference of larger sums: a corner whose weights are all
 // small keeps its own relative accuracy.
 struct CornerKahan32 {
-    Compensated<float> n00, n10, n01, n11, d00, d10, d01, d11;
+    Kahan<float> n00, n10, n01, n11, d00, d10, d01, d11;
     __device__ void zero() {
         n00.zero(); n10.zero(); n01.zero(); n11.zero();
         d00.zero(); d10.zero(); d01.zero(); d11.zero();
@@ -645,9 +639,7 @@ __device__ __forceinline__ void recon_task(const Geo& g, const typename RT<PREC>
             const size_t gi = (size_t)tj * nx + col;
             fgrid[gi] = (T)fv;
             if (Dgrid) Dgrid[gi] = (T)Dv;
-            // rho is the sum of the stored f; with compensated sums, of the
-            // quotients before FP32 storage rounds them
-            rp += KAHAN ? fv : (double)(T)fv;
+            rp += (double)(T)fv;
         }
         cN = upward ? uN : c.n00;
         cD = upward ? uD : c.d00;
