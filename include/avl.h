@@ -87,10 +87,15 @@ typedef enum { AVL_FP64 = 0, AVL_FP32 = 1 } avl_precision;
  * and every result is reproducible bit for bit.
  *  AVL_OPT_KAHAN32: FP32 form of 1D-1V only: accumulate the four corner sums
  *                   of N and D directly in FP32 with compensated (Kahan)
- *                   summation instead (reproducible to rounding, not bit for
- *                   bit: the order of a run's markers varies from run to run;
+ *                   summation instead; rho is then summed from the quotients
+ *                   N/D before they are rounded for the FP32 grid.
+ *                   Reproducible to rounding, not bit for bit: the order of a
+ *                   run's markers varies from run to run, and its sums with it
+ *                   by an FP32 rounding of a term (512 x 777 cells, 5 markers a
+ *                   cell: 1e-9 in rho; E and the step diagnostics, which are
+ *                   small differences of it, by 3e-7 to 1e-6 in five steps).
  *                   AVL_ENOTSUP for 1D-3V, whose reconstruction always sums in
- *                   FP64). */
+ *                   FP64. */
 typedef enum { AVL_OPT_KAHAN32 = 1 } avl_option;
 
 typedef struct avl_config {

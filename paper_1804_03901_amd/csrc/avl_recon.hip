@@ -45,7 +45,9 @@ template <typename T> struct Kahan {
         c = (t - s) - y;
         s = t;
     }
-    __device__ T value() const { return s - c; }
+    // both words: rounded to one again, the value would lose what c carries, and
+    // its last bit would follow the order of the terms
+    __device__ double value() const { return (double)s - (double)c; }
 };
 
 // Per-run moments of the marker offsets: with them the four cloud-in-cell
@@ -639,7 +641,9 @@ __device__ __forceinline__ void recon_task(const Geo& g, const typename RT<PREC>
             const size_t gi = (size_t)tj * nx + col;
             fgrid[gi] = (T)fv;
             if (Dgrid) Dgrid[gi] = (T)Dv;
-            rp += (double)(T)fv;
+            // rho is the sum of the stored f; with compensated sums, of the
+            // quotients before FP32 storage rounds them
+            rp += KAHAN ? fv : (double)(T)fv;
         }
         cN = upward ? uN : c.n00;
         cD = upward ? uD : c.d00;
