@@ -193,6 +193,9 @@ template <> struct RT<1> {
 template <int KU> constexpr int recon_cap() { return kWave * (KU + 1); }
 template <int PREC, int KU> constexpr size_t recon_lds() { return 3 * sizeof(typename RT<PREC>::T) * recon_cap<KU>(); }
 
+// Rows of up to this many markers may share one bound of their sums (recon_task).
+template <int PREC> constexpr int kSharedBound = kWave * (PREC ? 20 : 18);
+
 // Descriptors cover exactly one range of markers [first, first+count): lanes
 // past the end read zero and cost no memory traffic.
 template <int PREC> struct Src;
@@ -551,12 +554,16 @@ __device__ __forceinline__ void recon_task(const Geo& g, const typename RT<PREC>
             // marker the f grid is then c times the offset grid, every N sum is
             // c times its D sum, and f = c comes out exactly
             //
-            // A segment whose nonzero |f| all share one binary exponent
-            // or two (a factor below 4, as along x in a smooth distribution)
-            // takes the segment's largest |f| as every run's bound: each run's
-            // own largest |f| is at least the segment's smallest, so its grid is
-            // at most twice as coarse as its own bound would give, and the pass
-            // over the run is saved.  Otherwise each run takes its own bound.
+            // A segment whose nonzero |f| all share one binary exponent (in one of
+            // up to kSharedBound markers, one or two: a factor below 4, as along x in
+            // a smooth distribution) takes the segment's largest |f| as every run's
+            // bound, and the pass over the run is saved.  With one exponent the
+            // run's own bound would give the same grid; with two each run's own
+            // largest |f| is at least the segment's smallest, so its grid is at most
+            // twice as coarse (one of 51 bits).  Otherwise each run takes its own
+            // bound.  The line is a number of markers, not what this kernel stages,
+            // so that every form gives the same bits, and longer rows, which sum the
+            // more terms, keep their own grids.
             unsigned kmax = 0;
             if (!staged) {
 #pragma unroll 8
@@ -567,18 +574,13 @@ __device__ __forceinline__ void recon_task(const Geo& g, const typename RT<PREC>
                 }
             }
             const unsigned gmax = wave_max_u32(smax), gmin = wave_min_u32(smin1) + 1u;
-            const bool narrow = gmax == 0u || fix_exp_of_key(gmax, T()) - fix_exp_of_key(gmin, T()) <= 1;
-            if (narrow) kmax = gmax;
-            if (!narrow) {
-                if (staged) {
-                    for (int u = 0; u < len; ++u) kmax = max(kmax, fix_key(lds.f[p0 + u]));
-                } else {
-                    for (int base = 0; base < tot; base += MAIN) {
-                        int lo, hi;
-                        piece(base, lo, hi);
-                        for (int u = lo; u < hi; ++u) kmax = max(kmax, fix_key(lds.f[u]));
-                    }
-                }
+            const int span = gmax == 0u ? 0 : fix_exp_of_key(gmax, T()) - fix_exp_of_key(gmin, T());
+            if (span <= (seg.fits(kSharedBound<PREC>) ? 1 : 0)) {
+                kmax = gmax;
+            } else if (staged) {
+                for (int u = 0; u < len; ++u) kmax = max(kmax, fix_key(lds.f[p0 + u]));
+            } else {
+                for (int u = 0; u < len; ++u) kmax = max(kmax, fix_key(m.f[beg + u]));
             }
             const int emax = len > 0 ? fix_exp_of_key(kmax, T()) : -1100;
             const FixGrid gf = fix_grid(emax, len), gd = fix_grid(0, len);
