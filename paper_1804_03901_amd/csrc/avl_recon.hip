@@ -79,6 +79,17 @@ struct FixMoments {
         ab = fma(a_, b_, ab);
         abf = fma(ab_, f_, abf);
     }
+    // default rounding: each term is rounded down onto its grid explicitly
+    __device__ void add_floor(const FixGrid& gf, const FixGrid& gd, double a_, double b_, double f_) {
+        const double ab_ = a_ * b_;
+        f += fixsum_floor(gf, f_);
+        a += fixsum_floor(gd, a_);
+        b += fixsum_floor(gd, b_);
+        af += fixsum_floor(gf, a_ * f_);
+        bf += fixsum_floor(gf, b_ * f_);
+        ab += fixsum_floor(gd, ab_);
+        abf += fixsum_floor(gf, ab_ * f_);
+    }
     __device__ void pin() {
         fixsum_pin(f); fixsum_pin(af); fixsum_pin(bf); fixsum_pin(abf);
         fixsum_pin(a); fixsum_pin(b); fixsum_pin(ab);
@@ -192,6 +203,10 @@ template <> struct RT<1> {
 // f in the storage type.
 template <int KU> constexpr int recon_cap() { return kWave * (KU + 1); }
 template <int PREC, int KU> constexpr size_t recon_lds() { return 3 * sizeof(typename RT<PREC>::T) * recon_cap<KU>(); }
+
+// Marker bytes (a, b, f or x, v, f) up to which rows beyond the staging capacity
+// are summed by each lane from memory: somewhat more than the eight 4 MB L2s.
+constexpr long long kLoopBytes = 48ll << 20;
 
 // Rows of up to this many markers may share one bound of their sums (recon_task).
 template <int PREC> constexpr int kSharedBound = kWave * (PREC ? 20 : 18);
@@ -509,12 +524,22 @@ __device__ __forceinline__ void recon_task(const Geo& g, const typename RT<PREC>
         sg[DEPTH] = make_seg(rb[DEPTH], re[DEPTH], first_lane, last_lane, wrapped);
         prefetch<PREC, KU, SPARSE>(m, sg[DEPTH], lane, R, W);
 
-        // A segment beyond the capacity is staged piece by piece, straight from
-        // memory (256 x 256 at 40 markers a cell, every row beyond it: FP64 115 us
-        // with a lane's loop over its run in memory, 82 us in pieces; FP32 86, 76):
-        // piece(base) fills LDS with its positions [base, base + MAIN)
-        // (the wrapped run follows the main range), lo to hi of them the lane's.
+        // A segment beyond the capacity is summed from memory, by a lane's loop
+        // over its run while the markers fit the L2s, else staged piece by piece:
+        // piece(base) fills LDS with its positions [base, base + MAIN) (the wrapped
+        // run follows the main range), lo to hi of them the lane's.  The loops keep
+        // every lane at work but fetch each line many times; in a piece the lanes
+        // whose runs lie elsewhere wait, the more the longer the row.  Loops /
+        // pieces, us: 128 x 128, ppc 64 (1.0M markers): FP64 119 / 147, FP32 62 /
+        // 106; 256 x 300, ppc 36 (2.8M): 97 / 92, 74 / 83; 512 x 300, ppc 32 (4.9M):
+        // 133 / 115, 113 / 83; 512 x 200, ppc 80 (8.2M): 263 / 241, 230 / 196.  The
+        // compensated sums stay with the loops in rows of more than two pieces as
+        // well (1024 x 100, ppc 64, 6.6M: 143 / 171), of more than four beyond
+        // three times those bytes (128 x 2000, ppc 64, 16.4M: 874 / 449; 64 x 2000,
+        // ppc 128, 16.4M: 330 / 431).
         const int tot = seg.nmain + seg.wlen;
+        const long long bytes = (long long)g.n * (3 * sizeof(T));
+        const bool pieces = bytes > kLoopBytes && (!KAHAN || tot <= (bytes > 3 * kLoopBytes ? 4 : 2) * MAIN);
         auto source = [&](int p) { return p < seg.nmain ? seg.lo + p : seg.wbeg + (p - seg.nmain); };
         auto piece = [&](int base, int& lo, int& hi) {
             wave_sync_lds();
@@ -534,6 +559,11 @@ __device__ __forceinline__ void recon_task(const Geo& g, const typename RT<PREC>
                     T a, b, f;
                     lds.get(p0 + u, a, b, f);
                     K.add(a, b, f);
+                }
+            } else if (!pieces) {
+                for (int u = 0; u < len; ++u) {
+                    const Raw r = load_raw<PREC>(m, beg + u);
+                    K.add(r.a, r.b, r.f);
                 }
             } else {
                 for (int base = 0; base < tot; base += MAIN) {
@@ -597,6 +627,28 @@ __device__ __forceinline__ void recon_task(const Geo& g, const typename RT<PREC>
                 M.pin();
                 fixsum_round_nearest();
                 M.pin();
+            } else if (!pieces) {
+                // the FP64 form locates each marker here, in the default rounding
+                if constexpr (PREC == 0) {
+                    for (int u = 0; u < len; ++u) {
+                        const Raw r = load_raw<PREC>(m, beg + u);
+                        int ix, jp[1];
+                        double a, b[1];
+                        const double vv[1] = {r.v};
+                        locate64<1>(g, r.x, vv, ix, jp, a, b);
+                        M.add_floor(gf, gd, a, b[0], r.f);
+                    }
+                } else {
+                    fixsum_round_down();
+                    M.pin();
+                    for (int u = 0; u < len; ++u) {
+                        const Raw r = load_raw<PREC>(m, beg + u);
+                        M.add_rd((double)r.a, (double)r.b, (double)r.f);
+                    }
+                    M.pin();
+                    fixsum_round_nearest();
+                    M.pin();
+                }
             } else {
                 for (int base = 0; base < tot; base += MAIN) {
                     int lo, hi;
