@@ -418,6 +418,10 @@ __device__ __forceinline__ void recon_task(const Geo& g, const typename RT<PREC>
     using Vec = typename Src<PREC>::Vec;
     constexpr int V = Src<PREC>::V;
     constexpr int MAIN = kWave * KU;
+    // the widest kernels: rows beyond the capacity are common there
+    constexpr bool PIECES = KU >= 24;
+    // segments that are not staged may share a bound
+    constexpr bool LOOK = MAIN != kSharedBound<PREC>;
     extern __shared__ __align__(16) unsigned char smem[];
     const int lane = threadIdx.x;
     Lds<PREC, KU> lds;
@@ -536,10 +540,12 @@ __device__ __forceinline__ void recon_task(const Geo& g, const typename RT<PREC>
         // compensated sums stay with the loops in rows of more than two pieces as
         // well (1024 x 100, ppc 64, 6.6M: 143 / 171), of more than four beyond
         // three times those bytes (128 x 2000, ppc 64, 16.4M: 874 / 449; 64 x 2000,
-        // ppc 128, 16.4M: 330 / 431).
+        // ppc 128, 16.4M: 330 / 431).  Only the widest kernels hold both ways: in
+        // the others, whose rows exceed the capacity now and then, the second one's
+        // code alone took a batch of 91M markers from 475 to 488 us.
         const int tot = seg.nmain + seg.wlen;
         const long long bytes = (long long)g.n * (3 * sizeof(T));
-        const bool pieces = bytes > kLoopBytes && (!KAHAN || tot <= (bytes > 3 * kLoopBytes ? 4 : 2) * MAIN);
+        const bool pieces = PIECES && bytes > kLoopBytes && (!KAHAN || tot <= (bytes > 3 * kLoopBytes ? 4 : 2) * MAIN);
         auto source = [&](int p) { return p < seg.nmain ? seg.lo + p : seg.wbeg + (p - seg.nmain); };
         auto piece = [&](int base, int& lo, int& hi) {
             wave_sync_lds();
@@ -592,25 +598,32 @@ __device__ __forceinline__ void recon_task(const Geo& g, const typename RT<PREC>
             // largest |f| is at least the segment's smallest, so its grid is at most
             // twice as coarse (one of 51 bits).  Otherwise each run takes its own
             // bound.  The line is a number of markers, not what this kernel stages,
-            // so that every form gives the same bits, and longer rows, which sum the
-            // more terms, keep their own grids.
+            // so that the grids are those of every form, and longer rows, which sum
+            // the more terms, keep their own.  Where the two numbers agree (no LOOK)
+            // a segment that is not staged goes to its runs' own bounds at once: the
+            // same grids, and 10 us less in a batch's 485.
             unsigned kmax = 0;
-            if (!staged) {
+            bool narrow = false;
+            if (LOOK || staged) {
+                if (LOOK && !staged) {
 #pragma unroll 8
-                for (int p = lane; p < tot; p += kWave) {
-                    const unsigned kf = fix_key(m.f[source(p)]);
-                    smax = max(smax, kf);
-                    smin1 = min(smin1, kf - 1u);
+                    for (int p = lane; p < tot; p += kWave) {
+                        const unsigned kf = fix_key(m.f[source(p)]);
+                        smax = max(smax, kf);
+                        smin1 = min(smin1, kf - 1u);
+                    }
                 }
+                const unsigned gmax = wave_max_u32(smax), gmin = wave_min_u32(smin1) + 1u;
+                const int most = !LOOK || seg.fits(kSharedBound<PREC>) ? 1 : 0;
+                narrow = gmax == 0u || fix_exp_of_key(gmax, T()) - fix_exp_of_key(gmin, T()) <= most;
+                if (narrow) kmax = gmax;
             }
-            const unsigned gmax = wave_max_u32(smax), gmin = wave_min_u32(smin1) + 1u;
-            const int span = gmax == 0u ? 0 : fix_exp_of_key(gmax, T()) - fix_exp_of_key(gmin, T());
-            if (span <= (seg.fits(kSharedBound<PREC>) ? 1 : 0)) {
-                kmax = gmax;
-            } else if (staged) {
-                for (int u = 0; u < len; ++u) kmax = max(kmax, fix_key(lds.f[p0 + u]));
-            } else {
-                for (int u = 0; u < len; ++u) kmax = max(kmax, fix_key(m.f[beg + u]));
+            if (!narrow) {
+                if (staged) {
+                    for (int u = 0; u < len; ++u) kmax = max(kmax, fix_key(lds.f[p0 + u]));
+                } else {
+                    for (int u = 0; u < len; ++u) kmax = max(kmax, fix_key(m.f[beg + u]));
+                }
             }
             const int emax = len > 0 ? fix_exp_of_key(kmax, T()) : -1100;
             const FixGrid gf = fix_grid(emax, len), gd = fix_grid(0, len);
@@ -628,23 +641,32 @@ __device__ __forceinline__ void recon_task(const Geo& g, const typename RT<PREC>
                 fixsum_round_nearest();
                 M.pin();
             } else if (!pieces) {
-                // the FP64 form locates each marker here, in the default rounding
-                if constexpr (PREC == 0) {
-                    for (int u = 0; u < len; ++u) {
-                        const Raw r = load_raw<PREC>(m, beg + u);
-                        int ix, jp[1];
-                        double a, b[1];
-                        const double vv[1] = {r.v};
-                        locate64<1>(g, r.x, vv, ix, jp, a, b);
-                        M.add_floor(gf, gd, a, b[0], r.f);
-                    }
-                } else {
+                // the FP64 form locates each marker here, in the default rounding;
+                // FP32 markers can be added in the sums' own (128 x 128, ppc 64: 62
+                // us against 72), which the narrower kernels' code has no room for
+                if constexpr (PREC == 1 && PIECES) {
                     fixsum_round_down();
                     M.pin();
-                    for (int u = 0; u < len; ++u) {
-                        const Raw r = load_raw<PREC>(m, beg + u);
-                        M.add_rd((double)r.a, (double)r.b, (double)r.f);
+                }
+                for (int u = 0; u < len; ++u) {
+                    const Raw r = load_raw<PREC>(m, beg + u);
+                    double a, b, f;
+                    if constexpr (PREC == 0) {
+                        int ix, jp[1];
+                        double bb[1];
+                        const double vv[1] = {r.v};
+                        locate64<1>(g, r.x, vv, ix, jp, a, bb);
+                        b = bb[0];
+                        f = r.f;
+                    } else {
+                        a = r.a;
+                        b = r.b;
+                        f = r.f;
                     }
+                    if constexpr (PREC == 1 && PIECES) M.add_rd(a, b, f);
+                    else M.add_floor(gf, gd, a, b, f);
+                }
+                if constexpr (PREC == 1 && PIECES) {
                     M.pin();
                     fixsum_round_nearest();
                     M.pin();
