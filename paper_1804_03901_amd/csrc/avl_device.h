@@ -521,13 +521,13 @@ __device__ __forceinline__ void fixsum_round_nearest() { asm volatile("s_setreg_
 // in the default rounding mode; the multiplication by 2^-e is exact).
 __device__ __forceinline__ double fixsum_floor(const FixGrid& gr, double t) { return floor(t * gr.inv_q) * gr.q; }
 
-// Bucket of position p of a sorted FP32 1D-1V order of n markers: the largest b
-// with off[b] <= p, between the buckets tfirst holds for the neighbouring
-// positions that are multiples of kTfStride (at most nb, the overflow run).
-__device__ __forceinline__ int run_at(const int* __restrict__ off, const int* __restrict__ tfirst, int nb, int n, int p)
+// Bucket of position p < sorted of a sorted FP32 1D-1V order, sorted the start of
+// its overflow run: the largest b with off[b] <= p, between the buckets tfirst
+// holds for the neighbouring positions that are multiples of kTfStride.
+__device__ __forceinline__ int run_at(const int* __restrict__ off, const int* __restrict__ tfirst, int nb, int sorted, int p)
 {
     const int t = p >> kTfLog;
-    int lo = tfirst[t], hi = ((t + 1) << kTfLog) < n ? tfirst[t + 1] : nb;
+    int lo = tfirst[t], hi = ((t + 1) << kTfLog) < sorted ? tfirst[t + 1] : nb;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
         if (off[mid] <= p) lo = mid;

@@ -518,7 +518,7 @@ __global__ __launch_bounds__(256) void k_to64(Geo g, M32 m, double* __restrict__
         const int i = (int)u;
         const int o = id ? id[i] : i;
         const float ma = m.a[i], mb = m.b[i];      // under way before the search for the cell
-        const int cell = i < sorted ? run_at(off, tfirst, g.nb, g.n, i) : m.cell[i];
+        const int cell = i < sorted ? run_at(off, tfirst, g.nb, sorted, i) : m.cell[i];
         const int ix = cell & (g.nx - 1);
         const int r = cell >> g.lognx;
         int jp[3];

@@ -1325,8 +1325,10 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_total(const int* __restri
 
 // Offsets of one tile of kScanTile buckets: the tile's start plus an in-block
 // exclusive scan of its counts, four per thread, both reduced behind one
-// barrier.  Also (tfirst non-null) records for every position p = t kTfStride
-// of the new order the bucket whose run holds it: tfirst[t].
+// barrier.  Also (tfirst non-null: FP32 1D-1V) records for every position
+// p = t kTfStride of the new order, up to the overflow run, the bucket whose run
+// holds it: tfirst[t].  (16.8M markers, a third of them in the overflow run: the
+// one lane that recorded it took 566 us.)
 __device__ __forceinline__ void scan_tile(const int* __restrict__ counts, int nbt, const int* __restrict__ tsum,
                                           int from, int* __restrict__ offsets, int tile, int* __restrict__ tfirst)
 {
@@ -1371,10 +1373,20 @@ __device__ __forceinline__ void scan_tile(const int* __restrict__ counts, int nb
         run += c[k];
     }
     if (tfirst) {
+        // the entries inside each run; a wave shares those of a long one
 #pragma unroll
-        for (int k = 0; k < kScanItems; ++k)
-            for (int t = (o[k] + kTfStride - 1) >> kTfLog; c[k] > 0 && t <= (o[k] + c[k] - 1) >> kTfLog; ++t)
-                tfirst[t] = (int)(base + k);
+        for (int k = 0; k < kScanItems; ++k) {
+            const bool some = c[k] > 0 && base + k + 1 < end;       // not the overflow run
+            const int t0 = (o[k] + kTfStride - 1) >> kTfLog, t1 = some ? (o[k] + c[k] - 1) >> kTfLog : -1;
+            const bool big = t1 - t0 >= 8;
+            if (!big)
+                for (int t = t0; t <= t1; ++t) tfirst[t] = (int)(base + k);
+            for (unsigned long long rest = __ballot(big); rest; rest &= rest - 1) {
+                const int l = __builtin_ctzll(rest), last = __builtin_amdgcn_readlane(t1, l);
+                const int b = __builtin_amdgcn_readlane((int)(base + k), l);
+                for (int t = __builtin_amdgcn_readlane(t0, l) + lane; t <= last; t += kWave) tfirst[t] = b;
+            }
+        }
     }
     if (base + kScanItems <= end) {
         *reinterpret_cast<int4*>(offsets + base) = make_int4(o[0], o[1], o[2], o[3]);
@@ -1574,16 +1586,16 @@ static hipError_t launch_sort_t(const Geo& g, void* src, void* dst, const double
 // phase 0 = count, 1 = scan, 2 = scatter.  offsets: the run offsets of the new
 // order (written by the scan, used by the scatter); off_old / tf_old: the
 // order the markers are in, for implied cells (FP32 1D-1V; nullptr when every
-// cell index is stored); tf_new (may be null): the scan's record of the new
+// cell index is stored); tf_new (FP32 1D-1V, may be null): the scan's record of the new
 // order's tile starts.
 hipError_t launch_sort(const Geo& g, void* src, void* dst, const double* E, const RowShift* rows,
                        double dtk, float bk, int* counts, int* offsets, int* tile_sums, int* flags,
                        bool push, hipStream_t st, int phase, const int* off_old, const int* tf_old, int* tf_new)
 {
-    if (g.prec == 0 && g.vdim == 1) return launch_sort_t<0, 1>(g, src, dst, E, rows, dtk, bk, counts, offsets, tile_sums, flags, push, st, phase, nullptr, nullptr, tf_new);
-    if (g.prec == 0 && g.vdim == 3) return launch_sort_t<0, 3>(g, src, dst, E, rows, dtk, bk, counts, offsets, tile_sums, flags, push, st, phase, nullptr, nullptr, tf_new);
+    if (g.prec == 0 && g.vdim == 1) return launch_sort_t<0, 1>(g, src, dst, E, rows, dtk, bk, counts, offsets, tile_sums, flags, push, st, phase, nullptr, nullptr, nullptr);
+    if (g.prec == 0 && g.vdim == 3) return launch_sort_t<0, 3>(g, src, dst, E, rows, dtk, bk, counts, offsets, tile_sums, flags, push, st, phase, nullptr, nullptr, nullptr);
     if (g.prec == 1 && g.vdim == 1) return launch_sort_t<1, 1>(g, src, dst, E, rows, dtk, bk, counts, offsets, tile_sums, flags, push, st, phase, off_old, tf_old, tf_new);
-    return launch_sort_t<1, 3>(g, src, dst, E, rows, dtk, bk, counts, offsets, tile_sums, flags, push, st, phase, nullptr, nullptr, tf_new);
+    return launch_sort_t<1, 3>(g, src, dst, E, rows, dtk, bk, counts, offsets, tile_sums, flags, push, st, phase, nullptr, nullptr, nullptr);
 }
 
 // ---------------------------------------------------------------------------
@@ -1622,7 +1634,8 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_b(const BInst* __restrict
     const int* pr = pre + BPRE_SCAN * (ninst + 1);
     const int i = find_inst(pr, ninst, blockIdx.x);
     const BInst& I = tab[i];
-    scan_tile(I.counts, I.g.nb + 1, I.tsum, SCAN_TOTALS, I.offsets[1 - cur], blockIdx.x - pr[i], I.tfirst[1 - cur]);
+    scan_tile(I.counts, I.g.nb + 1, I.tsum, SCAN_TOTALS, I.offsets[1 - cur], blockIdx.x - pr[i],
+              I.g.prec ? I.tfirst[1 - cur] : nullptr);
 }
 
 // Batch instances carry no marker identities.

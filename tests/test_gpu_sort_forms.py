@@ -67,3 +67,48 @@ def test_field_that_weakens_and_grows_after_loading(nx, nv, ppc, precision):
         sim.step(1, graph=graph)
         _check(sim, w, precision)
     sim.close()
+
+
+def _crowded(w, n, beyond, seed):
+    """n markers: most in three cells, some anywhere, a share `beyond` off the velocity grid."""
+    rng = np.random.default_rng(seed)
+    x, v = rng.random(n) * w.L, w.vmin[0] + (w.vmax[0] - w.vmin[0]) * rng.random(n)
+    crowd = rng.random(n) < 0.8
+    cell = rng.integers(0, 3, n)
+    x[crowd] = ((cell * (w.nx // 3) + rng.random(n)) * w.dx)[crowd]
+    v[crowd] = (w.vmin[0] + (cell + 2 + rng.random(n)) * w.dv(0))[crowd]
+    off = rng.random(n) < beyond
+    v[off] = (w.vmax[0] + (1.0 + rng.random(n)) * (w.vmax[0] - w.vmin[0]))[off]
+    return x, v, 0.1 + rng.random(n)
+
+
+@pytest.mark.parametrize("nx,nv,n,beyond", [(32, 8, 40000, 0.0), (256, 64, 300001, 0.34), (64, 40, 70000, 0.97),
+                                            (128, 30, 2047, 1.0)])
+def test_runs_that_span_many_tiles(nx, nv, n, beyond):
+    # the FP32 sort records where its tiles start in the runs of the order before:
+    # runs of thousands of markers, and an overflow run of up to all of them
+    w = inputs.bump_on_tail(nx=nx, nv=nv, ppc=1, seed=61).replace(dt=1e-3)
+    sim = _sim(w, _crowded(w, n, beyond, n), avl.AVL_FP32)
+    for graph in (False, True, False):
+        sim.step(1, graph=graph)
+        sim.sort()
+        _check(sim, w, avl.AVL_FP32)
+    sim.close()
+
+
+@pytest.mark.parametrize("precision", [avl.AVL_FP64, avl.AVL_FP32])
+@pytest.mark.parametrize("nx,nv", [(256, 382), (256, 383), (512, 8190), (512, 8191)])
+def test_scan_changes_form(nx, nv, precision):
+    # 24 and 25 scan tiles of 4096 buckets (the totals get a launch of their own),
+    # 1024 and 1025 (and a scan of their own)
+    tiles = (nx * (nv + 1) + 1 + 4095) // 4096
+    assert tiles in (24, 25, 1024, 1025)
+    w = inputs.bump_on_tail(nx=nx, nv=nv, ppc=1, seed=62)
+    rng = np.random.default_rng(nv)
+    n = 150001
+    v = w.vmin[0] + (w.vmax[0] - w.vmin[0]) * rng.random(n)
+    sim = _sim(w, (rng.random(n) * w.L, v, 0.1 + rng.random(n)), precision)
+    for graph in (False, True):
+        sim.step(2, graph=graph)
+        _check(sim, w, precision)
+    sim.close()
