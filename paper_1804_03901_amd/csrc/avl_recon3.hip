@@ -134,7 +134,10 @@ struct Seg3 {
     int lo, nmain, wbeg, wlen;
 };
 
-template <int PREC>
+// RING: a grid of up to 64 columns is one strip without a halo: lane l owns run
+// and target column l.  (Decided at run time in one kernel it took the wider
+// grids of 512 x 64^3 FP32 from 8.97 to 9.2 ms.)
+template <int PREC, bool RING>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(R3<PREC>::WAVES)))
 void k_recon_3v(Geo g, typename R3<PREC>::M m, const int* __restrict__ offsets, typename R3<PREC>::T* __restrict__ fgrid,
                 typename R3<PREC>::T* __restrict__ Dgrid, double* __restrict__ rho_part, int tasks_per_xcd)
@@ -161,9 +164,7 @@ void k_recon_3v(Geo g, typename R3<PREC>::M m, const int* __restrict__ offsets, 
     const int nx = g.nx, nvx = g.nv[0];
     // target vx rows [j_lo, j_hi) of the chunk, from dual rows r = jd + 1 = j_lo .. j_hi
     const int j_lo = chunk * g.rc, j_hi = min(j_lo + g.rc, nvx);
-    // a grid of up to 64 columns is one strip without a halo: lane l owns run
-    // and target column l
-    const bool ring = nx <= kWave;
+    constexpr bool ring = RING;
     const int col = ring ? lane : strip * kReconCols - 1 + lane;
     const bool run_ok = col < nx;
     const int colw = col < 0 ? nx - 1 : col;
@@ -175,7 +176,7 @@ void k_recon_3v(Geo g, typename R3<PREC>::M m, const int* __restrict__ offsets, 
     const int rowsy = g.nv[1] + 1, rowsx = nvx + 1;
     auto left = [&](double v) {
         double l = from_left3(v);
-        if (ring) {
+        if constexpr (ring) {
             const long long b = __double_as_longlong(v);
             const double e = __hiloint2double(__builtin_amdgcn_readlane((int)(b >> 32), nx - 1),
                                               __builtin_amdgcn_readlane((int)b, nx - 1));
@@ -404,7 +405,7 @@ size_t recon3_scratch_bytes(const Geo&) { return 0; }
 // (without a device, the register budget's).
 int recon3_waves_per_cu(int prec)
 {
-    const void* fn = prec ? (const void*)k_recon_3v<1> : (const void*)k_recon_3v<0>;
+    const void* fn = prec ? (const void*)k_recon_3v<1, false> : (const void*)k_recon_3v<0, false>;
     int per_cu = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kWave, 0) != hipSuccess || per_cu <= 0) {
         (void)hipGetLastError();
@@ -419,12 +420,13 @@ hipError_t launch_recon3(const Geo& g, void* m, const int* offsets, void* fgrid,
     const int tasks = g.nstrip * g.vchunk * ((g.nv[1] + 1) / 2) * ((g.nv[2] + 1) / 2);
     const int per_xcd = (tasks + 7) / 8;
     const int blocks = per_xcd * 8;
+    const bool ring = g.nx <= kWave;
     if (g.prec == 0)
-        launch(k_recon_3v<0>, dim3(blocks), dim3(kWave), 0, st, g, *reinterpret_cast<M64*>(m), offsets,
-                           (double*)fgrid, (double*)Dgrid, rho_part, per_xcd);
+        launch(ring ? k_recon_3v<0, true> : k_recon_3v<0, false>, dim3(blocks), dim3(kWave), 0, st, g,
+               *reinterpret_cast<M64*>(m), offsets, (double*)fgrid, (double*)Dgrid, rho_part, per_xcd);
     else
-        launch(k_recon_3v<1>, dim3(blocks), dim3(kWave), 0, st, g, *reinterpret_cast<M32*>(m), offsets,
-                           (float*)fgrid, (float*)Dgrid, rho_part, per_xcd);
+        launch(ring ? k_recon_3v<1, true> : k_recon_3v<1, false>, dim3(blocks), dim3(kWave), 0, st, g,
+               *reinterpret_cast<M32*>(m), offsets, (float*)fgrid, (float*)Dgrid, rho_part, per_xcd);
     return hipGetLastError();
 }
 
