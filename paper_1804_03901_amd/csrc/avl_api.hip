@@ -281,14 +281,17 @@ int make_geo(const avl_config* c, Geo* g)
         // the GPU holds waves is cut until it has one task a wave (64 x 24^3
         // FP64: 736 us whole, 112 us in chunks of two rows); a larger one into
         // five tasks a wave, in chunks of 16 rows or more, so that the last
-        // round of waves is a small part (256 x 64^3 FP32: 6.00 ms whole,
-        // 5.93, 5.48 and 5.52 ms in 2, 3 and 4 chunks)
+        // round of waves is a small part (256 x 64^3 FP32: 5.89 ms whole,
+        // 5.85, 5.30 and 5.36 ms in 2, 3 and 4 chunks), unless its blocks fill
+        // all rounds to 7/8 or more (128 x 64^3 FP32, one round: 3.13 ms whole,
+        // 3.17 in 4 chunks; 512 x 64^3, three, and 256 x 48^3, 0.94 of one: even)
         g->nstrip = c->nx <= kWave ? 1 : (c->nx + kReconCols - 1) / kReconCols;
         const int64_t blocks = (int64_t)g->nstrip * ((c->nv[1] + 1) / 2) * ((c->nv[2] + 1) / 2);
         const int64_t slots = (int64_t)recon3_waves_per_cu(c->precision == AVL_FP32 ? 1 : 0) * device_cus();
         const int64_t one = std::min<int64_t>((c->nv[0] + 1) / 2, slots / blocks);
         const int64_t five = std::min<int64_t>(c->nv[0] / 16, (5 * slots + blocks - 1) / blocks);
-        g->vchunk = (int)std::max<int64_t>(1, std::max(one, five));
+        const bool full = 8 * blocks >= 7 * slots * ((blocks + slots - 1) / slots);
+        g->vchunk = full ? 1 : (int)std::max<int64_t>(1, std::max(one, five));
         g->rc = (c->nv[0] + g->vchunk - 1) / g->vchunk;
         g->vchunk = (c->nv[0] + g->rc - 1) / g->rc;
         g->nchunk = c->nv[1] * c->nv[2] * g->vchunk;
