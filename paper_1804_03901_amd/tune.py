@@ -33,7 +33,7 @@ from . import avl, inputs
 DEFAULT_CANDIDATES = (0, 4, 6, 8, 10, 12, 16, 24)
 FORM_CANDIDATES = (0, 1, 2)
 SORT_BLOCK_CANDIDATES = (0, 2, 3, 4)
-CACHE_VERSION = "v2"
+CACHE_VERSION = "v3"      # the kernels that picks were timed on
 CACHE_PATH = os.path.join(os.path.expanduser("~"), ".cache", "avl", "tune.json")
 
 
