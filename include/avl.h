@@ -118,11 +118,15 @@ typedef struct avl_config {
                             [0] target velocity rows per 1D-1V reconstruction task, 1..256;
                             [1] row form of the FP32 1D-1V reconstruction: 1 dense rows (every
                                 register load issued), 2 sparse rows (loads past a row segment
-                                skipped); the default takes sparse rows when a segment averages
-                                below 0.6 of the register capacity; ignored by other forms;
-                            [2] resident blocks per compute unit of the 1D-1V count and
-                                scatter passes (four waves a block), 1..64 (at most what fits; the default is
-                                what fits);
+                                skipped), both with 20 markers a lane; the default takes sparse
+                                rows when a segment averages below 0.6 of that, and a dense form
+                                of 28 a lane when it averages above it; ignored by other forms;
+                            [2] resident blocks per compute unit of the 1D-1V wave count and
+                                scatter passes (four waves a block), 1..64 (at most what fits;
+                                the default is what fits); ignored by the FP64 passes that give
+                                a block each tile (steps of a state loaded with kicks of a
+                                velocity cell or more, and the scatter of 2^23 markers or more
+                                at 8 or more a cell on up to 1024 columns);
                             [3] reserved, must be 0 */
     double B[3];         /* uniform background magnetic field (1D-3V, AVL_FP64 only; all zero
                             otherwise): the acceleration is (q/m)(E + v x B), E along x, and

@@ -776,9 +776,9 @@ int avl_init(const avl_config* cfg, void* workspace, size_t ws_bytes, void* stre
         sort_launch_shapes(h->g);
         if (debug_on())
             std::fprintf(stderr,
-                         "[avl] lds limit %d B, recon cap %d, hist bins %d, rc %d, chunks %d, strips %d, "
+                         "[avl] lds limit %d B, recon cap %d, hist bins %d, wave bins %d, rc %d, chunks %d, strips %d, "
                          "recon waves per CU %d\n",
-                         lds, h->g.cap, h->g.prec ? h->g.wbins : h->g.hist_bins, h->g.rc, h->g.nchunk, h->g.nstrip,
+                         lds, h->g.cap, h->g.hist_bins, h->g.wbins, h->g.rc, h->g.nchunk, h->g.nstrip,
                          h->g.vdim == 1 ? recon_waves_per_cu(h->g, device_lds_per_cu()) : 0);
     }
     if (hipMemsetAsync(h->flags, 0, sizeof(int), h->st) != hipSuccess || (rc = upload_tables(h)) != AVL_OK) {

@@ -811,9 +811,9 @@ int recon_form(const Geo& g)
     const double per_row = g.nb > 0 ? (double)g.n / (double)g.nb * std::min(g.nx, kWave) : 1e30;
     const double full = per_row + 4.0 * std::sqrt(per_row);
     if (g.prec != 1) return per_row <= 0.75 * kWave * 6 ? (g.n < 1 << 23 ? F64_6 : F64_6D) : per_row <= 0.75 * kWave * 12 ? F64_12 : full <= kWave * 18 ? F64_18 : F64_24;
+    if (g.rform) return g.rform == 2 ? F32_20S : F32_20;      // the caller's choice
     if (full > kWave * 20) return F32_28;
-    if (g.rform == 1) return F32_20;
-    return g.rform == 2 || per_row <= 0.6 * kWave * 20 ? F32_20S : F32_20;
+    return per_row <= 0.6 * kWave * 20 ? F32_20S : F32_20;
 }
 
 // fn(PREC, KU, DEPTH, SPARSE) of a form, as integral constants
