@@ -1425,7 +1425,7 @@ static size_t sort_smem(const Geo& g)
 // count 8.3 / 9.5, 16.7 / 17.2, 27.1 / 27.5, 55.8 / 53.4.  The FP64 scatter
 // has registers for four only.
 static int count_mpl(const Geo& g) { return g.n < (g.prec ? 5 << 20 : 12 << 20) ? 4 : 8; }
-static int scatter_mpl(const Geo& g) { return g.prec == 0 || g.n < 10 << 20 ? 4 : 8; }
+static int scatter_mpl(const Geo& g) { return g.n < 10 << 20 ? 4 : 8; }          // FP32
 
 // The FP64 scatter of large, dense sorts goes by blocks of 2048 markers instead:
 // tiles of 256 span 32 columns or fewer at 8 markers a cell, and the bins at
@@ -1512,24 +1512,25 @@ static hipError_t launch_sort_1v(const Geo& g, const typename MarkersOf<PREC>::T
         }
         return hipGetLastError();
     }
-    constexpr int KB = PREC ? 8 : 4;
-    using K = decltype(&k_scatter_w<PREC, KB, true, F, true>);
-    static const K fns[16] = {
-        k_scatter_w<PREC, KB, false, false, false>, k_scatter_w<PREC, KB, false, false, true>,
-        k_scatter_w<PREC, KB, false, F, false>,     k_scatter_w<PREC, KB, false, F, true>,
-        k_scatter_w<PREC, KB, true, false, false>,  k_scatter_w<PREC, KB, true, false, true>,
-        k_scatter_w<PREC, KB, true, F, false>,      k_scatter_w<PREC, KB, true, F, true>,
-        k_scatter_w<PREC, 4, false, false, false>,  k_scatter_w<PREC, 4, false, false, true>,
-        k_scatter_w<PREC, 4, false, F, false>,      k_scatter_w<PREC, 4, false, F, true>,
-        k_scatter_w<PREC, 4, true, false, false>,   k_scatter_w<PREC, 4, true, false, true>,
-        k_scatter_w<PREC, 4, true, F, false>,       k_scatter_w<PREC, 4, true, F, true>};
-    static int granted[16] = {};
-    const int mpl = scatter_mpl(g), v = (mpl == 4 ? 8 : 0) + 4 * (push ? 1 : 0) + 2 * (impl ? 1 : 0) + (s.id ? 1 : 0);
-    hipError_t e = ensure_lds((const void*)fns[v], smem, granted[v]);
-    if (e != hipSuccess) return e;
-    launch(fns[v], grid(mpl, s.id ? g.sblocks : g.sblocks_step), bl, smem, st, g, s, d, E, rows, dtk, bk,
-           (const int*)offsets, counts, flags, pv);
-    return hipGetLastError();
+    const auto scatter = [&](auto lanes) {
+        constexpr int K = decltype(lanes)::value;
+        using Fn = decltype(&k_scatter_w<PREC, K, true, F, true>);
+        static const Fn fns[8] = {
+            k_scatter_w<PREC, K, false, false, false>, k_scatter_w<PREC, K, false, false, true>,
+            k_scatter_w<PREC, K, false, F, false>,     k_scatter_w<PREC, K, false, F, true>,
+            k_scatter_w<PREC, K, true, false, false>,  k_scatter_w<PREC, K, true, false, true>,
+            k_scatter_w<PREC, K, true, F, false>,      k_scatter_w<PREC, K, true, F, true>};
+        static int granted[8] = {};
+        const int v = 4 * (push ? 1 : 0) + 2 * (impl ? 1 : 0) + (s.id ? 1 : 0);
+        hipError_t e = ensure_lds((const void*)fns[v], smem, granted[v]);
+        if (e != hipSuccess) return e;
+        launch(fns[v], grid(K, s.id ? g.sblocks : g.sblocks_step), bl, smem, st, g, s, d, E, rows, dtk, bk,
+               (const int*)offsets, counts, flags, pv);
+        return hipGetLastError();
+    };
+    if constexpr (PREC == 1)
+        if (scatter_mpl(g) == 8) return scatter(std::integral_constant<int, 8>());
+    return scatter(std::integral_constant<int, 4>());
 }
 
 template <int PREC, int VD>
