@@ -129,12 +129,15 @@ __device__ __forceinline__ void vload(const T* __restrict__ src, T* out)
 
 // A thread's group of K consecutive markers [first, first+K), all loads issued
 // together.  Past the last marker, indices are clamped (values masked later).
+// `first` is unsigned where it may pass 2^31 (1D-3V); int addresses are cheaper
+// (FP64 count of 16.8M markers on the wave kernels: 53.2 us against 53.8).
 template <int PREC, int VD, int K> struct Group;
 
 template <int VD, int K> struct Group<0, VD, K> {
     Pay<0, VD> p[K];
-    __device__ void load(const M64& m, const Geo& g, unsigned first, int last, bool with_f, int = VD, int = -1) {
-        if (first + K - 1 <= (unsigned)last) {
+    template <class I>
+    __device__ void load(const M64& m, const Geo& g, I first, int last, bool with_f, int = VD, int = -1) {
+        if (first + K - 1 <= (I)last) {
             double t[K];
             vload<double, K>(m.x + first, t);
 #pragma unroll
@@ -152,7 +155,7 @@ template <int VD, int K> struct Group<0, VD, K> {
             }
         } else {
 #pragma unroll
-            for (int k = 0; k < K; ++k) p[k].load(m, g, (int)min(first + k, (unsigned)last), with_f);
+            for (int k = 0; k < K; ++k) p[k].load(m, g, (int)min(first + (I)k, (I)last), with_f);
         }
     }
 };
@@ -163,8 +166,9 @@ template <int VD, int K> struct Group<1, VD, K> {
     // needs the cell index, a and the x-velocity offset only).  ovf >= 0:
     // implied cells, read from memory only at positions >= ovf (the
     // overflow run of the previous order); the rest are filled in later.
-    __device__ void load(const M32& m, const Geo& g, unsigned first, int last, bool with_f, int nvel = VD, int ovf = -1) {
-        if (first + K - 1 <= (unsigned)last) {
+    template <class I>
+    __device__ void load(const M32& m, const Geo& g, I first, int last, bool with_f, int nvel = VD, int ovf = -1) {
+        if (first + K - 1 <= (I)last) {
             int ti[K];
             float t[K];
             if (ovf < 0) {
@@ -174,10 +178,10 @@ template <int VD, int K> struct Group<1, VD, K> {
             } else {
 #pragma unroll
                 for (int k = 0; k < K; ++k) p[k].cell = 0;
-                if (first + K - 1 >= (unsigned)ovf) {
+                if (first + K - 1 >= (I)ovf) {
 #pragma unroll
                     for (int k = 0; k < K; ++k)
-                        if (first + k >= (unsigned)ovf) p[k].cell = m.cell[first + k];
+                        if (first + k >= (I)ovf) p[k].cell = m.cell[first + k];
                 }
             }
             vload<float, K>(m.a + first, t);
@@ -202,7 +206,7 @@ template <int VD, int K> struct Group<1, VD, K> {
         } else {
 #pragma unroll
             for (int k = 0; k < K; ++k) {
-                const int i = (int)min(first + k, (unsigned)last);
+                const int i = (int)min(first + (I)k, (I)last);
                 p[k].load(m, g, i, with_f, nvel, ovf < 0 || i >= ovf);
             }
         }
