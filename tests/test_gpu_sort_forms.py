@@ -112,3 +112,36 @@ def test_scan_changes_form(nx, nv, precision):
         sim.step(2, graph=graph)
         _check(sim, w, precision)
     sim.close()
+
+
+@pytest.mark.parametrize("precision,nx,nv,ppc", [
+    (avl.AVL_FP32, 1024, 512, 10),      # 5 * 2^20 markers: eight a lane in the count
+    (avl.AVL_FP32, 1024, 1024, 10),     # 10 * 2^20: and in the scatter
+    (avl.AVL_FP64, 1024, 911, 9),       # 2^23 dense markers: the scatter by blocks
+    (avl.AVL_FP64, 2048, 512, 9),       # wider grids stay with the waves
+    (avl.AVL_FP64, 1024, 1024, 12),     # 12 * 2^20: eight a lane in the count
+])
+def test_large_sorts(precision, nx, nv, ppc):
+    w = inputs.bump_on_tail(nx=nx, nv=nv, ppc=ppc, seed=63)
+    sim = _sim(w, inputs.markers_threaded(w), precision)
+    sim.step(1)
+    sim.step(2, graph=True)
+    _check(sim, w, precision)
+    sim.close()
+
+
+@pytest.mark.parametrize("precision,nv,ppc", [(avl.AVL_FP32, 1024, 10), (avl.AVL_FP64, 911, 9)])
+def test_large_sorts_carry_identities(precision, nv, ppc):
+    # the gradient is a function of the marker multiset: loaded in another order it
+    # is the same bit for bit, marker by marker, only if each keeps its identity
+    from paper_1804_03901_amd import adjoint
+    w = inputs.bump_on_tail(nx=1024, nv=nv, ppc=ppc, seed=64)
+    x, v, f = inputs.markers_threaded(w)
+    v = v.reshape(-1)
+    order = np.random.default_rng(1).permutation(x.size)
+    sim = _sim(w, (x, v, f), precision)
+    J, grad = adjoint.energy_and_gradient(sim, x, v, f, 2, 2)
+    Jp, gradp = adjoint.energy_and_gradient(sim, x[order], v[order], f[order], 2, 2)
+    sim.close()
+    assert float(J) == float(Jp)
+    assert torch.equal(grad[torch.as_tensor(order, device=grad.device)], gradp)
