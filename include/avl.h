@@ -309,9 +309,9 @@ int avl_destroy(avl_handle* h);
 
 /* ---------------------------------------------------------------------------
  * Batches: many independent 1D-1V instances (a parameter scan) stepped
- * together.  Each step of the batch is six launches that cover every
- * instance (count, scan, scatter, reconstruction, rho, field solve), replayed
- * as a HIP graph; each launch holds a work list of (instance, block or task)
+ * together.  Each step of the batch is seven launches that cover every
+ * instance (count, scan in two, scatter, reconstruction, rho, field solve),
+ * replayed as a HIP graph; each launch holds a work list of (instance, block or task)
  * items, so uneven instances share the GPU without one launch per instance.
  * The method per instance is exactly the single-handle step above.
  * ------------------------------------------------------------------------- */

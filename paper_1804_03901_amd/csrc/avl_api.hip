@@ -254,7 +254,8 @@ int make_geo(const avl_config* c, Geo* g)
         g->nstrip = c->nx <= kWave ? 1 : (c->nx + kReconCols - 1) / kReconCols;
         // In the FP32 form the chunks group rho's partial sums, whose last bit
         // decides how a kicked marker rounds: they are those of the dense form's
-        // two waves a SIMD and of 63-column strips, whatever kernel runs
+        // two waves a SIMD and of 63-column strips, whatever kernel runs (28
+        // markers a lane admit seven waves a compute unit)
         const bool fp32 = c->precision == AVL_FP32;
         const int64_t slots = (fp32 ? 8 : (int64_t)recon_waves_per_cu(*g, device_lds_per_cu())) * device_cus();
         const int64_t strips = fp32 ? (c->nx + kReconCols - 1) / kReconCols : g->nstrip;
@@ -1170,7 +1171,7 @@ void drop_batch_graphs(avl_batch* b)
     b->graph_ok = false;
 }
 
-// One step of every instance: six batched launches on `st`, from buffer parity cur.
+// One step of every instance: seven batched launches on `st`, from buffer parity cur.
 int batch_launch(avl_batch* b, int cur, hipStream_t st)
 {
     AVL_TRY(launch_sort_batch(b->prec, b->tab, b->pre, b->n, b->tot[BPRE_COUNT], b->lds, cur, st, 0));
@@ -1259,10 +1260,12 @@ int avl_batch_init(const avl_config* cfgs, int32_t count, void* workspace, size_
     b->lds = 0;
     // Reconstruction chunks of a batch: an instance's own rule cuts its rows
     // until they alone fill the GPU, and every chunk walks one dual row more
-    // than it has; together FP64 instances need no more than two tasks a wave.
-    // FP32 instances keep their own chunks (64 of them, 91M markers, ppc 8: 473
-    // us, 312 at two tasks a wave), for the grouping of rho: its last bit moves
-    // FP32 markers, and E by 1e-8 in five steps.
+    // than it has; together FP64 instances need no more than two tasks a wave
+    // (a step of 64 instances with 46, 91 and 182M markers: 1409, 2236 and 4328 us
+    // in their own chunks, 1380, 2133 and 3975 in the batch's; even for 2 and 8).
+    // FP32 instances keep their own chunks (64 of them, 91M markers: 475 us a
+    // reconstruction, 312 at two tasks a wave), for the grouping of rho: its last
+    // bit moves FP32 markers, and E by 1e-8 in five steps.
     int64_t strip_rows = 0, waves = 0;
     for (const avl_handle* h : b->h) {
         strip_rows += (int64_t)h->g.nstrip * h->g.nv[0];

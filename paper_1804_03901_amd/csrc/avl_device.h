@@ -158,7 +158,7 @@ struct BInst {
     const RowShift* rows;
     int* counts;
     int* offsets[2];           // run offsets of the order of marker buffer p
-    int* tfirst[2];            // bucket of every 2048th position of that order (implied FP32 cells)
+    int* tfirst[2];            // bucket of every kTfStride-th position of that order (implied FP32 cells)
     int* tsum;                 // per-scan-tile totals
     void* fgrid;
     double* rho_part;

@@ -5,17 +5,18 @@
 // are contiguous.  A run (i, j) contributes to the four grid cells
 // (i, j), (i+1, j), (i, j+1), (i+1, j+1) with weights (1-a)(1-b), a(1-b),
 // (1-a)b, ab.  One wavefront owns a strip of 63 target columns and a chunk of
-// target rows; lane l owns run column strip*63 - 1 + l.  The wave walks the
-// dual rows of its chunk, upwards for even chunks and downwards for odd ones,
-// so that the dual row two neighbouring chunks share is read by both at about
-// the same time and the second read hits L2.  For each row it stages the row
-// segment's markers (one contiguous range of the sorted arrays, plus the
-// wrapped run at x = L for the first strip) into LDS with coalesced loads and
-// 16-byte LDS stores, then every lane sums its own run into four (N, D)
-// corner partials.  Staging is software-pipelined: the next two rows'
-// markers are loaded into registers while the current row is summed.  Row
-// segments larger than the LDS capacity are summed straight from global
-// memory (same order, slower).  Tasks are dealt to blocks so that each XCD
+// target rows; lane l owns run column strip*63 - 1 + l (a grid of up to 64
+// columns is one strip without a halo: lane l owns run and target column l).
+// The wave walks the dual rows of its chunk, upwards for even chunks and
+// downwards for odd ones, so that the dual row two neighbouring chunks share is
+// read by both at about the same time and the second read hits L2.  For each
+// row it stages the row segment's markers (one contiguous range of the sorted
+// arrays, plus the wrapped run at x = L for the first strip) into LDS with
+// coalesced loads and 16-byte LDS stores, then every lane sums its own run into
+// four (N, D) corner partials.  Staging is software-pipelined: the next row's
+// markers, or the next two rows', are loaded into registers while the current
+// row is summed.  Row segments larger than a wave stages are summed from memory
+// or staged in pieces (recon_task).  Tasks are dealt to blocks so that each XCD
 // gets consecutive chunks of the same strip.  Target cell (i, j) is then
 //   ((up01(i, j-1) + up11(i-1, j-1)) + S00(i, j)) + S10(i-1, j)
 // in both walk directions, where the (i-1) terms come from the neighbouring
