@@ -790,7 +790,8 @@ __global__ __launch_bounds__(kWave) void k_recon_b(const BInst* __restrict__ tab
 // Which kernel a grid takes, by the markers of an average strip row.  A
 // capacity leaves a smooth placement's rows room: up to 75% of it on average
 // for the small ones, four standard deviations of a random placement's below
-// it for the large.  A segment beyond it is staged in pieces.  Smaller staging
+// it for the large.  A segment beyond it is summed from memory or staged in pieces
+// (recon_task).  Smaller staging
 // buffers and fewer registers mean more waves a compute unit, which is what
 // hides the loads of rows this short (before: 18 a lane in FP64, 20 in FP32 for
 // every grid).  Reconstruction times, us:

@@ -11,13 +11,13 @@
 // One wave owns a strip of 63 target x columns (a grid of up to 64 columns is
 // one strip, whose last lane is the first one's left neighbour), a chunk of vx
 // rows, and a 2x2 block of target (vy, vz) planes; the block draws on a 3x3
-// block of dual planes.  For every dual vx row the wave walks the nine dual-plane row segments; each
-// is loaded from memory once into registers (the next segment's loads go out
-// once the last staging of the current one has read them) and serves every
-// target plane of the block it reaches (one, two or four): per (segment,
-// target) pass it is staged through LDS with that target's w, and one lane
-// per run sums eight moments of (a, bx)
-// weighted by f w and by w (product-sums as fused multiply-adds).  The
+// block of dual planes.  For every dual vx row the wave walks the nine
+// dual-plane row segments; each is loaded from memory once into registers (the
+// next segment's loads go out once the last staging of the current one has read
+// them) and serves every target plane of the block it reaches (one, two or
+// four): per (segment, target) pass it is staged through LDS with that target's
+// w, and one lane per run sums eight moments of (a, bx) weighted by f w and by w
+// (product-sums as fused multiply-adds).  The
 // corners of the runs go to the target rows jd (lower) and jd + 1 (upper, kept
 // until the next dual row).  Sums are FP64: a run's sums are independent of
 // the order of its markers (FixGrid in avl_device.h) and everything above
@@ -32,7 +32,7 @@
 // runs (4 markers a cell: about 10), at two to three waves a SIMD.  So what
 // counts is that every SIMD has its waves to the end: the chunks of vx rows
 // (make_geo) took 64 x 24^3 FP64, ppc 4, 144 waves as one chunk, from 736 to
-// 112 us, and 256 x 64^3 FP32, ppc 4, from 6.00 to 5.48 ms.  Staging each
+// 112 us, and 256 x 64^3 FP32, ppc 4, from 5.89 to 5.30 ms.  Staging each
 // segment once for all its targets (raw, weights formed per run) cut the LDS
 // traffic to a third but moved the conversions and weights into the runs'
 // lanes: 6.9 to 7.7 ms; separate LDS arrays for w and f w 5.6 to 5.9 ms.

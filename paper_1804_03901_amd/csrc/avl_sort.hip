@@ -14,8 +14,8 @@
 //
 // Counting uses integer atomics only.  Consecutive markers of the previous
 // order land in few buckets after the push, so a wave (1D-1V) or a block
-// (1D-3V, and FP64 kicks of velocity cells) counts its markers in an LDS window of
-// the buckets it expects and issues one global atomic per touched bucket.  The
+// (1D-3V, FP64 kicks of velocity cells, and the scatter of large dense FP64 sorts)
+// counts its markers in an LDS window of the buckets it expects and issues one global atomic per touched bucket.  The
 // windows follow the markers: by the drift and kick of the tile, by the kick
 // column by column, or over the planes a gyration reaches.  Markers that miss
 // the window use one global atomic each, those of the overflow bucket one a
