@@ -343,8 +343,8 @@ def main():
                     help="also time the batch's instances one after another (default on)")
     ap.add_argument("--batch-steps", type=int, default=100)
     ap.add_argument("--cpu-cores", type=int, default=16,
-                    help="most processes of the all-core CPU baseline (nproc of the host, capped here: a GPU "
-                         "box grants one GPU's share of 16 CPUs; 0: skip)")
+                    help="most processes of the all-core CPU baseline (nproc of the host, capped here at "
+                         "one GPU's share of 16 CPUs; 0: skip)")
     ap.add_argument("--cpu-child", action="store_true", help=argparse.SUPPRESS)
     args = ap.parse_args()
     if args.cpu_child:
@@ -465,7 +465,7 @@ def main():
                 "cpu": cpu_model(),
                 "sample": f"{procs} independent copies of the full {w.n_markers}-marker workload, "
                           f"{steps_all} steps each after the initial solve ({secs_all:.1f} s), FP64, one thread each "
-                          f"(nproc {nproc}; at most {args.cpu_cores} processes, the CPU share a GPU box grants)"}
+                          f"(nproc {nproc}; at most {args.cpu_cores} processes, the CPU share of one GPU)"}
     print(json.dumps(out), flush=True)
 
 
