@@ -196,7 +196,11 @@ int avl_poisson(avl_handle* h, const double* rho, double* E_out, double* W_out);
  * rho^{n+1}, solve E^{n+1}.  diag_out (may be NULL) receives 2*nsteps doubles,
  * per step the field energy W and the amplitude (2/nx)|sum_i E_i e^{-2 pi i
  * i/nx}| of the longest-wavelength mode of E (Sec. 4.2).  AVL_ESTATE unless
- * the handle holds a current field (after avl_init, avl_poisson or a step). */
+ * the handle holds a current field (after avl_init, avl_poisson or a step).
+ * FP64 1D-1V: whether the sort's kernels are those for kicks of a velocity cell
+ * or more is decided once, by the field of the loaded markers.  It changes no
+ * result; a run whose kicks grow to several cells later steps more slowly (512 x
+ * 6600 cells, 13.5M markers, kicks of 8 cells: 702 us a step against 446). */
 int avl_step(avl_handle* h, int32_t nsteps, double* diag_out);
 
 /* Same as avl_step, replaying a HIP graph of one step captured on first use
